@@ -1,6 +1,7 @@
 // abi.hip -- status handling, block-hash chains and table construction.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <mutex>
 #include <stdarg.h>
 #include <stdio.h>
@@ -47,6 +48,22 @@ int32_t* status_word()
     return g_status_addr[dev];
 }
 
+// The current device's compute units, asked for once per device (0 if unknown).
+int32_t compute_units()
+{
+    static std::atomic<int32_t> known[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+    int32_t n = known[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        int v = 0;
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+        n = v;
+        known[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
 EpisodeLayout episode_layout(int32_t W, int32_t cache_blocks, int32_t max_blocks, int32_t max_conv,
                              int32_t max_routes)
 {
@@ -66,7 +83,7 @@ EpisodeLayout episode_layout(int32_t W, int32_t cache_blocks, int32_t max_blocks
     L.off_queue = o;   o = align_up(o + ((size_t)max_conv + 1) * sizeof(int32_t), 256);
     L.off_next = o;    o = align_up(o + ((size_t)max_conv + 1) * sizeof(int32_t), 256);
     L.off_hist = o;    o = align_up(o + ((size_t)max_routes + 1) * 2 * sizeof(int32_t), 256);
-    L.off_replay = o;  o = align_up(o + (size_t)kEpisodeThreads * 16, 256);
+    L.off_replay = o;  o = align_up(o + (size_t)kEpisodeThreadsMax * 16, 256);
     L.off_later = o;   o = align_up(o + ((size_t)max_conv + 1) * sizeof(int32_t), 256);
     L.off_ctl = o;     o = align_up(o + 256, 256);     // launch control (episode queue counter)
     L.off_runs = o;    o = align_up(o + L.runs * sizeof(RunSlot), 256);

@@ -1,6 +1,7 @@
 // episode.hip -- independent sequential routing episodes, one workgroup each.
 //
-// Per episode the workgroup (256 threads, 4 wavefronts) keeps in LDS the
+// Per episode the workgroup (256 threads, or 512 when it has a compute unit to
+// itself; wavefront 0 decides, the others write and search) keeps in LDS the
 // worker loads A_j, the LRU bookkeeping of every worker, the in-flight routes
 // of the last H steps and the controller's load window.  Each worker's cached
 // blocks live in HBM as an open-addressing table of 16-byte slots (key, stamp)
@@ -26,7 +27,7 @@
 //      prefixes, a later request b'' then has overlap
 //      max(o[b''][sigma], lcp(b'', b)) on sigma and unchanged overlaps
 //      elsewhere.  The cache writes themselves are deferred;
-//   C. meanwhile the other three wavefronts apply the touches and inserts of
+//   C. meanwhile the other wavefronts apply the touches and inserts of
 //      the decided routes, a few routes per claim.
 // A route that must evict (and every route in scan mode, where caches need
 // not be prefix-closed) stops phase B: once every decided route's writes are
@@ -72,8 +73,7 @@
 
 namespace rk {
 
-constexpr int NT = kEpisodeThreads;
-constexpr int NW = NT / 64;
+constexpr int kMaxWaves = kEpisodeThreadsMax / 64;
 constexpr int kMaxBatch = 64;       // routes per batch (at most one wavefront of lanes)
 constexpr int32_t kMoreTurns = 0x40000000;   // flag on an in-flight conversation index: it has a next turn
 
@@ -111,13 +111,17 @@ struct EpShared {
     uint32_t new_head, first_kept, adv;
     int64_t ev_row, ev_total;
     unsigned long long digest, rb_mask;
-    int32_t wtot[NW];
+    int32_t wtot[kMaxWaves];
 };
+
+// NT below: the threads of the episode's workgroup.
 
 // Exclusive rank of `flag` among the workgroup's threads (thread order) and the
 // total count.  Every thread of the workgroup must call it.
+template <int NT>
 __device__ __forceinline__ int32_t block_scan(bool flag, int32_t* wtot, int32_t& total)
 {
+    constexpr int NW = NT / 64;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const unsigned long long b = __ballot(flag);
     const int32_t rank = __popcll(b & ((1ull << lane) - 1ull));
@@ -137,8 +141,10 @@ __device__ __forceinline__ int32_t block_scan(bool flag, int32_t* wtot, int32_t&
 
 // Exclusive prefix sum of v over the workgroup's threads (thread order) and the
 // total.  Every thread of the workgroup must call it.
+template <int NT>
 __device__ __forceinline__ int32_t block_excl_sum(int32_t v, int32_t* wtot, int32_t& total)
 {
+    constexpr int NW = NT / 64;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     int32_t x = v;
 #pragma unroll
@@ -674,7 +680,7 @@ constexpr int KP = 4;   // batch pairs a thread searches together for their comm
 // thread issue the same loads from addresses chosen by masks (a finished
 // search reads the first group of the slots and the first chain hash again),
 // so that no branch separates them and all are in flight together.
-template <class Info, class Put>
+template <int NT, class Info, class Put>
 __device__ __forceinline__ void prefix_searches(int32_t n, const Info& info, const Put& put, const Slot* slots,
                                                 uint64_t S, const uint64_t* chains, uint16_t* list,
                                                 int32_t* nlist)
@@ -917,7 +923,7 @@ __device__ __forceinline__ void run_insert(RunSlot* rt, uint64_t rsmask, uint64_
 // that needs fewer reads the index's first pair or the first chain hash
 // again), so that no branch separates the KI items' loads and all of them are
 // in flight together; a wavefront skips a load that none of its lanes needs.
-template <class Info, class Put>
+template <int NT, class Info, class Put>
 __device__ __forceinline__ void run_searches(int32_t n, const Info& info, const Put& put, const RunSlot* rt,
                                              uint64_t rsmask, const uint64_t* chains, uint16_t* list,
                                              int32_t* nlist)
@@ -1123,7 +1129,7 @@ __device__ __forceinline__ void run_searches(int32_t n, const Info& info, const 
 // table and the bound.  Binary search when the tier's blocks form a prefix of
 // the chain (prefix-closed caches: stamps fall along a cached prefix), else a
 // scan from block 0.
-template <class Info, class Put>
+template <int NT, class Info, class Put>
 __device__ __forceinline__ void tier_searches(int32_t n, bool bsearch, const Info& info, const Put& put,
                                               const Slot* slots, uint64_t S)
 {
@@ -1247,7 +1253,7 @@ __global__ void episode_queue_init(int32_t* __restrict__ q)
     if (threadIdx.x == 0) *q = 0;
 }
 
-// Two waves per SIMD: two episodes share a CU (the sweep has more episodes than CUs).
+// Two waves per SIMD: two episodes of 256 threads share a CU, or one of 512 threads has it.
 // With one workspace per episode, workgroup x runs episode x.  With fewer
 // workspaces (n_slots < E), workgroup x owns workspace x and takes episodes from
 // the launch's queue counter in index order until none is left.  An episode
@@ -1574,9 +1580,10 @@ __device__ __noinline__ void lean_decide(const LeanCtx c_arg, LeanState* st_arg)
     st->tot[6] = tot6;
 }
 
-template <bool Queued>
+template <bool Queued, int NT>
 __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
 {
+    constexpr int NW = NT / 64;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ EpShared sh;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1755,7 +1762,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
             turns2 |= a.turn_off[gc0 + c + 1] - a.turn_off[gc0 + c] > 1 ? 1 : 0;
         }
         int32_t total;
-        const int32_t rank = block_scan(has, sh.wtot, total);
+        const int32_t rank = block_scan<NT>(has, sh.wtot, total);
         if (has) g_queue[qn + rank] = c;
         qn += total;
     }
@@ -1792,7 +1799,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                 }
             }
             int32_t total;
-            const int32_t rank = block_scan(live, sh.wtot, total);
+            const int32_t rank = block_scan<NT>(live, sh.wtot, total);
             if (live && (uint64_t)(cnt + rank) < scratch_cap) {
                 g_scratch[cnt + rank] = key;
                 g_scratch_f[cnt + rank] = fk;
@@ -1834,7 +1841,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
         __syncthreads();
     };
 
-    // ---- waves 1-3 while wavefront 0 decides (and wavefront 0 once it stops): claim the next
+    // ---- the other waves while wavefront 0 decides (and wavefront 0 once it stops): claim the next
     //      128 writes of the decided routes (sh.claimed counts writes, r_wend numbers them; a
     //      compare-and-swap) and apply them with the wave's 64 lanes, two each; stop once
     //      wavefront 0 has stopped and every decided write is claimed.  sh.decided and
@@ -1966,7 +1973,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                 }
             }
             int32_t total;
-            const int32_t rank = block_scan(live, sh.wtot, total);
+            const int32_t rank = block_scan<NT>(live, sh.wtot, total);
             const int32_t need = n - K;
             if (total >= need) {
                 if (live && rank == need - 1) sh.adv = pos + 1;
@@ -2012,8 +2019,8 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                     }
                 }
                 int32_t n_r, ptot;
-                const int32_t rank = block_scan(P > 0, sh.wtot, n_r);
-                const int32_t off = block_excl_sum(P, sh.wtot, ptot);
+                const int32_t rank = block_scan<NT>(P > 0, sh.wtot, n_r);
+                const int32_t off = block_excl_sum<NT>(P, sh.wtot, ptot);
                 if (P > 0) {
                     r_off[rank] = off;
                     r_cbs[rank] = cb;
@@ -2060,7 +2067,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
 #pragma unroll
                         for (int u = 0; u < kRU; ++u) {
                             int32_t nl;
-                            const int32_t lr = block_scan(last[u], sh.wtot, nl);
+                            const int32_t lr = block_scan<NT>(last[u], sh.wtot, nl);
                             if (last[u]) {
                                 const uint32_t ns = (uint32_t)(live + lr);
                                 tk[sl[u]].stamp = ns;
@@ -2130,7 +2137,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
             int64_t cb;
             route_of(base + tid, P, cb, cv);
             int32_t ptot;
-            block_excl_sum(P, sh.wtot, ptot);
+            block_excl_sum<NT>(P, sh.wtot, ptot);
             T += ptot;
         }
         if (T > (int64_t)R) return false;
@@ -2143,12 +2150,12 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
             int64_t cb;
             route_of(c * NT + tid, P, cb, cv);
             int32_t n_r, ptot, ltot;
-            const int32_t rank = block_scan(P > 0, sh.wtot, n_r);
+            const int32_t rank = block_scan<NT>(P > 0, sh.wtot, n_r);
             const int32_t D = multi_turn && P > 0 ? m_P[cv] : 0;   // blocks touched again later
-            const int32_t off = block_excl_sum(P, sh.wtot, ptot);
+            const int32_t off = block_excl_sum<NT>(P, sh.wtot, ptot);
             int32_t loff = off;
             ltot = ptot;
-            if (multi_turn) loff = block_excl_sum(P - min(P, D), sh.wtot, ltot);
+            if (multi_turn) loff = block_excl_sum<NT>(P - min(P, D), sh.wtot, ltot);
             if (P > 0) {
                 r_off[rank] = loff;
                 r_cbs[rank] = cb;
@@ -2304,7 +2311,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                 }
             }
             int32_t total;
-            const int32_t rank = block_scan(cand, sh.wtot, total);
+            const int32_t rank = block_scan<NT>(cand, sh.wtot, total);
             const bool gone = cand && rank < rem;
             if (gone) {
                 tk[sl].stamp = kTomb;
@@ -2346,7 +2353,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
             const unsigned long long st = __ballot(lane < W && s_stamped[lane] != 0 && (j < 0 || lane == j));
             const unsigned long long lz = __ballot(lane < W && s_stamped[lane] == 0 && (j < 0 || lane == j));
             if (st)
-                prefix_searches(
+                prefix_searches<NT>(
                     n,
                     [&](int32_t i, const uint64_t*& ch, int32_t& P, int32_t& jj, uint64_t& h0) {
                         const int32_t b = b_lo + i / per;
@@ -2358,7 +2365,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                     },
                     put, g_slots, S, a.chains, l_items, &sh.nlist);
             if (lz)
-                run_searches(
+                run_searches<NT>(
                     n,
                     [&](int32_t i, const uint64_t*& ch, int32_t& P, int32_t& jj, uint64_t& h0) {
                         const int32_t b = b_lo + i / per;
@@ -2433,7 +2440,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
     auto tier_search = [&](int32_t b_lo, int32_t nb, int32_t j) {
         const int32_t per = j < 0 ? W : 1;
         const int32_t n = (nb - b_lo) * per;
-        tier_searches(
+        tier_searches<NT>(
             n, !scan,
             [&](int32_t i, const uint64_t*& ch, int32_t& hi, int32_t& jj, uint32_t& bound) {
                 const int32_t b = b_lo + i / per;
@@ -2448,7 +2455,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
             },
             g_slots, S);
         __syncthreads();
-        tier_searches(
+        tier_searches<NT>(
             n, !scan,
             [&](int32_t i, const uint64_t*& ch, int32_t& hi, int32_t& jj, uint32_t& bound) {
                 const int32_t b = b_lo + i / per;
@@ -2590,9 +2597,9 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
         more = (int64_t)k + 1 < tb1 - tb0;
     };
     int32_t nb_cur = 0;            // routes of the batch being decided
-    // Waves 1-3: every (request, worker) overlap of the next batch (all workers add runs), by the
+    // Waves 1 .. NW-2: every (request, worker) overlap of the next batch (all workers add runs), by the
     // run-index search of run_searches: a first probe of block 0 settles the misses and lists the
-    // rest; once the three waves have listed theirs, the listed items are searched with KI slots
+    // rest; once these waves have listed theirs, the listed items are searched with KI slots
     // per thread, each slot taking the next listed item when its search ends.
     auto job_search_part = [&]() {
         enum : int32_t { DONE = 0, HASH = 1, LOOK = 2, CMP = 3, CKPT = 4 };
@@ -2903,7 +2910,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
         }
     };
 
-    // the next batch's overlaps, computed by waves 1-3 while wavefront 0 decides this batch
+    // the next batch's overlaps, computed by the other waves while wavefront 0 decides this batch
     // (run-index searches against the caches as this batch found them); nx_ready: they are
     // complete and this batch had no eviction, compaction or epoch stop, so the caches grew by
     // this batch's chains only
@@ -3623,6 +3630,13 @@ extern "C" int rk_simulate_episodes(const rk_episode_batch* b, const rk_episode_
     a.ws = (unsigned char*)workspace;
     a.L = L;
     a.status = st;
+    // a workgroup that has a compute unit to itself takes 512 threads: the same registers per
+    // thread as two workgroups of 256, and every phase between the decisions (the deferred writes,
+    // the recency rebuilds, the evictions, the searches: rounds of dependent loads, as many at a
+    // time as there are lanes) takes fewer rounds.  Multi-turn steps, 256 against 512 threads: 64
+    // LRU episodes 35.7 / 31.2 ms, 8 with frequency eviction 75.0 / 56.8 ms, 8 with tiers 168.8 /
+    // 155.5 ms.  With more episodes than compute units two workgroups of 256 share one.
+    const bool wide = n_slots <= compute_units();
     // LDS: worker state, in-flight routes, controller window, then the batch arrays of the largest
     // batch that fits in 76 KiB (two episodes can then share a CU)
     size_t o = 0;
@@ -3633,7 +3647,7 @@ extern "C" int rk_simulate_episodes(const rk_episode_batch* b, const rk_episode_
     a.lds_u = (uint32_t)o;
     o = align_up(o + (size_t)b->max_ctrl_window * 8, 16);
     a.lds_roff = (uint32_t)o;
-    o = align_up(o + (size_t)kEpisodeThreads * 4, 16);
+    o = align_up(o + (size_t)(wide ? kEpisodeThreadsMax : kEpisodeThreads) * 4, 16);
     a.lds_batch = (uint32_t)o;
     const size_t limit = 76 * 1024;
     int32_t NB = kMaxBatch;
@@ -3651,7 +3665,13 @@ extern "C" int rk_simulate_episodes(const rk_episode_batch* b, const rk_episode_
         rc = hip_check(hipGetLastError(), "rk_simulate_episodes queue init");
         if (rc) return rc;
     }
-    if (n_slots < b->E) hipLaunchKernelGGL(episode_kernel<true>, dim3((unsigned)n_slots), dim3(NT), lds, s, a);
-    else hipLaunchKernelGGL(episode_kernel<false>, dim3((unsigned)n_slots), dim3(NT), lds, s, a);
+    const dim3 grid((unsigned)n_slots), block((unsigned)(wide ? kEpisodeThreadsMax : kEpisodeThreads));
+    if (n_slots < b->E) {
+        if (wide) hipLaunchKernelGGL((episode_kernel<true, kEpisodeThreadsMax>), grid, block, lds, s, a);
+        else hipLaunchKernelGGL((episode_kernel<true, kEpisodeThreads>), grid, block, lds, s, a);
+    } else {
+        if (wide) hipLaunchKernelGGL((episode_kernel<false, kEpisodeThreadsMax>), grid, block, lds, s, a);
+        else hipLaunchKernelGGL((episode_kernel<false, kEpisodeThreads>), grid, block, lds, s, a);
+    }
     return hip_check(hipGetLastError(), "rk_simulate_episodes launch");
 }

@@ -239,6 +239,7 @@ __device__ __forceinline__ bool table_has(const uint64_t* __restrict__ t, uint64
 int fail(int status, const char* fmt, ...);                  // records rk_last_error
 int hip_check(hipError_t e, const char* what);
 int32_t* status_word();                                      // device address for the current device
+int32_t compute_units();                                     // of the current device
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline uint64_t next_pow2(uint64_t x)
 {
@@ -268,7 +269,8 @@ struct __align__(16) RunSlot {
 };
 constexpr int kCkptLog = 4;
 
-constexpr int kEpisodeThreads = 256;   // threads of an episode's workgroup
+constexpr int kEpisodeThreads = 256;      // threads of an episode's workgroup: several share a CU,
+constexpr int kEpisodeThreadsMax = 512;   // or one has a CU to itself
 
 // Episode workspace layout (bytes), shared by the size query and the launch.
 struct EpisodeLayout {
