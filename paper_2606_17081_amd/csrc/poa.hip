@@ -1,25 +1,46 @@
 // poa.hip -- PoA-hat per window of routes (frozen cost matrix, selfish sum and
 // the optimal capacity-constrained assignment) and per-episode ratios.
 //
-// OPT is computed by successive shortest paths: rows are added one at a time
-// and each is placed along a cheapest augmenting path, which keeps the partial
-// assignment optimal.  Because every replica of a worker column costs the
-// same, the residual graph collapses onto the W workers: moving an assigned
-// row r from worker a to worker b costs c[r][b] - c[r][a], so the edge a -> b
-// weighs the minimum of that over rows on a.  A path starts with the new row
-// on some worker and ends on a worker with spare capacity; Bellman-Ford over
-// the W nodes finds it (no negative cycles, since the partial assignment is
-// optimal).  Edge minima are kept across rows and recomputed only for workers
-// whose rows changed on the last path.  One wavefront solves one window; the
-// window's matrix lives in LDS when it fits, else in the workspace.  Lane y
-// keeps worker y's distance, predecessor and row count in registers, values
-// move between lanes by readlane and DPP, and the path is walked by the whole
-// wavefront in lockstep.  With few workers the idle lanes share the work: for
-// W <= 16 (W <= 32) the rows (halves) of the wavefront each relax from a part
-// of the workers, and the edges that lost their argmin row are recomputed by
-// groups of lanes side by side.  Windows are dispatched longest first (a
-// bucket sort by size class), since the longest ones set the length of the
-// launch.
+// Because every replica of a worker column costs the same, the residual graph
+// of the assignment collapses onto the W workers: moving an assigned row r from
+// worker a to worker b costs c[r][b] - c[r][a], so the edge a -> b weighs the
+// minimum of that over rows on a.  OPT comes in three parts:
+//   1. Placement at fixed prices.  With K W close to m nearly every place is
+//      taken in the end, and what keeps a row off a cheap worker is the other
+//      rows: worker y is priced at its base cost's distance from the highest
+//      one, and every row goes to a worker of least cost + price while one has
+//      a place free (rows with fewer such workers first).  A placement where
+//      every row sits on a worker of least cost + price is optimal for the row
+//      counts it has, whatever the prices.  Only the prices equalise the base
+//      costs, so rows without overlap tie over all workers: 1-10% of the rows
+//      are left waiting (without prices over 80%: they all want the cheapest
+//      workers).
+//   2. Each waiting row along a shortest path from it to a worker with a free
+//      place (Bellman-Ford over the W nodes; no negative cycles, since the
+//      partial assignment is optimal for its counts, and a shortest path keeps
+//      it optimal for the counts it leads to, whichever free place it ends at).
+//   3. With free places left over (K W > m), units are moved along the shortest
+//      path that ends at one while that lowers the cost.
+// With many free places the prices are zero, and 1 and 2 are plain successive
+// shortest paths, which need no 3.
+//
+// Edge minima are built once the rows are placed and recomputed only for
+// workers whose rows changed on the last path.  One wavefront solves a window,
+// or four (poa_window_kernel); the window's matrix lives in LDS when it fits,
+// else in the workspace.  Lane y keeps worker y's distance, predecessor and row
+// count in registers, values move between lanes by readlane and DPP, and the
+// path is walked by the whole wavefront in lockstep.  With few workers the idle
+// lanes share the work: for W <= 16 (W <= 32) the rows (halves) of the
+// wavefront each relax from a part of the workers, and the edges that lost
+// their argmin row are recomputed by groups of lanes side by side.  Windows are
+// dispatched longest first (a bucket sort by size class), since the longest
+// ones set the length of the launch.
+//
+// A window is bound by the latency of its serial steps (a path takes 4-10 us,
+// a placement 0.05 us).  Measured against successive shortest paths from the
+// first row on, one wavefront per window: 128 windows of 512 rows x 64 workers
+// 5.82 -> 0.62 ms (four wavefronts; one 1.05 ms); the 163,200 windows of a
+// saturation sweep over 64 traces 5.0 -> 1.8 ms.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -28,7 +49,10 @@
 
 namespace rk {
 
-constexpr int PT = 64;   // threads per window
+constexpr int PT = 64;   // threads of a wavefront
+constexpr int kMat = 4;  // matrix entries a lane computes together
+// a row that is not placed yet, in place of its position: it waits for a path, or any worker is as good
+constexpr int32_t kPending = -2, kAnywhere = -3;
 
 struct PoaArgs {
     int32_t n_windows, max_window, W, kmax;
@@ -86,6 +110,25 @@ __device__ __forceinline__ void relax_from_row(double rot, double e, int32_t x, 
         bv = v;
         bx = x;
     }
+}
+
+// LDS writes of one wavefront made visible to its other lanes.
+__device__ __forceinline__ void wave_sync_poa()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Minimum over the wavefront.
+__device__ __forceinline__ uint32_t wave_min_u32_poa(uint32_t v)
+{
+    v = min(v, dpp32<kDppQuadSwap1>(v, v));
+    v = min(v, dpp32<kDppQuadSwap2>(v, v));
+    v = min(v, dpp32<kDppRowHalfMirror>(v, v));
+    v = min(v, dpp32<kDppRowMirror>(v, v));
+    const auto rl = [&](int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+    return min(min(rl(0), rl(16)), min(rl(32), rl(48)));
 }
 
 // Least (value, index) pair over the 64 lanes, by value and then by index;
@@ -186,16 +229,23 @@ __global__ __launch_bounds__(256) void poa_order_scatter_kernel(int32_t n_window
     }
 }
 
-// For W <= 16 the kernel is held to 80 registers (six waves per SIMD, 24 windows per CU, about what
-// the LDS allows) without spills: the saturation sweep's windows take 2% less time than at 85
-// registers (five waves); at 64 registers (eight waves) the spills cost more than the waves gain.
-template <bool LDSMAT, int WMAX>
-__global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ? 6 : 1))) void poa_window_kernel(
-    PoaArgs a)
+// WAVES wavefronts solve a window.  With one, W <= 16 is held to 80 registers (six waves per SIMD, 24
+// windows per CU, about what the LDS allows).  With four, the frozen matrix, the rows' least workers
+// and the first edge weights spread over them, wavefront 0 places the rows, and for W > 32 each
+// relaxes from 16 workers.
+template <bool LDSMAT, int WMAX, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((
+    amdgpu_waves_per_eu(WAVES == 1 && WMAX <= 16 ? 6 : 1))) void poa_window_kernel(PoaArgs a)
 {
+    constexpr int NTH = 64 * WAVES;
+    constexpr bool kSplit = WAVES > 1 && WMAX > 32;   // the relaxation is shared by the wavefronts
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int32_t sh_bad;
-    const int tid = threadIdx.x;
+    __shared__ int32_t sh_bad, sh_pend, sh_row;
+    __shared__ int32_t s_cnt[64];                     // rows on each worker once the rows are placed
+    __shared__ uint64_t s_least[WAVES > 1 ? NTH : 1];
+    __shared__ double s_bv[kSplit ? 2 * NTH : 1];     // best of each wavefront's workers, by round parity
+    __shared__ int32_t s_bx[kSplit ? 2 * NTH : 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int32_t W = a.W;
     int32_t* s_n = (int32_t*)(smem + a.lds_int);   // [W] window counts of the greedy assignment
     float* s_base = (float*)(s_n + W);               // [W]
@@ -237,17 +287,17 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
         }
         float* cm = LDSMAT ? (float*)(smem + a.lds_mat) : a.cm + r0 * W;
         // ---- frozen matrix
-        for (int32_t j = tid; j < W; j += PT) s_n[j] = 0;
-        for (int32_t pq = tid; pq < W * W; pq += PT) s_e[pq] = dinf();
+        for (int32_t j = tid; j < W; j += NTH) s_n[j] = 0;
+        for (int32_t pq = tid; pq < W * W; pq += NTH) s_e[pq] = dinf();
         if (tid == 0) sh_bad = 0;
         __syncthreads();
-        for (int32_t i = tid; i < m; i += PT) {
+        for (int32_t i = tid; i < m; i += NTH) {
             const int32_t sg = a.route_worker[r0 + i];
             if (sg >= 0 && sg < W) atomicAdd(&s_n[sg], 1);
             else sh_bad = 1;
         }
         __syncthreads();
-        for (int32_t j = tid; j < W; j += PT) {
+        for (int32_t j = tid; j < W; j += NTH) {
             const int32_t gap = a.p.C_cap - s_n[j];
             const float g = (float)(gap > 1 ? gap : 1);
             float gb = g;
@@ -255,12 +305,34 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
             s_base[j] = __fadd_rn(__fadd_rn(__fmul_rn(a.p.a, (float)s_n[j]), a.p.b), __fdiv_rn(a.p.d, gb));
         }
         __syncthreads();
-        for (int64_t idx = tid; idx < (int64_t)m * W; idx += PT) {
-            const int64_t i = idx / W;
-            const int32_t j = (int32_t)(idx - i * W);
-            const int32_t P = a.route_blocks[r0 + i];
-            const float oh = P > 0 ? __fdiv_rn((float)a.overlap[(r0 + i) * W + j], (float)P) : 0.0f;
-            cm[idx] = __fsub_rn(s_base[j], __fmul_rn(a.p.w_c, oh));
+        {
+            // kMat entries per thread at a time, their loads issued together; a thread's entry moves on by
+            // NTH entries, NTH / W rows and NTH % W workers
+            const int32_t n = m * W, di = NTH / W, dj = NTH % W;
+            int32_t i = tid / W, j = tid % W;
+            for (int32_t idx0 = tid; idx0 < n; idx0 += NTH * kMat) {
+                int32_t ov[kMat], P[kMat], jj[kMat];
+#pragma unroll
+                for (int u = 0; u < kMat; ++u) {
+                    const int32_t idx = idx0 + u * NTH;
+                    const bool in = idx < n;
+                    jj[u] = in ? j : 0;
+                    P[u] = a.route_blocks[r0 + (in ? i : 0)];
+                    ov[u] = a.overlap[r0 * W + (in ? idx : 0)];
+                    i += di;
+                    j += dj;
+                    if (j >= W) {
+                        j -= W;
+                        ++i;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < kMat; ++u) {
+                    const int32_t idx = idx0 + u * NTH;
+                    const float oh = P[u] > 0 ? __fdiv_rn((float)ov[u], (float)P[u]) : 0.0f;
+                    if (idx < n) cm[idx] = __fsub_rn(s_base[jj[u]], __fmul_rn(a.p.w_c, oh));
+                }
+            }
         }
         __syncthreads();
         const bool bad_rows = sh_bad != 0;
@@ -273,21 +345,165 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
             }
             continue;
         }
-        if (a.selfish) {
+        if (a.selfish && wave == 0) {
             const double s = window_sum(m, [&](int32_t i) { return (double)cm[(int64_t)i * W + a.route_worker[r0 + i]]; });
-            if (tid == 0) a.selfish[w] = s;
+            if (lane == 0) a.selfish[w] = s;
         }
-        // ---- successive shortest paths (lane y < W stands for worker y)
-        for (int32_t pq = tid; pq < W * W; pq += PT) s_er[pq] = -1;
+        // ---- OPT (lane y < W stands for worker y)
+        for (int32_t pq = tid; pq < W * W; pq += NTH) s_er[pq] = -1;
         __syncthreads();
-        const bool wl = tid < W;
+        const bool wl = lane < W;
         // lanes that share the recomputation of one edge: a power of two up to a row of 16 lanes,
         // so that DPP moves within rows combine them
         int32_t G = 1;
         while (G < 16 && 2 * G * W <= PT) G *= 2;
         int32_t cnt = 0;   // lane y: rows on worker y in the partial optimum
         bool placed_all = true;
-        for (int32_t i = 0; i < m; ++i) {
+        // The prices: worker y's base cost below the highest one, when nearly all of the K W places
+        // will be taken; else none.
+        const int32_t slack = K * W - m;
+        float bmax = wl ? s_base[lane] : -__builtin_inff(), bmin = wl ? s_base[lane] : __builtin_inff();
+#pragma unroll
+        for (int32_t sft = 1; sft < PT; sft <<= 1) {
+            bmax = fmaxf(bmax, __shfl_xor(bmax, sft));
+            bmin = fminf(bmin, __shfl_xor(bmin, sft));
+        }
+        const bool priced = 4 * (int64_t)slack <= m && bmax - bmin < __builtin_inff();
+        const double price = wl && priced ? (double)bmax - (double)s_base[lane] : 0.0;
+        // ---- rows on workers of least cost + price.  A lane takes a row and finds the workers
+        //      that attain its least; rows with fewer of them choose first, those with all of them
+        //      last; a row whose workers are all full waits.
+        uint64_t avail = __ballot(wl && cnt < K);
+        int32_t n_pend = 0;
+        auto place = [&](int32_t row, int32_t y) {
+            if (lane == y) {
+                s_mem[y * a.kmax + cnt] = (int16_t)row;
+                s_pos[row] = (int16_t)cnt;
+                ++cnt;
+            }
+            avail = __ballot(wl && cnt < K);
+        };
+        for (int32_t base0 = 0; base0 < m; base0 += NTH) {
+            const bool in = base0 + tid < m;
+            const float* crow = cm + (int64_t)(in ? base0 + tid : 0) * W;
+            uint64_t least = 0ull;
+            double lv = dinf();
+#pragma unroll 8
+            for (int32_t y = 0; y < W; ++y) {
+                const double v = (double)crow[y] + (priced ? (double)bmax - (double)s_base[y] : 0.0);
+                if (v < lv) {
+                    lv = v;
+                    least = 0ull;
+                }
+                if (v == lv) least |= 1ull << y;
+            }
+            if constexpr (WAVES > 1) {
+                s_least[tid] = least;
+                __syncthreads();
+            }
+            for (int32_t c = 0; c < (wave == 0 ? WAVES : 0); ++c) {
+                const int32_t base = base0 + 64 * c;
+                const bool here = base + lane < m;
+                if constexpr (WAVES > 1) least = s_least[64 * c + lane];
+                const uint32_t ways = (uint32_t)__popcll(least);
+                const bool any = ways == (uint32_t)W;
+                if (here) s_pos[base + lane] = (int16_t)(any ? kAnywhere : kPending);
+                uint64_t todo = __ballot(here && !any);
+                while (todo) {
+                    const bool mine = ((todo >> lane) & 1ull) != 0;
+                    const uint32_t fewest = wave_min_u32_poa(mine ? ways : 0xffffffffu);
+                    const uint64_t now = __ballot(mine && ways == fewest);
+                    todo &= ~now;
+                    for (uint64_t b = now; b; b &= b - 1) {
+                        const int k = __ffsll((unsigned long long)b) - 1;
+                        const uint64_t to = readlane64(least, k) & avail;
+                        if (to) place(base + k, __ffsll((unsigned long long)to) - 1);
+                        else ++n_pend;
+                    }
+                }
+            }
+            if constexpr (WAVES > 1) __syncthreads();
+        }
+        if (wave == 0) {
+            wave_sync_poa();
+            for (int32_t base = 0; base < m; base += 64) {
+                uint64_t now = __ballot(base + lane < m && s_pos[base + lane < m ? base + lane : 0] == kAnywhere);
+                for (; now; now &= now - 1)
+                    place(base + __ffsll((unsigned long long)now) - 1, __ffsll((unsigned long long)avail) - 1);
+            }
+            s_cnt[lane] = cnt;
+            if (lane == 0) sh_pend = n_pend;
+        }
+        __syncthreads();
+        n_pend = __builtin_amdgcn_readfirstlane(sh_pend);
+        // edge x -> z (mine: lane G z + g of it has to), the least c[r][z] - c[r][x] over the cx rows r
+        // on x, four rows per lane at a time, their loads issued before any is used
+        auto edge = [&](int32_t x, int32_t cx, bool mine) {
+            const int32_t z = lane / G, g = lane % G;
+            double best = dinf();
+            int32_t brow = 0x7fffffff;
+            if (mine) {
+                for (int32_t k0 = g; k0 < cx; k0 += 4 * G) {
+                    int32_t q[4];
+                    float cz[4], cxv[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int32_t k = k0 + u * G;
+                        q[u] = k < cx ? s_mem[x * a.kmax + k] : -1;
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int64_t row = q[u] >= 0 ? (int64_t)q[u] * W : 0;
+                        cz[u] = cm[row + z];
+                        cxv[u] = cm[row + x];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (q[u] >= 0) pick(best, brow, (double)cz[u] - (double)cxv[u], q[u]);
+                }
+            }
+            if (G >= 2) argmin_dpp_step<0xB1>(best, brow);    // quad_perm [1,0,3,2]
+            if (G >= 4) argmin_dpp_step<0x4E>(best, brow);    // quad_perm [2,3,0,1]
+            if (G >= 8) argmin_dpp_step<0x141>(best, brow);   // row_half_mirror
+            if (G >= 16) argmin_dpp_step<0x140>(best, brow);  // row_mirror
+            if (g == 0 && mine) {
+                s_e[x * W + z] = best;
+                s_er[x * W + z] = (int16_t)(brow == 0x7fffffff ? -1 : brow);
+            }
+        };
+        const bool balance = priced && slack > 0;
+        if (n_pend > 0 || balance) {
+            for (int32_t x = wave; x < W; x += WAVES) edge(x, s_cnt[x], lane / G < W && lane / G != x);
+            __syncthreads();
+        }
+        // ---- the waiting rows along shortest paths, then (with prices and free places) units moved
+        //      to free places while that lowers the cost
+        int32_t pbase = -64, moves = 0;
+        uint64_t pend = 0ull;
+        for (bool more = kSplit || wave == 0; more;) {
+            int32_t i = -1;            // the row to place, or -1 for a move
+            if (kSplit && wave > 0) {
+                __syncthreads();       // wavefront 0 has chosen
+                i = __builtin_amdgcn_readfirstlane(sh_row);
+                if (i < -1) break;
+            } else if (n_pend > 0) {
+                while (pend == 0ull) {
+                    pbase += 64;
+                    pend = __ballot(pbase + lane < m && s_pos[pbase + lane < m ? pbase + lane : 0] == kPending);
+                }
+                i = pbase + __ffsll((unsigned long long)pend) - 1;
+                pend &= pend - 1;
+                --n_pend;
+            } else if (!balance || moves++ >= m + W) {
+                more = false;
+            }
+            if constexpr (kSplit) {
+                if (wave == 0) {
+                    if (lane == 0) sh_row = more ? i : -2;
+                    __syncthreads();
+                }
+            }
+            if (!more) break;
             double dist;
             int32_t pred = -1;
             float c_row;   // lane y < W (row 0): the new row's cost on worker y
@@ -297,7 +513,7 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
                 // workers 4g .. 4g + 3 (lane (g, y) keeps the weights e[4g + p][y] in registers),
                 // and the rows' least (distance, worker) pairs are merged; worker order breaks ties
                 // as in a relaxation from every worker in turn
-                const int32_t g = tid >> 4, y = tid & 15;
+                const int32_t g = lane >> 4, y = lane & 15;
                 const bool wy = y < W;
                 double ec[4];
 #pragma unroll
@@ -305,9 +521,9 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
                     const int32_t x = 4 * g + p;
                     ec[p] = (x < W && wy) ? s_e[x * W + y] : dinf();
                 }
-                c_row = wy ? cm[(int64_t)i * W + y] : 0.0f;
+                c_row = wy && i >= 0 ? cm[(int64_t)i * W + y] : 0.0f;
                 dist = wy ? (double)c_row : dinf();
-                const int32_t src = (tid & ~15) | (4 * g + (tid & 3));   // position p < 4 of row g: dist[4g + p]
+                const int32_t src = (lane & ~15) | (4 * g + (lane & 3));   // position p < 4 of row g: dist[4g + p]
                 for (int32_t round = 0;; ++round) {
                     const long long db = __double_as_longlong(dist);
                     const uint32_t rlo = (uint32_t)__shfl((int)(uint32_t)db, src);
@@ -338,7 +554,7 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
                     pred = pb;
                     if (fell == 0ull) break;
                     if (round > W + 1) {
-                        if (tid == 0) atomicOr(a.status, RK_DEV_NO_CONVERGE);
+                        if (lane == 0) atomicOr(a.status, RK_DEV_NO_CONVERGE);
                         break;
                     }
                 }
@@ -346,7 +562,7 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
                 // the same with two halves of 32 lanes (16 < W <= 32): every half keeps dist[y] at
                 // position y, half h relaxes from workers 16h .. 16h + 15, each row of the half
                 // reading them through a copy that holds dist[16h + q] at position q
-                const int32_t hh = tid >> 5, y = tid & 31;
+                const int32_t hh = lane >> 5, y = lane & 31;
                 const bool wy = y < W;
                 double ec[16];
 #pragma unroll
@@ -354,9 +570,9 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
                     const int32_t x = 16 * hh + p;
                     ec[p] = (x < W && wy) ? s_e[x * W + y] : dinf();
                 }
-                c_row = wy ? cm[(int64_t)i * W + y] : 0.0f;
+                c_row = wy && i >= 0 ? cm[(int64_t)i * W + y] : 0.0f;
                 dist = wy ? (double)c_row : dinf();
-                const int32_t src = 48 * hh + (tid & 15);
+                const int32_t src = 48 * hh + (lane & 15);
                 for (int32_t round = 0;; ++round) {
                     const long long db = __double_as_longlong(dist);
                     const uint32_t rlo = (uint32_t)__shfl((int)(uint32_t)db, src);
@@ -399,17 +615,21 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
                     pred = pb;
                     if (fell == 0ull) break;
                     if (round > W + 1) {
-                        if (tid == 0) atomicOr(a.status, RK_DEV_NO_CONVERGE);
+                        if (lane == 0) atomicOr(a.status, RK_DEV_NO_CONVERGE);
                         break;
                     }
                 }
             } else {
-                // Bellman-Ford over the workers (Jacobi rounds): lane y keeps dist[y]
-                // and pred[y]; lane y's column of edge weights sits in registers
-                double ecol[WMAX];
+                // Bellman-Ford over the workers (Jacobi rounds): lane y keeps dist[y] and pred[y], and
+                // lane y's column of edge weights sits in registers; each wavefront has the distances
+                // and relaxes from WX of the workers, the wavefronts' least (distance, worker) pairs
+                // merged in worker order
+                constexpr int WX = WMAX / WAVES;
+                const int32_t x0 = WX * wave;
+                double ecol[WX];
 #pragma unroll
-                for (int32_t x = 0; x < WMAX; ++x) ecol[x] = (x < W && wl) ? s_e[x * W + tid] : dinf();
-                c_row = wl ? cm[(int64_t)i * W + tid] : 0.0f;
+                for (int32_t p = 0; p < WX; ++p) ecol[p] = (x0 + p < W && wl) ? s_e[(x0 + p) * W + lane] : dinf();
+                c_row = wl && i >= 0 ? cm[(int64_t)i * W + lane] : 0.0f;
                 dist = wl ? (double)c_row : dinf();
                 // workers to relax from: all in the first round, then those whose distance fell in
                 // the round before (from any other worker every candidate was tried already with
@@ -419,12 +639,28 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
                     double nd = dist;
                     int32_t pb = pred;
 #pragma unroll
-                    for (int32_t x = 0; x < WMAX; ++x) {
-                        if (x < W && ((relax >> x) & 1ull)) {
-                            const double v = lane_f64(dist, x) + ecol[x];
+                    for (int32_t p = 0; p < WX; ++p) {
+                        if (x0 + p < W && ((relax >> (x0 + p)) & 1ull)) {
+                            const double v = lane_f64(dist, x0 + p) + ecol[p];
                             if (wl && v < nd) {
                                 nd = v;
-                                pb = x;
+                                pb = x0 + p;
+                            }
+                        }
+                    }
+                    if constexpr (kSplit) {
+                        const int32_t half = (round & 1) * NTH;
+                        s_bv[half + tid] = nd;
+                        s_bx[half + tid] = pb;
+                        __syncthreads();
+                        nd = dist;
+                        pb = pred;
+#pragma unroll
+                        for (int32_t q = 0; q < WAVES; ++q) {
+                            const double v = s_bv[half + 64 * q + lane];
+                            if (v < nd) {
+                                nd = v;
+                                pb = s_bx[half + 64 * q + lane];
                             }
                         }
                     }
@@ -439,14 +675,22 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
                     }
                 }
             }
-            // target: least distance among workers with spare capacity (lowest index on ties)
-            double bd = wl && cnt < K ? dist : dinf();
-            int32_t t = wl && cnt < K ? tid : 0x7fffffff;
+            if (kSplit && wave > 0) continue;
+            // target: least distance + price (a move: least distance) among workers with spare capacity,
+            // lowest index on ties
+            double bd = wl && cnt < K ? (i >= 0 ? dist + price : dist) : dinf();
+            int32_t t = wl && cnt < K ? lane : 0x7fffffff;
             wave_argmin_f64<WMAX <= 16 ? 1 : WMAX <= 32 ? 2 : 4>(bd, t);
             if (t < 0 || t >= W) {   // no worker with spare capacity: impossible when K * W >= m
-                if (tid == 0) atomicOr(a.status, RK_DEV_NO_CONVERGE);
+                if (lane == 0) atomicOr(a.status, RK_DEV_NO_CONVERGE);
                 placed_all = false;
-                break;
+                n_pend = 0;
+                moves = m + W;
+                continue;
+            }
+            if (i < 0 && !(bd < 0.0)) {
+                moves = m + W;         // no move lowers the cost
+                continue;
             }
             // walk the path back from the target, moving one row per edge; lane h
             // records move h (losing worker, gaining worker, row)
@@ -459,18 +703,18 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
                 const int32_t r = s_er[x * W + y];
                 const int32_t kk = r >= 0 ? s_pos[r] : -1;
                 if (hops >= W - 1 || kk < 0 || kk >= cx || s_mem[x * a.kmax + kk] != r || cy >= a.kmax) {
-                    if (tid == 0) atomicOr(a.status, RK_DEV_NO_CONVERGE);
+                    if (lane == 0) atomicOr(a.status, RK_DEV_NO_CONVERGE);
                     break;
                 }
                 const int32_t last = s_mem[x * a.kmax + cx - 1];
-                if (tid == 0) {
+                if (lane == 0) {
                     s_mem[x * a.kmax + kk] = (int16_t)last;
                     s_pos[last] = (int16_t)kk;
                     s_mem[y * a.kmax + cy] = (int16_t)r;
                     s_pos[r] = (int16_t)cy;
                 }
-                cnt += (tid == y) - (tid == x);
-                if (tid == hops) {
+                cnt += (lane == y) - (lane == x);
+                if (lane == hops) {
                     hx = x;        // x lost r ...
                     hy = y;        // ... and y gained it
                     hr = r;
@@ -478,25 +722,25 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
                 y = x;
                 ++hops;
             }
-            {
+            if (i >= 0) {
                 const int32_t cy = __builtin_amdgcn_readlane(cnt, y);
                 if (cy < a.kmax) {
-                    if (tid == 0) {
+                    if (lane == 0) {
                         s_mem[y * a.kmax + cy] = (int16_t)i;
                         s_pos[i] = (int16_t)cy;
                     }
-                    cnt += tid == y;
-                } else if (tid == 0) {
+                    cnt += lane == y;
+                } else if (lane == 0) {
                     atomicOr(a.status, RK_DEV_NO_CONVERGE);
                 }
-                if (tid == hops) {
+                if (lane == hops) {
                     hx = -1;       // no loss
                     hy = y;        // the new row's worker gained row i
                     hr = i;
                 }
                 ++hops;
             }
-            __syncthreads();
+            wave_sync_poa();
             // ---- edge maintenance, e[x][z] = min over rows r on x of c[r][z] - c[r][x]:
             // the edges whose argmin row left x are recomputed over x's rows together
             // (lane G z + g scans x's rows g, g + G, ... for edge x -> z; the G lanes of
@@ -504,7 +748,7 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
             for (int32_t h = 0; h < hops; ++h) {
                 const int32_t x = __builtin_amdgcn_readlane(hx, h), r = __builtin_amdgcn_readlane(hr, h);
                 if (x < 0) continue;
-                const bool lz = wl && tid != x && s_er[x * W + tid] == r;
+                const bool lz = wl && lane != x && s_er[x * W + lane] == r;
                 const uint64_t lost = __ballot(lz);
                 if (lost == 0ull) continue;
                 const int32_t cx = __builtin_amdgcn_readlane(cnt, x);
@@ -513,75 +757,47 @@ __global__ __launch_bounds__(PT) __attribute__((amdgpu_waves_per_eu(WMAX <= 16 ?
                     const int32_t z1 = __ffsll((unsigned long long)lost) - 1;
                     double best = dinf();
                     int32_t brow = 0x7fffffff;
-                    for (int32_t k = tid; k < cx; k += PT) {
+                    for (int32_t k = lane; k < cx; k += 64) {
                         const int32_t q = s_mem[x * a.kmax + k];
                         pick(best, brow, (double)cm[(int64_t)q * W + z1] - (double)cm[(int64_t)q * W + x], q);
                     }
                     wave_argmin_f64(best, brow);
-                    if (tid == 0) {
+                    if (lane == 0) {
                         s_e[x * W + z1] = best;
                         s_er[x * W + z1] = (int16_t)(brow == 0x7fffffff ? -1 : brow);
                     }
                     continue;
                 }
-                const int32_t z = tid / G, g = tid % G;
-                const bool mine = z < W && z != x && s_er[x * W + z] == r;
-                double best = dinf();
-                int32_t brow = 0x7fffffff;
-                if (mine) {
-                    // four rows per lane at a time, their loads issued before any is used
-                    for (int32_t k0 = g; k0 < cx; k0 += 4 * G) {
-                        int32_t q[4];
-                        float cz[4], cxv[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int32_t k = k0 + u * G;
-                            q[u] = k < cx ? s_mem[x * a.kmax + k] : -1;
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int64_t row = q[u] >= 0 ? (int64_t)q[u] * W : 0;
-                            cz[u] = cm[row + z];
-                            cxv[u] = cm[row + x];
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-                            if (q[u] >= 0) pick(best, brow, (double)cz[u] - (double)cxv[u], q[u]);
-                    }
-                }
-                if (G >= 2) argmin_dpp_step<0xB1>(best, brow);    // quad_perm [1,0,3,2]
-                if (G >= 4) argmin_dpp_step<0x4E>(best, brow);    // quad_perm [2,3,0,1]
-                if (G >= 8) argmin_dpp_step<0x141>(best, brow);   // row_half_mirror
-                if (G >= 16) argmin_dpp_step<0x140>(best, brow);  // row_mirror
-                if (g == 0 && mine) {
-                    s_e[x * W + z] = best;
-                    s_er[x * W + z] = (int16_t)(brow == 0x7fffffff ? -1 : brow);
-                }
+                const int32_t z = lane / G;
+                edge(x, cx, z < W && z != x && s_er[x * W + z] == r);
             }
             for (int32_t h = 0; h < hops; ++h) {
                 const int32_t yg = __builtin_amdgcn_readlane(hy, h), r = __builtin_amdgcn_readlane(hr, h);
                 // the new row's costs are in registers already
                 const float cg = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(c_row), yg));
-                if (wl && tid != yg) {
+                if (wl && lane != yg) {
                     const double v = r == i ? (double)c_row - (double)cg
-                                            : (double)cm[(int64_t)r * W + tid] - (double)cm[(int64_t)r * W + yg];
-                    if (v < s_e[yg * W + tid]) {
-                        s_e[yg * W + tid] = v;
-                        s_er[yg * W + tid] = (int16_t)r;
+                                            : (double)cm[(int64_t)r * W + lane] - (double)cm[(int64_t)r * W + yg];
+                    if (v < s_e[yg * W + lane]) {
+                        s_e[yg * W + lane] = v;
+                        s_er[yg * W + lane] = (int16_t)r;
                     }
                 }
             }
-            __syncthreads();
+            wave_sync_poa();
         }
         if (tid == 0 && a.coord && !placed_all) a.coord[w] = __longlong_as_double(0x7ff8000000000000ll);
-        if (a.coord && placed_all) {
-            // lane y adds the rows of worker y in list order, then the W sums in worker order
+        if (a.coord && placed_all && wave == 0) {
+            // lane G y + g adds every G-th row of worker y, then the sums in lane order
+            const int32_t y = lane / G, yc = y < W ? y : 0;
+            const int32_t cy = __shfl(cnt, yc);
             double part = 0.0;
-            if (wl)
-                for (int32_t k = 0; k < cnt; ++k) part += (double)cm[(int64_t)s_mem[tid * a.kmax + k] * W + tid];
+            if (y < W)
+#pragma unroll 4
+                for (int32_t k = lane % G; k < cy; k += G) part += (double)cm[(int64_t)s_mem[y * a.kmax + k] * W + y];
             double sum = 0.0;
-            for (int32_t y = 0; y < W; ++y) sum += lane_f64(part, y);
-            if (tid == 0) a.coord[w] = sum;
+            for (int32_t l = 0; l < G * W; ++l) sum += lane_f64(part, l);
+            if (lane == 0) a.coord[w] = sum;
         }
         __syncthreads();
     }
@@ -613,13 +829,14 @@ extern "C" size_t rk_poa_workspace_size(int64_t n_rows, int32_t W)
            align_up(((size_t)n_rows + 1) * sizeof(int32_t), 256) + 256;
 }
 
-template <bool LDSMAT>
+template <bool LDSMAT, int WAVES>
 static void launch_windows(int32_t W, unsigned grid, size_t lds, hipStream_t s, const PoaArgs& a)
 {
-    if (W <= 8) hipLaunchKernelGGL((poa_window_kernel<LDSMAT, 8>), dim3(grid), dim3(PT), lds, s, a);
-    else if (W <= 16) hipLaunchKernelGGL((poa_window_kernel<LDSMAT, 16>), dim3(grid), dim3(PT), lds, s, a);
-    else if (W <= 32) hipLaunchKernelGGL((poa_window_kernel<LDSMAT, 32>), dim3(grid), dim3(PT), lds, s, a);
-    else hipLaunchKernelGGL((poa_window_kernel<LDSMAT, 64>), dim3(grid), dim3(PT), lds, s, a);
+    const dim3 g(grid), b(64 * WAVES);
+    if (W <= 8) hipLaunchKernelGGL((poa_window_kernel<LDSMAT, 8, WAVES>), g, b, lds, s, a);
+    else if (W <= 16) hipLaunchKernelGGL((poa_window_kernel<LDSMAT, 16, WAVES>), g, b, lds, s, a);
+    else if (W <= 32) hipLaunchKernelGGL((poa_window_kernel<LDSMAT, 32, WAVES>), g, b, lds, s, a);
+    else if constexpr (WAVES > 1) hipLaunchKernelGGL((poa_window_kernel<LDSMAT, 64, WAVES>), g, b, lds, s, a);
 }
 
 // Argument checks shared by rk_poa_estimate and rk_poa_estimate_noalloc;
@@ -718,8 +935,17 @@ static int poa_launch(int32_t n_windows, const int64_t* win_off, int32_t n_episo
         // up to 2^17 workgroups, each looping over the windows a grid-stride apart (2^16: 0.9% slower on
         // the saturation sweep's 652,800 windows; one workgroup per window: no faster)
         unsigned grid = (unsigned)(n_windows < 131072 ? n_windows : 131072);
-        if (lds_mat) launch_windows<true>(W, grid, o, s, a);
-        else launch_windows<false>(W, grid, o, s, a);
+        // four wavefronts per window where the windows leave the chip's SIMDs idle (128 windows of
+        // 512 rows x 64 workers: 1.05 ms with one, 0.62 ms with four) and a window has enough entries
+        // to spread, and always for W > 32, where one wavefront's 64 edge weights per lane would leave a SIMD one window
+        const bool four = W > 32 || (n_windows <= 2 * compute_units() && (int64_t)max_window * W >= 2048);
+        if (lds_mat) {
+            if (four) launch_windows<true, 4>(W, grid, o, s, a);
+            else launch_windows<true, 1>(W, grid, o, s, a);
+        } else {
+            if (four) launch_windows<false, 4>(W, grid, o, s, a);
+            else launch_windows<false, 1>(W, grid, o, s, a);
+        }
         int rc = hip_check(hipGetLastError(), "rk_poa_estimate window launch");
         if (rc) return rc;
     }

@@ -50,3 +50,35 @@ def test_workgroup_widths(gpu, orc):
         for k, e in enumerate(order):
             for key, v in ref[e].items():
                 assert np.array_equal(got[k][key], v), (label, e, key)
+
+
+@pytest.mark.parametrize("W,m,spare", [(1, 9, 0), (3, 64, 0), (6, 32, 0), (6, 300, 40), (16, 8, 0), (16, 65, 3),
+                                       (16, 256, 0), (16, 256, 4), (16, 256, 20), (32, 255, 1), (33, 130, 0),
+                                       (64, 64, 0), (64, 200, 1), (64, 512, 0)])
+@pytest.mark.parametrize("levels", [(0.0,), (0.0, 0.5), (0.0, 0.1, 0.3, 0.35, 0.7, 1.0)])
+def test_poa_free_places(gpu, orc, W, m, spare, levels):
+    """The optimum starts from priced placements when nearly all of the K W places are taken and
+    without prices otherwise; spare adds places to K = ceil(m / W).  Overlaps from few levels tie
+    whole rows, and workers of very unequal counts make the prices matter."""
+    torch, rk = gpu
+    rng = np.random.default_rng([W, m, spare, len(levels)])
+    K = -(-m // W) + spare
+    n = 3 * m
+    P = rng.integers(1, 300, n).astype(np.int32)
+    am = np.minimum(rng.integers(0, W, n), rng.integers(0, W, n)).astype(np.int32)
+    ov = np.floor(rng.choice(levels, size=(n, W)) * P[:, None]).astype(np.int32)
+    ov[m: 2 * m] = ov[m: 2 * m, :1]                    # a window of rows cached alike everywhere
+    up, pp = rk.to_device, dict(wl.POA_PARAMS)
+    sel, coo = (torch.zeros(3, dtype=torch.float64, device="cuda") for _ in range(2))
+    hat = torch.zeros(1, dtype=torch.float64, device="cuda")
+    params = rk.PoaParams(pp["a"], pp["b"], pp["d"], pp["beta"], pp["C_cap"], pp["w_c"], K)
+    ws = torch.empty(rk.poa_workspace_size(n, W), dtype=torch.uint8, device="cuda")
+    rk.poa_estimate(up(np.arange(0, n + 1, m, dtype=np.int64)), up(np.array([0, 3], np.int64)), n, m, W, up(am), up(ov),
+                    up(P), params, sel, coo, hat, ws)
+    torch.cuda.synchronize()
+    assert rk.device_status(reset=True) == 0
+    for w in range(3):
+        r = slice(w * m, (w + 1) * m)
+        s, c, _ = orc.poa_window(am[r], ov[r], P[r], W, K=K, **pp)
+        # sums of at most 512 fp32 costs in fp64 on both sides
+        assert float(sel[w]) == pytest.approx(s, rel=1e-13) and float(coo[w]) == pytest.approx(c, rel=1e-13)
