@@ -228,6 +228,90 @@ __global__ __launch_bounds__(kChainWG) void chain_kernel(int64_t n_seq, const in
     }
 }
 
+// FNV-1a and chain of few sequences, a workgroup per sequence.  What bounds a
+// small call is the chain, one splitmix64 step after another; a wavefront that
+// chains one sequence does it in scalar registers (about 28 scalar
+// instructions a block), with no memory access in between: wavefront 0 takes 64
+// block values from LDS, one per lane, chains them by readlane and keeps the
+// results in the lanes for one coalesced store, while the other wavefronts hash
+// the blocks kFewSpan further on.  A block takes 73 ns along the chain
+// (lane-per-sequence: about 0.4 us, its loads and stores in between), but a
+// CU's scalar unit chains no more than 25 G blocks/s over the chip, so it is
+// the path of up to kFewSeqs sequences (a workgroup / a lane each, 128 blocks
+// on average: 4,096 sequences 61 / 118 us, 8,192 98 / 128, 16,384 169 / 147;
+// 600 blocks: 271 / 451, 422 / 509, 737 / 700).
+constexpr int64_t kFewSeqs = 8192;
+constexpr int kFewThreads = 256;
+constexpr int kFewSpan = kFewThreads;    // blocks hashed ahead of the chain
+
+__device__ __forceinline__ uint64_t block_fnv(const int32_t* __restrict__ tk)
+{
+    uint64_t h = 0xcbf29ce484222325ull;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) h = fnv_word(h, (uint32_t)tk[q]);
+    return h;
+}
+
+__global__ __launch_bounds__(kFewThreads) void hash_few_kernel(int64_t n_seq, const int32_t* __restrict__ tokens,
+                                                               const int64_t* __restrict__ tok_off,
+                                                               const int64_t* __restrict__ chain_off,
+                                                               uint64_t* __restrict__ chains, int32_t* status)
+{
+    __shared__ uint64_t s_f[2][kFewSpan];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int64_t s = blockIdx.x; s < n_seq; s += gridDim.x) {
+        const int64_t t0 = tok_off[s], t1 = tok_off[s + 1];
+        const int64_t c0 = chain_off[s], c1 = chain_off[s + 1];
+        if (t1 < t0 || c1 < c0) {
+            if (tid == 0) atomicOr(status, RK_DEV_BAD_OFFSETS);
+            continue;
+        }
+        const int64_t nb = c1 - c0, avail = (t1 - t0) / 16;
+        if (nb > avail && tid == 0) atomicOr(status, RK_DEV_SHORT_INPUT);
+        const int64_t n = nb < avail ? nb : avail;
+        for (int64_t k = n + tid; k < nb; k += kFewThreads) chains[c0 + k] = 0ull;
+        const int32_t* __restrict__ tk = tokens + t0;
+        if (tid < n) s_f[0][tid] = block_fnv(tk + 16 * (int64_t)tid);
+        __syncthreads();
+        uint64_t h = 0;
+        int cur = 0;
+        for (int64_t k0 = 0; k0 < n; k0 += kFewSpan) {
+            if (wave > 0) {
+                for (int x = tid - 64; x < kFewSpan; x += kFewThreads - 64) {
+                    const int64_t k = k0 + kFewSpan + x;
+                    if (k < n) s_f[cur ^ 1][x] = block_fnv(tk + 16 * k);
+                }
+            } else {
+                for (int64_t k1 = k0; k1 < k0 + kFewSpan && k1 < n; k1 += 64) {
+                    const int m = (int)(n - k1 < 64 ? n - k1 : 64);
+                    const uint64_t f = s_f[cur][(int)(k1 - k0) + lane];
+                    int lo = 0, hi = 0;
+                    // lane x keeps the value (the lane comes from m0: a VALU instruction reads one scalar)
+                    auto step = [&](int x) {
+                        h = chain_next(h, readlane64(f, x));
+                        asm("s_mov_b32 m0, %4\n\tv_writelane_b32 %0, %2, m0\n\tv_writelane_b32 %1, %3, m0"
+                            : "+v"(lo), "+v"(hi)
+                            : "s"((uint32_t)h), "s"((uint32_t)(h >> 32)), "s"(x)
+                            : "m0");
+                    };
+                    int x = 0;
+                    for (; x + 4 <= m; x += 4) {
+                        step(x);
+                        step(x + 1);
+                        step(x + 2);
+                        step(x + 3);
+                    }
+                    for (; x < m; ++x) step(x);
+                    if (lane < m) chains[c0 + k1 + lane] = ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
+                }
+            }
+            __syncthreads();
+            cur ^= 1;
+        }
+    }
+}
+
 // ------------------------------------------------------------------ tables
 
 __global__ __launch_bounds__(256) void table_clear_kernel(uint64_t* __restrict__ t, uint64_t n)
@@ -310,6 +394,11 @@ int rk_hash_chains(int64_t n_seq, const int32_t* tokens, const int64_t* tok_off,
     int32_t* st = status_word();
     if (!st) return fail(RK_EHIP, "rk_hash_chains: no status word");
     hipStream_t s = (hipStream_t)stream;
+    if (n_seq <= kFewSeqs) {
+        hipLaunchKernelGGL(hash_few_kernel, dim3((unsigned)n_seq), dim3(kFewThreads), 0, s, n_seq, tokens, tok_off,
+                           chain_off, chains, st);
+        return hip_check(hipGetLastError(), "rk_hash_chains launch");
+    }
     const int64_t waves_per_block = 4;
     int64_t blocks = (n_seq + waves_per_block - 1) / waves_per_block;
     if (blocks > 65536) blocks = 65536;

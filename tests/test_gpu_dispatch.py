@@ -82,3 +82,31 @@ def test_poa_free_places(gpu, orc, W, m, spare, levels):
         s, c, _ = orc.poa_window(am[r], ov[r], P[r], W, K=K, **pp)
         # sums of at most 512 fp32 costs in fp64 on both sides
         assert float(sel[w]) == pytest.approx(s, rel=1e-13) and float(coo[w]) == pytest.approx(c, rel=1e-13)
+
+
+@pytest.mark.parametrize("n_seq", [1, 3, 8192, 8193])
+def test_hash_few_and_many_sequences(gpu, orc, n_seq):
+    """Up to 8,192 sequences take a workgroup each, more a lane each: lengths around the spans of
+    64 and 256 blocks, partial blocks, token ranges at odd addresses and ranges that are too short."""
+    torch, rk = gpu
+    rng = np.random.default_rng(n_seq)
+    edges = np.array([0, 1, 2, 63, 64, 65, 255, 256, 257, 511, 512, 513, 700])
+    blocks = np.concatenate([edges, rng.integers(0, 40, n_seq)])[:n_seq] if n_seq > 3 else np.array([513, 700, 65])[:n_seq]
+    short = rng.random(n_seq) < 0.05                       # a token short of the last block
+    length = np.maximum(16 * blocks + rng.integers(0, 16, n_seq) - 16 * (short & (blocks > 0)), 0)
+    tok_off, chain_off = (np.concatenate([[3 * k], 3 * k + np.cumsum(x)]).astype(np.int64)
+                          for k, x in ((1, length), (0, blocks)))
+    tokens = rng.integers(-2 ** 31, 2 ** 31, int(tok_off[-1]) + 1).astype(np.int32)
+    ch = torch.full((int(chain_off[-1]) + 1,), 77, dtype=torch.int64, device="cuda")
+    rk.hash_chains(rk.to_device(tokens), rk.to_device(tok_off), rk.to_device(chain_off), ch)
+    torch.cuda.synchronize()
+    bits = rk.device_status(reset=True)
+    assert bits == (2 if (length // 16 < blocks).any() else 0)
+    got = rk.to_host_u64(ch)
+    assert got[-1] == 77
+    for s in range(n_seq):
+        n = int(min(blocks[s], length[s] // 16))
+        row = got[chain_off[s]: chain_off[s + 1]]
+        assert not row[n:].any()
+        ref = orc.hash_chains(tokens[tok_off[s]: tok_off[s] + 16 * n], [0, 16 * n], [n])
+        assert np.array_equal(row[:n], np.asarray(ref, np.uint64)[:n]), s
