@@ -107,10 +107,8 @@ struct LeanTag {
 
 struct EpShared {
     int32_t next_e, nlist, jn, jsync, jnext, jp, jpnext, jq, jqnext;
-    int32_t qhead, qsize, nb, event, ev_b, ins, remaining, ev, decided, claimed, stop, tdone, h1, h2;
-    uint32_t new_head, first_kept, adv;
-    int64_t ev_row, ev_total;
-    unsigned long long digest, rb_mask;
+    int32_t qhead, qsize, nb, event, ev_b, ins, decided, claimed, stop, tdone;
+    unsigned long long ev_total, dirty;
     int32_t wtot[kMaxWaves];
 };
 
@@ -1298,7 +1296,7 @@ __device__ __forceinline__ T wave_uniform(const T& v)
 // What the lean decision loop reads: LDS addresses of the episode's arrays, global arrays and
 // the episode's parameters.
 struct LeanCtx {
-    uint32_t sh, s_A, s_N, s_tail, s_live, s_used, s_head, s_stamped, s_stw, s_stP, s_stc, s_stepn, s_u;
+    uint32_t sh, s_A, s_N, s_tail, s_live, s_used, s_head, s_stamped, s_evb, s_stw, s_stP, s_stc, s_stepn, s_u;
     uint32_t r_P, r_c, r_k, o_cur, o_tab, lcp, r_sig, r_wend, r_stamp, r_ep, r_otab, r_step, r_reg, r_evc, r_evd;
     glb_p<int32_t> g_hist;
     glb_p<int32_t> g_next;
@@ -1337,7 +1335,7 @@ __device__ __noinline__ void lean_decide(const LeanCtx c_arg, LeanState* st_arg)
     const lds_p<int32_t> s_A = lds_at<int32_t>(c.s_A), s_N = lds_at<int32_t>(c.s_N);
     const lds_p<uint32_t> s_tail = lds_at<uint32_t>(c.s_tail), s_head = lds_at<uint32_t>(c.s_head);
     const lds_p<int32_t> s_live = lds_at<int32_t>(c.s_live), s_used = lds_at<int32_t>(c.s_used);
-    const lds_p<int32_t> s_stamped = lds_at<int32_t>(c.s_stamped);
+    const lds_p<int32_t> s_stamped = lds_at<int32_t>(c.s_stamped), s_evb = lds_at<int32_t>(c.s_evb);
     const lds_p<int32_t> s_stw = lds_at<int32_t>(c.s_stw), s_stP = lds_at<int32_t>(c.s_stP);
     const lds_p<int32_t> s_stc = lds_at<int32_t>(c.s_stc), s_stepn = lds_at<int32_t>(c.s_stepn);
     const lds_p<int64_t> s_u = lds_at<int64_t>(c.s_u);
@@ -1387,6 +1385,7 @@ __device__ __noinline__ void lean_decide(const LeanCtx c_arg, LeanState* st_arg)
     }
     // the overlaps of the next route (all earlier routes' raises are in)
     int32_t oj = lane < W && b_start < nb ? o_cur[b_start * W + lane] : 0;
+    uint64_t dirty = 0ull;   // workers over their capacity, not settled yet
     for (;;) {
         if (!step_open) {
             // release the routes of step s - H (their loads, in registers); queue their
@@ -1446,6 +1445,10 @@ __device__ __noinline__ void lean_decide(const LeanCtx c_arg, LeanState* st_arg)
         }
         const int32_t b = t - t0;
         if (b >= nb) break;
+        if (__builtin_expect((__ballot(oj > 0) & dirty) != 0ull, 0)) {
+            event = EV_FLUSH;
+            break;
+        }
         // one route: controller, cost of every worker, argmin
         const int32_t sb = s_slot * rps;
         bool active = false;
@@ -1461,6 +1464,10 @@ __device__ __noinline__ void lean_decide(const LeanCtx c_arg, LeanState* st_arg)
         }
         const uint32_t mn = ep_wave_min_u32(bits);
         const int32_t sg = __ffsll(__ballot(lane < W && bits == mn)) - 1;
+        if (__builtin_expect(((dirty >> sg) & 1ull) != 0, 0)) {
+            event = EV_FLUSH;
+            break;
+        }
         const int32_t osg = __builtin_amdgcn_readlane(oj, sg);
         const int32_t live_after = __builtin_amdgcn_readlane(rlive, sg) + P - osg;
         const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)rtail, sg);
@@ -1516,11 +1523,9 @@ __device__ __noinline__ void lean_decide(const LeanCtx c_arg, LeanState* st_arg)
             c.g_hist[2 * t] = rc & ~kMoreTurns;
             c.g_hist[2 * t + 1] = P | (sg << 16);
             c.g_next[rc & ~kMoreTurns] = __builtin_amdgcn_readlane(vk, b) + 1;
-            if (flush) {
-                sh->ev_b = b;
-                sh->ev_row = row;
-            }
+            if (flush) s_evb[sg] = b;
         }
+        if (flush) dirty |= 1ull << sg;
         u_tot += P;
         q_head = q_head + 1 == c.qcap ? 0 : q_head + 1;
         q_size -= 1;
@@ -1542,10 +1547,6 @@ __device__ __noinline__ void lean_decide(const LeanCtx c_arg, LeanState* st_arg)
         ++r_in_step;
         ep_wave_sync();
         if (lane == 0) __hip_atomic_store(&sh->decided, b + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (__builtin_expect(flush, 0)) {
-            event = EV_FLUSH;
-            break;
-        }
     }
     if (lane < W) {
         s_A[lane] = rA;
@@ -1558,6 +1559,7 @@ __device__ __noinline__ void lean_decide(const LeanCtx c_arg, LeanState* st_arg)
         sh->qhead = q_head;
         sh->qsize = q_size;
         sh->event = event;
+        sh->dirty = dirty;
         sh->tdone = t;
         __hip_atomic_store(&sh->stop, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
@@ -1618,6 +1620,12 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
     int32_t* s_n1 = (int32_t*)(s_b2 + W);                   //   live records from each boundary on
     int32_t* s_n2 = s_n1 + W;
     int32_t* s_stamped = s_n2 + W;                          // recency kept (else insert-only until the first eviction)
+    int32_t* s_evb = s_stamped + W;                         // an unsettled worker's route (batch index)
+    int32_t* s_evl = s_evb + W;                             // the unsettled workers
+    int32_t* s_h1 = s_evl + W;                              // its hits whose old records lay in G1's run,
+    int32_t* s_h2 = s_h1 + W;                               //   in G1 u G2's
+    uint32_t* s_sp = (uint32_t*)(s_h2 + W);                 // frequency eviction: no record before s_sp can go
+    uint32_t* s_spe = s_sp + W;                             //   in decay epoch s_spe - 1
     // in-flight routes of the last H steps, by step slot
     int32_t* s_stw = (int32_t*)(smem + a.lds_inflight);   // worker
     int32_t* s_stP = s_stw + a.max_inflight;               // prompt blocks
@@ -1749,6 +1757,10 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
         s_tail[tid] = 0;
         s_live[tid] = 0;
         s_used[tid] = 0;
+        s_h1[tid] = 0;
+        s_h2[tid] = 0;
+        s_sp[tid] = 0;
+        s_spe[tid] = 0;
     }
     for (int32_t i = tid; i < a.max_inflight; i += NT) s_stepn[i] = 0;
     int32_t qn = 0;
@@ -1771,10 +1783,9 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
         sh.qhead = 0;
         sh.qsize = qn;
         sh.ins = 0;
-        sh.h1 = 0;
-        sh.h2 = 0;
         sh.ev_total = 0;
         sh.tdone = 0;
+        sh.dirty = 0;
     }
     __syncthreads();
     const int32_t qcap = n_conv + 1;
@@ -1837,6 +1848,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
             s_n2[j] = min(s_n2[j], cnt);
             s_b1[j] = (uint32_t)(cnt - s_n1[j]);
             s_b2[j] = (uint32_t)(cnt - s_n2[j]);
+            s_spe[j] = 0;
         }
         __syncthreads();
     };
@@ -1847,7 +1859,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
     //      wavefront 0 has stopped and every decided write is claimed.  sh.decided and
     //      sh.claimed only grow until the workgroup synchronizes.
     auto writer = [&]() {
-        int my_ins = 0, my_h1 = 0, my_h2 = 0;
+        int my_ins = 0;
         for (;;) {
             const int32_t c = __builtin_amdgcn_readfirstlane(
                 __hip_atomic_load(&sh.claimed, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
@@ -1921,8 +1933,8 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                                                                     __HIP_MEMORY_SCOPE_WORKGROUP);
                         if (freq) freq_touch(&tk[u][sl[u]].fkey, ins[u] != 0, r_ep[b]);
                         if (tiers && !ins[u]) {       // a hit whose old record lay in a tier's run
-                            my_h1 += old >= s_b1[sg];
-                            my_h2 += old >= s_b2[sg];
+                            if (old >= s_b1[sg]) atomicAdd(&s_h1[sg], 1);
+                            if (old >= s_b2[sg]) atomicAdd(&s_h2[sg], 1);
                         }
                     }
                     g_log[(uint64_t)sg * R + (stamp & rmask)] = (uint32_t)sl[u];   // a failed insert logs an out-of-range slot
@@ -1943,54 +1955,68 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
             __builtin_amdgcn_s_sleep(2);
         }
         if (my_ins) atomicAdd(&sh.ins, my_ins);
-        if (my_h1) atomicAdd(&sh.h1, my_h1);
-        if (my_h2) atomicAdd(&sh.h2, my_h2);
     };
 
-    // ---- memory tiers: move worker j's boundary bk forward until the run from it holds at most K
-    //      live records (all threads)
-    auto advance = [&](uint32_t* bk, int32_t* nk, int32_t K, int32_t j) {
+    // ---- memory tiers: move worker j's two boundaries forward until the runs from them hold at most
+    //      K1 and K12 live records (one wavefront; 256 records from each boundary at a time)
+    auto advance = [&](int32_t j) {
+        constexpr int U = 4;
         const Slot* tk = g_slots + (uint64_t)j * S;
         const uint32_t* tl = g_log + (uint64_t)j * R;
-        uint32_t b = bk[j];
-        int32_t n = nk[j];
-        const uint32_t tail = s_tail[j];
-        while (n > K) {
-            if (b >= tail) {
-                if (tid == 0) atomicOr(a.status, RK_DEV_TABLE_FULL);
-                n = K;
-                break;
-            }
-            const uint32_t pos = b + (uint32_t)tid;
-            bool live = false;
-            if (pos < tail) {
-                const uint32_t sl = tl[pos & rmask];
-                if (sl < S) {
-                    uint64_t key;
-                    uint32_t st;
-                    load_slot(tk + sl, key, st);
-                    live = st == pos;
+        const uint32_t tail = __builtin_amdgcn_readfirstlane(s_tail[j]);
+        uint32_t bnd[2] = {(uint32_t)__builtin_amdgcn_readfirstlane(s_b1[j]),
+                           (uint32_t)__builtin_amdgcn_readfirstlane(s_b2[j])};
+        int32_t n[2] = {__builtin_amdgcn_readfirstlane(s_n1[j]), __builtin_amdgcn_readfirstlane(s_n2[j])};
+        const int32_t K[2] = {K1, K12};
+        while (n[0] > K[0] || n[1] > K[1]) {
+            uint32_t sl[2][U], st[2][U];
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t pos = bnd[q] + (uint32_t)(64 * u + lane);
+                    sl[q][u] = n[q] > K[q] && pos < tail ? tl[pos & rmask] : 0xFFFFFFFFu;
+                }
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int u = 0; u < U; ++u) st[q][u] = sl[q][u] < S ? tk[sl[q][u]].stamp : kTomb;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                if (n[q] <= K[q]) continue;
+                if (bnd[q] >= tail) {
+                    if (lane == 0) atomicOr(a.status, RK_DEV_TABLE_FULL);
+                    n[q] = K[q];
+                    continue;
+                }
+                int32_t need = n[q] - K[q];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t pos = bnd[q] + (uint32_t)(64 * u + lane);
+                    const unsigned long long m = __ballot(st[q][u] == pos);
+                    const int32_t c = __popcll(m);
+                    if (need > 0 && c >= need) {     // the last record to pass
+                        const unsigned long long l = __ballot(((m >> lane) & 1ull) &&
+                                                              __popcll(m & ((1ull << lane) - 1ull)) == need - 1);
+                        bnd[q] += (uint32_t)(64 * u + __ffsll(l));
+                        n[q] = K[q];
+                        need = -0x40000000;
+                    } else {
+                        need -= c;
+                    }
+                }
+                if (n[q] > K[q]) {
+                    n[q] = K[q] + need;
+                    bnd[q] = min(bnd[q] + 64u * U, tail);
                 }
             }
-            int32_t total;
-            const int32_t rank = block_scan<NT>(live, sh.wtot, total);
-            const int32_t need = n - K;
-            if (total >= need) {
-                if (live && rank == need - 1) sh.adv = pos + 1;
-                __syncthreads();
-                b = sh.adv;
-                n = K;
-            } else {
-                n -= total;
-                b = min(b + (uint32_t)NT, tail);
-            }
         }
-        __syncthreads();
-        if (tid == 0) {
-            bk[j] = b;
-            nk[j] = n;
+        if (lane == 0) {
+            s_b1[j] = bnd[0];
+            s_b2[j] = bnd[1];
+            s_n1[j] = n[0];
+            s_n2[j] = n[1];
         }
-        __syncthreads();
     };
 
     // ---- recency of worker j rebuilt from the episode's routes [0, t_end) (all threads): pass 1
@@ -2277,63 +2303,76 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
         return true;
     };
 
-    // ---- evict blocks of worker sg down to the capacity (all threads): live log records in log
-    //      (recency) order, under frequency eviction only those at frequency 1 in epoch ep; the
-    //      head moves to the first record left live
-    auto evict = [&](int32_t sg, uint32_t ep) {
+    // ---- evict blocks of worker sg down to the capacity (one wavefront, 512 records at a time): live
+    //      log records in log (recency) order, under frequency eviction only those at frequency 1
+    //      in epoch ep; the head moves to the first record left live.  A live record that is too
+    //      frequent in an epoch stays so until it is touched (and moves to the tail), so within an
+    //      epoch the next eviction starts behind the last one's.  The blocks evicted and the sum
+    //      of their digests go to the route at batch index b.
+    auto evict = [&](int32_t sg, uint32_t ep, int32_t b) {
+        constexpr int U = 8;
         Slot* tk = g_slots + (uint64_t)sg * S;
-        uint32_t* tl = g_log + (uint64_t)sg * R;
-        uint32_t head = s_head[sg];
-        while (sh.remaining > 0) {
-            const uint32_t tail = s_tail[sg];
-            const int32_t rem = sh.remaining;
+        const uint32_t* tl = g_log + (uint64_t)sg * R;
+        const uint32_t tail = __builtin_amdgcn_readfirstlane(s_tail[sg]);
+        const uint32_t head0 = __builtin_amdgcn_readfirstlane(s_head[sg]);
+        const int32_t gone0 = max(0, __builtin_amdgcn_readfirstlane(s_live[sg]) - a.cache);
+        int32_t rem = gone0;
+        uint32_t head = head0, new_head = head0, kept = 0xFFFFFFFFu;
+        if (freq && (uint32_t)__builtin_amdgcn_readfirstlane(s_spe[sg]) == ep + 1u)
+            head = max(head0, (uint32_t)__builtin_amdgcn_readfirstlane(s_sp[sg]));
+        const bool skipped = head > head0;
+        uint64_t dig = 0;
+        while (rem > 0) {
             if (head >= tail) {
-                __syncthreads();
-                if (tid == 0) {
-                    atomicOr(a.status, RK_DEV_TABLE_FULL);
-                    s_head[sg] = min(sh.first_kept, tail);
-                    sh.remaining = 0;
-                }
-                __syncthreads();
+                if (lane == 0) atomicOr(a.status, RK_DEV_TABLE_FULL);
+                new_head = tail;
                 break;
             }
-            const uint32_t pos = head + (uint32_t)tid;
-            uint32_t sl = 0;
-            bool live = false, cand = false;
-            uint64_t key = 0;
-            if (pos < tail) {
-                sl = tl[pos & rmask];
-                if (sl < S) {
-                    uint32_t st, fk;
-                    load_slot(tk + sl, key, st, fk);
-                    live = st == pos;
-                    cand = live && (!freq || fk <= ep + 1u);
+            uint32_t sl[U], st[U], fk[U];
+            uint64_t key[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t pos = head + (uint32_t)(64 * u + lane);
+                sl[u] = pos < tail ? tl[pos & rmask] : 0xFFFFFFFFu;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                key[u] = 0ull;
+                st[u] = kTomb;
+                fk[u] = 0u;
+                if (sl[u] < S) load_slot(tk + sl[u], key[u], st[u], fk[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t pos = head + (uint32_t)(64 * u + lane);
+                const bool live = st[u] == pos;
+                const bool cand = live && (!freq || fk[u] <= ep + 1u);
+                const unsigned long long m = __ballot(cand);
+                const int32_t rank = __popcll(m & ((1ull << lane) - 1ull));
+                const bool gone = cand && rank < rem;
+                if (gone) {
+                    tk[sl[u]].stamp = kTomb;
+                    dig += mix64(key[u]);
                 }
+                if (freq && live && !gone) kept = min(kept, pos);
+                const int32_t c = min((int32_t)__popcll(m), rem);
+                if (c > 0 && c == rem) new_head = head + (uint32_t)(64 * u + __ffsll(__ballot(gone && rank == rem - 1)));
+                rem -= c;
             }
-            int32_t total;
-            const int32_t rank = block_scan<NT>(cand, sh.wtot, total);
-            const bool gone = cand && rank < rem;
-            if (gone) {
-                tk[sl].stamp = kTomb;
-                atomicAdd(&sh.digest, (unsigned long long)mix64(key));
-                if (rank == rem - 1) sh.new_head = pos + 1;
+            head = min(head + 64u * U, tail);
+        }
+        const uint32_t first = freq ? ep_wave_min_u32(kept) : 0xFFFFFFFFu;
+        const uint64_t digest = wave_sum_u64(dig);
+        if (lane == 0) {
+            if (gone0 > 0) {
+                s_head[sg] = skipped ? head0 : min(first, new_head);
+                s_live[sg] -= gone0 - rem;
+                s_sp[sg] = new_head;
+                s_spe[sg] = ep + 1u;
             }
-            if (live && !gone) atomicMin(&sh.first_kept, pos);
-            __syncthreads();
-            if (tid == 0) {
-                if (total >= rem) {
-                    s_head[sg] = min(sh.first_kept, sh.new_head);
-                    sh.ev += rem;
-                    s_live[sg] -= rem;
-                    sh.remaining = 0;
-                } else {
-                    sh.ev += total;
-                    s_live[sg] -= total;
-                    sh.remaining = rem - total;
-                }
-            }
-            head = min(head + (uint32_t)NT, tail);
-            __syncthreads();
+            r_evc[b] = gone0 - rem;
+            r_evd[b] = digest;
+            atomicAdd(&sh.ev_total, (unsigned long long)(gone0 - rem));
         }
     };
 
@@ -2398,39 +2437,51 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
         __syncthreads();
     };
 
-    // overlaps of batch routes b in [b_lo, nb) on worker j after j evicted (prefix mode): the
-    // caches stay prefix-closed, so an eviction can only cut a suffix off a route's cached prefix,
-    // and with every decided route's writes in, the table holds exactly o_cur[b][j] leading blocks
-    // before it.  One lookup of the last of them decides the usual case; otherwise a binary search
-    // within it finds the first block no longer live.
-    auto research = [&](int32_t b_lo, int32_t nb, int32_t j) {
-        const Slot* tj = g_slots + (uint64_t)j * S;
-        for (int32_t b = b_lo + tid; b < nb; b += NT) {
-            int32_t hi = o_cur[b * W + j];
-            if (hi > 0) {
-                const uint64_t* ch = a.chains + r_cb[b];
-                auto live = [&](int32_t k) {
-                    const uint64_t h = ch[k];
-                    const uint64_t s0 = home_slot(h, smask);
-                    uint64_t kw[kWin];
-                    uint32_t sw[kWin];
+    // overlaps (and tier overlaps) of batch routes b in [b_lo, nb) on the nd workers of s_evl, settled
+    // just now (prefix mode).  The caches stay prefix-closed, so an eviction can only cut a suffix
+    // off a route's cached prefix, and with every decided route's writes in, the table holds
+    // exactly o_cur[b][j] leading blocks before it.  A tier's leading blocks were in it before, or
+    // the worker's one route touched them: at most the larger of the old tier overlap and the
+    // common prefix with that route.  One lookup of the last of them decides the usual case;
+    // otherwise a binary search within finds the first block out.
+    auto research = [&](int32_t b_lo, int32_t nb, int32_t nd) {
+        const int32_t n = (nb - b_lo) * nd;
+        for (int32_t i = tid; i < n; i += NT) {
+            const int32_t b = b_lo + i / nd, j = s_evl[i % nd];
+            const Slot* tj = g_slots + (uint64_t)j * S;
+            int32_t o = o_cur[b * W + j];
+            const uint64_t* ch = a.chains + r_cb[b];
+            // block k held at a stamp of at least bound
+            auto held = [&](int32_t k, uint32_t bound) {
+                const uint64_t h = ch[k];
+                const uint64_t s0 = home_slot(h, smask);
+                uint64_t kw[kWin];
+                uint32_t sw[kWin], stamp = 0;
 #pragma unroll
-                    for (int x = 0; x < kWin; ++x) load_slot(tj + s0 + group_slot(h, x), kw[x], sw[x]);
-                    return finish_lookup(tj, smask, h, s0, kw, sw);
-                };
-                if (!live(hi - 1)) {
-                    int32_t lo = 0;
-                    --hi;
-                    while (lo < hi) {
-                        const int32_t mid = (lo + hi) >> 1;
-                        if (live(mid)) lo = mid + 1;
-                        else hi = mid;
-                    }
-                    hi = lo;
+                for (int x = 0; x < kWin; ++x) load_slot(tj + s0 + group_slot(h, x), kw[x], sw[x]);
+                return finish_lookup_stamp(tj, smask, h, s0, kw, sw, stamp) && stamp >= bound;
+            };
+            auto first_out = [&](int32_t hi, uint32_t bound) {
+                if (hi == 0 || held(hi - 1, bound)) return hi;
+                int32_t lo = 0;
+                --hi;
+                while (lo < hi) {
+                    const int32_t mid = (lo + hi) >> 1;
+                    if (held(mid, bound)) lo = mid + 1;
+                    else hi = mid;
                 }
+                return lo;
+            };
+            if (o > 0) o = first_out(o, 0u);
+            o_tab[b * W + j] = o;
+            o_cur[b * W + j] = o;
+            if (tiers) {
+                const int32_t l = l_lcp[s_evb[j] * NB + b];
+                const int32_t o12 = first_out(min(o, max((int32_t)t12_tab[b * W + j], l)), s_b2[j]);
+                const int32_t o1 = first_out(min(o12, max((int32_t)t1_tab[b * W + j], l)), s_b1[j]);
+                t12_tab[b * W + j] = (uint16_t)o12;
+                t1_tab[b * W + j] = (uint16_t)o1;
             }
-            o_tab[b * W + j] = hi;
-            o_cur[b * W + j] = hi;
         }
         __syncthreads();
     };
@@ -3039,6 +3090,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
             // writes of the batch's routes decided so far (run-index entries or touches; the
             // decisions go on in the same batch after a stop)
             int32_t rwork = t > t0 ? r_wend[t - t0 - 1] : 0;
+            uint64_t dirty = 0ull;   // workers to settle (evictions, tier boundaries)
             for (;;) {
                 if (!step_open) {
                     // release the routes of step s - H; queue their conversations' next turns
@@ -3131,8 +3183,12 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                 uint32_t bits = 0xFFFFFFFFu;
                 int32_t oj = 0;
                 float cj = 0.0f;
+                if (lane < W) oj = o_cur[b * W + lane];
+                if (__builtin_expect((__ballot(oj > 0) & dirty) != 0ull, 0)) {
+                    event = EV_FLUSH;
+                    break;
+                }
                 if (lane < W) {
-                    oj = o_cur[b * W + lane];
                     if (__builtin_expect(tiers_d, 0)) {
                         const int32_t o1 = t1_tab[b * W + lane], o12 = t12_tab[b * W + lane];
                         cj = route_cost_tiers(w, prm.w_act, prm.w_sat, prm.cap_blocks, P, oj, o1, o12,
@@ -3182,6 +3238,10 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                         const float fb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cj), cb2));
                         if (fb < fa || (fb == fa && cb2 < ca)) sg = cb2;
                     }
+                }
+                if (__builtin_expect(((dirty >> sg) & 1ull) != 0, 0)) {
+                    event = EV_FLUSH;
+                    break;
                 }
                 const int32_t osg = __builtin_amdgcn_readlane(oj, sg);
                 const int32_t live_after = __builtin_amdgcn_readlane(rlive, sg) + (scan_d ? 0 : P - osg);
@@ -3240,11 +3300,9 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                     r_reg[b] = regime_d ? rg_r : 0;
                     r_evc[b] = 0;
                     r_evd[b] = 0ull;
-                    if (flush) {
-                        sh.ev_b = b;
-                        sh.ev_row = row;
-                    }
+                    if (flush) s_evb[sg] = b;
                 }
+                if (flush) dirty |= 1ull << sg;
                 u_tot += P;
                 q_head = q_head + 1 == qcap ? 0 : q_head + 1;
                 q_size -= 1;
@@ -3309,7 +3367,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                 ep_wave_sync();
                 if (lane == 0)
                     __hip_atomic_store(&sh.decided, b + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (__builtin_expect(flush, 0)) {
+                if (scan_d) {              // any route may change any later one's overlaps on its worker
                     event = EV_FLUSH;
                     break;
                 }
@@ -3325,6 +3383,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                 sh.qhead = q_head;
                 sh.qsize = q_size;
                 sh.event = event;
+                sh.dirty = dirty;
                 sh.tdone = t;
                 __hip_atomic_store(&sh.stop, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
@@ -3349,6 +3408,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                     lc.s_used = lds_off(s_used);
                     lc.s_head = lds_off(s_head);
                     lc.s_stamped = lds_off(s_stamped);
+                    lc.s_evb = lds_off(s_evb);
                     lc.s_stw = lds_off(s_stw);
                     lc.s_stP = lds_off(s_stP);
                     lc.s_stc = lds_off(s_stc);
@@ -3438,75 +3498,68 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
             job = false;
             __syncthreads();
             event = sh.event;
-            if (event != EV_BATCH && event != EV_DONE) had_stop = true;
-            if (event == EV_ROOM) {
-                // every decided route's writes are in: compact the route's worker, then decide on
-                rebuild(sh.ev_b);
-                if (tid == 0) sh.stop = 0;
+            const unsigned long long dirty = sh.dirty;
+            if ((event != EV_BATCH && event != EV_DONE) || dirty) had_stop = true;
+            if (dirty) {
+                // settle the workers whose routes wait for it (one route each; every decided route's
+                // writes are in): tier boundaries and evictions, then the pending requests' overlaps
+                const int32_t nd = __popcll(dirty), b_lo = sh.tdone - tb0;
+                if (wave == 0 && ((dirty >> lane) & 1ull)) {
+                    s_evl[__popcll(dirty & ((1ull << lane) - 1ull))] = lane;
+                    if (scan) {
+                        s_live[lane] += sh.ins;
+                        s_used[lane] += sh.ins;
+                    }
+                    if (tiers) {
+                        // the route's P records joined both tier runs; its hits left them where
+                        // their old records lay inside
+                        const int32_t P = r_P[s_evb[lane]];
+                        s_n1[lane] += P - s_h1[lane];
+                        s_n2[lane] += P - s_h2[lane];
+                        s_h1[lane] = 0;
+                        s_h2[lane] = 0;
+                    }
+                }
                 __syncthreads();
-                continue;
-            }
-            if (event == EV_EPOCH) {
-                if (tid == 0) sh.stop = 0;
+                if (tid == 0) sh.ins = 0;
+                if (!eager) {
+                    for (int32_t q = 0; q < nd; ++q) {
+                        const int32_t sg = s_evl[q];
+                        if (s_stamped[sg]) continue;
+                        // the worker's first eviction: its blocks go into its (cleared) block table
+                        // with the recency of its routes
+                        __syncthreads();
+                        clear_tables(sg, sg + 1);
+                        __syncthreads();
+                        if (!materialize(sg, sh.tdone)) replay(sg, sh.tdone);
+                    }
+                }
+                for (int32_t q = wave; q < nd; q += NW) {
+                    const int32_t sg = s_evl[q], b = s_evb[sg];
+                    if (tiers) advance(sg);
+                    evict(sg, r_ep[b], b);
+                    if (tiers && lane == 0) {
+                        // evictions take the oldest records: a run keeps at most the live count
+                        s_n1[sg] = min(s_n1[sg], s_live[sg]);
+                        s_n2[sg] = min(s_n2[sg], s_live[sg]);
+                        s_b1[sg] = max(s_b1[sg], s_head[sg]);
+                        s_b2[sg] = max(s_b2[sg], s_head[sg]);
+                    }
+                }
                 __syncthreads();
-                continue;
+                if (!scan) {
+                    research(b_lo, nb, nd);
+                } else {
+                    const int32_t sg = s_evl[0];
+                    search(b_lo, nb, sg);
+                    if (tiers) tier_search(b_lo, nb, sg);
+                }
             }
-            if (event != EV_FLUSH) break;
-            // the route's worker (every decided route's writes are in): evict, search the pending
-            // requests again
-            const int32_t b = sh.ev_b;
-            const int32_t sg = r_sig[b];
+            if (event == EV_BATCH || event == EV_DONE) break;
+            if (event == EV_ROOM) rebuild(sh.ev_b);   // compact the route's worker, then decide on
             if (tid == 0) {
                 sh.stop = 0;
-                if (scan) {
-                    s_live[sg] += sh.ins;
-                    s_used[sg] += sh.ins;
-                }
-                sh.ins = 0;
-                sh.remaining = max(0, s_live[sg] - a.cache);
-                sh.ev = 0;
-                sh.digest = 0ull;
-                sh.first_kept = 0xFFFFFFFFu;
-            }
-            __syncthreads();
-            if (tiers) {
-                // the route's P records joined both tier runs; its hits left them where their old
-                // records lay inside
-                if (tid == 0) {
-                    s_n1[sg] += r_P[b] - sh.h1;
-                    s_n2[sg] += r_P[b] - sh.h2;
-                    sh.h1 = 0;
-                    sh.h2 = 0;
-                }
-                __syncthreads();
-                advance(s_b1, s_n1, K1, sg);
-                advance(s_b2, s_n2, K12, sg);
-            }
-            if (!s_stamped[sg] && sh.remaining > 0) {
-                // the worker's first eviction: its blocks go into its (cleared) block table with
-                // the recency of its routes
-                clear_tables(sg, sg + 1);
-                __syncthreads();
-                if (!materialize(sg, sh.tdone)) replay(sg, sh.tdone);
-            }
-            evict(sg, r_ep[b]);
-            if (tiers) {
-                // evictions take the oldest records: a run keeps at most the live count
-                if (tid == 0) {
-                    s_n1[sg] = min(s_n1[sg], s_live[sg]);
-                    s_n2[sg] = min(s_n2[sg], s_live[sg]);
-                    s_b1[sg] = max(s_b1[sg], s_head[sg]);
-                    s_b2[sg] = max(s_b2[sg], s_head[sg]);
-                }
-                __syncthreads();
-            }
-            if (!scan && !tiers) research(b + 1, nb, sg);
-            else search(b + 1, nb, sg);
-            if (tiers) tier_search(b + 1, nb, sg);
-            if (tid == 0) {
-                r_evc[sh.ev_b] = sh.ev;
-                r_evd[sh.ev_b] = sh.digest;
-                sh.ev_total += sh.ev;
+                sh.dirty = 0;
             }
             __syncthreads();
         }
@@ -3538,7 +3591,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
     if (tid == 0 && a.out.totals) {
         int64_t cachedsum = 0;
         for (int32_t j = 0; j < W; ++j) cachedsum += s_live[j];
-        tot[1] = sh.ev_total;
+        tot[1] = (int64_t)sh.ev_total;
         tot[7] = cachedsum;
         for (int k = 0; k < 8; ++k) a.out.totals[(int64_t)e * 8 + k] = tot[k];
     }
@@ -3641,7 +3694,7 @@ extern "C" int rk_simulate_episodes(const rk_episode_batch* b, const rk_episode_
     // batch that fits in 76 KiB (two episodes can then share a CU)
     size_t o = 0;
     a.lds_w = 0;
-    o = align_up(o + (size_t)b->W * 11 * 4, 16);
+    o = align_up(o + (size_t)b->W * 17 * 4, 16);
     a.lds_inflight = (uint32_t)o;
     o = align_up(o + (size_t)b->max_inflight * 4 * 4, 16);
     a.lds_u = (uint32_t)o;

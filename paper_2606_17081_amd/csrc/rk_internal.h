@@ -192,6 +192,16 @@ __device__ __forceinline__ uint64_t wave_or_u64(uint64_t v)
     return (readlane64(v, 0) | readlane64(v, 16)) | (readlane64(v, 32) | readlane64(v, 48));
 }
 
+// Sum of v over the lanes, the same value in every lane.  All lanes must be active.
+__device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v)
+{
+    v += dpp64<kDppQuadSwap1>(v, v);
+    v += dpp64<kDppQuadSwap2>(v, v);
+    v += dpp64<kDppRowHalfMirror>(v, v);
+    v += dpp64<kDppRowMirror>(v, v);
+    return (readlane64(v, 0) + readlane64(v, 16)) + (readlane64(v, 32) + readlane64(v, 48));
+}
+
 // route_cost for the episodes, where A + P stays far below 2^31 (blocks in
 // flight), so the sum converts from 32 bits; a power-of-two cap divides by the
 // exact multiplication with its reciprocal inv_cap (the same correctly
