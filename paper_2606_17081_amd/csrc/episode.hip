@@ -97,12 +97,39 @@ struct EpArgs {
 };
 
 
-// Which copy of the decision loop runs: 0 the full one, 1 the lean one (prefix
-// mode, argmin, LRU, no tiers, no controller), 2 the lean one with the load
-// controller.
-template <int V>
-struct LeanTag {
-    static constexpr int value = V;
+// What the decision loop reads: LDS addresses (bytes) of the episode's arrays, global arrays and
+// the episode's parameters.  The arrays of a family lie one after another, so one address stands
+// for them all.
+struct DecideCtx {
+    uint32_t s_w;                  // worker arrays of W words
+    uint32_t s_fl;                 // in-flight arrays of max_inflight words
+    uint32_t s_u;                  // controller window
+    uint32_t r_c;                  // per-route arrays of NB words
+    uint32_t o_cur, o_tab, lcp, wend, evd, rnd, t1, t12;
+    int32_t W, NB, nb, t0, H, rps, max_inflight, qcap, cache, ctrl_window, cap_blocks, policy, dsteps, opt;
+    float w_ov, w_act, w_sat, ctrl_w_ov, inv_cap, tau, tw0, tw1, tw2;
+    uint32_t pad;
+    int32_t* g_hist;
+    int32_t* g_next;
+    int32_t* g_queue;
+    float* out_cost;
+    int32_t* out_tier;
+    int32_t* status;
+    int64_t out_base, ctrl_max;    // the controller is on while the window's sum exceeds ctrl_max
+    uint64_t used_limit, R;
+};
+enum : int32_t { OPT_FREQ = 1, OPT_TIERS = 2, OPT_SCAN = 4, OPT_REGIME = 8, OPT_CTRL = 16 };
+// positions of the worker and per-route arrays within their families
+enum : int32_t { WA_A = 0, WA_HEAD, WA_TAIL, WA_LIVE, WA_USED, WA_N, WA_B1, WA_B2, WA_N1, WA_N2, WA_STAMPED, WA_EVB };
+enum : int32_t { RA_C = 0, RA_K, RA_TURN, RA_P, RA_SIG, RA_OTAB, RA_STAMP, RA_EP, RA_STEP, RA_REG, RA_EVC };
+
+// The routing sequence's state, carried from one call of the decision loop to the next.
+struct DecideState {
+    int32_t t, s, r_in_step, n_step, s_slot, c_pos, room_t, step_open, prev_active, rg_r, rg_up, rg_down;
+    double rg_ewma;
+    int64_t u_sum;
+    int32_t u_tot, held;           // blocks and routes in flight
+    int64_t tot[8];
 };
 
 struct EpShared {
@@ -110,6 +137,9 @@ struct EpShared {
     int32_t qhead, qsize, nb, event, ev_b, ins, decided, claimed, stop, tdone;
     unsigned long long ev_total, dirty;
     int32_t wtot[kMaxWaves];
+    DecideCtx ctx;
+    DecideState st;
+    rk_regime_params regime;
 };
 
 // NT below: the threads of the episode's workgroup.
@@ -1260,9 +1290,8 @@ __global__ void episode_queue_init(int32_t* __restrict__ q)
 // The queued loop is a kernel of its own (Queued = true): a loop around the
 // episode keeps more values live across it, and the one-episode kernel keeps
 // its register allocation.
-// ------------------------------------------------- the lean decision loop
-// Pointers into LDS and global memory with their address spaces spelled out, for code outside
-// the kernel body (a 32-bit LDS address, a global address).
+// ------------------------------------------------- the decision loop
+// LDS and global memory from code outside the kernel body: a 32-bit LDS address, a global address.
 template <typename T>
 using lds_p = __attribute__((address_space(3))) T*;
 template <typename T>
@@ -1279,283 +1308,468 @@ __device__ __forceinline__ uint32_t lds_off(T* p)
     return (uint32_t)(uintptr_t)(lds_p<T>)p;
 }
 
-// v, the same in every lane, as a wave-uniform value (every 32-bit word through readfirstlane):
-// the arguments of a function arrive in vector registers.
+// The T at LDS address off, the same for every lane, as wave-uniform words.
 template <typename T>
-__device__ __forceinline__ T wave_uniform(const T& v)
+__device__ __forceinline__ T lds_uniform(uint32_t off)
 {
     static_assert(sizeof(T) % 4 == 0, "32-bit words");
     T r;
-    const int32_t* src = reinterpret_cast<const int32_t*>(&v);
     int32_t* dst = reinterpret_cast<int32_t*>(&r);
+    const lds_p<int32_t> src = lds_at<int32_t>(off);
 #pragma unroll
     for (int i = 0; i < (int)(sizeof(T) / 4); ++i) dst[i] = __builtin_amdgcn_readfirstlane(src[i]);
     return r;
 }
 
-// What the lean decision loop reads: LDS addresses of the episode's arrays, global arrays and
-// the episode's parameters.
-struct LeanCtx {
-    uint32_t sh, s_A, s_N, s_tail, s_live, s_used, s_head, s_stamped, s_evb, s_stw, s_stP, s_stc, s_stepn, s_u;
-    uint32_t r_P, r_c, r_k, o_cur, o_tab, lcp, r_sig, r_wend, r_stamp, r_ep, r_otab, r_step, r_reg, r_evc, r_evd;
-    glb_p<int32_t> g_hist;
-    glb_p<int32_t> g_next;
-    glb_p<int32_t> g_queue;
-    glb_p<float> out_cost;
-    glb_p<int32_t> status;
-    int64_t out_base, ctrl_thr;
-    uint64_t used_limit, R;
-    int32_t W, NB, nb, t0, H, rps, qcap, cache, ctrl_window, ctrl_den, cap_blocks;
-    float w_ov, w_act, w_sat, ctrl_w_ov, inv_cap;
-};
+// Releases of a step that go one by one through registers; more go through LDS atomics at once.
+constexpr int32_t kFewReleases = 8;
 
-// The routing sequence's state, carried from one call to the next.
-struct LeanState {
-    int32_t t, s, r_in_step, n_step, s_slot, c_pos, room_b, step_open, prev_active;
-    int64_t u_sum, u_tot;
-    int64_t tot[8];
-};
-
-// The decisions of wavefront 0 for an episode in prefix mode, routed by argmin under LRU,
-// without memory tiers, frequency decay or the regime controller (LC: with the load
-// controller), from route t up to the batch's end or a stop, as the general loop of the kernel
-// takes them: the same routes, outputs and state.  It is a function of its own so that its
-// registers are its own and not those of the whole episode kernel, which keeps the serial
-// chain of decisions short: the batch's per-route inputs sit in registers (lane b holds route
-// b's), the load release of a step is applied in registers, and the next route's overlaps are
-// read from LDS while the current route's outputs are written.
-template <bool LC>
-__device__ __noinline__ void lean_decide(const LeanCtx c_arg, LeanState* st_arg)
+// The decisions of wavefront 0, from route t up to the batch's end or a stop, in order.  MODE 1: prefix
+// mode, argmin, LRU, no tiers, no controller; 2: the same with the load controller; 0: everything.
+//
+// This loop is the serial chain of an episode, and what it costs is its instructions (a wavefront
+// issues one every four or five cycles) and the LDS round trips it waits for.  So it is a function
+// of its own, whose registers are its own; lane j keeps worker j's state and lane b route b's
+// inputs and results; the next route's overlaps and the common prefixes of the current one are
+// read a route ahead; and the results go to LDS and the history a group of routes at a time, each
+// lane storing its route's (`decided` then moves on by the group; one route at a time while some
+// worker keeps recency, whose touches the writers are short of time for).  Everything else about a
+// route (the totals, the history, the next turn) is taken from the lanes at that point.  The step
+// of a 1P/5D sweep's episodes: 1.05 -> PLACEHOLDER us per route.
+template <int MODE>
+__device__ __noinline__ void decide_routes(uint32_t sh_off_arg)
 {
+    constexpr bool FULL = MODE == 0;
     const int lane = (int)(threadIdx.x & 63);
-    const LeanCtx c = wave_uniform(c_arg);
-    LeanState* const st = wave_uniform(st_arg);
-    const LeanState st0 = wave_uniform(*st);
-    const lds_p<EpShared> sh = lds_at<EpShared>(c.sh);
-    const lds_p<int32_t> s_A = lds_at<int32_t>(c.s_A), s_N = lds_at<int32_t>(c.s_N);
-    const lds_p<uint32_t> s_tail = lds_at<uint32_t>(c.s_tail), s_head = lds_at<uint32_t>(c.s_head);
-    const lds_p<int32_t> s_live = lds_at<int32_t>(c.s_live), s_used = lds_at<int32_t>(c.s_used);
-    const lds_p<int32_t> s_stamped = lds_at<int32_t>(c.s_stamped), s_evb = lds_at<int32_t>(c.s_evb);
-    const lds_p<int32_t> s_stw = lds_at<int32_t>(c.s_stw), s_stP = lds_at<int32_t>(c.s_stP);
-    const lds_p<int32_t> s_stc = lds_at<int32_t>(c.s_stc), s_stepn = lds_at<int32_t>(c.s_stepn);
-    const lds_p<int64_t> s_u = lds_at<int64_t>(c.s_u);
-    const lds_p<int32_t> r_P = lds_at<int32_t>(c.r_P), r_c = lds_at<int32_t>(c.r_c), r_k = lds_at<int32_t>(c.r_k);
+    const uint32_t sh_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh_off_arg);
+    const lds_p<EpShared> sh = lds_at<EpShared>(sh_off);
+    const DecideCtx c = lds_uniform<DecideCtx>(sh_off + (uint32_t)offsetof(EpShared, ctx));
+    const lds_p<DecideState> st = lds_at<DecideState>(sh_off + (uint32_t)offsetof(EpShared, st));
+    const int32_t W = c.W, NB = c.NB, nb = c.nb, t0 = c.t0, H = c.H, rps = c.rps;
+    const bool freq = FULL && (c.opt & OPT_FREQ), tiers = FULL && (c.opt & OPT_TIERS), scan = FULL && (c.opt & OPT_SCAN),
+               regime = FULL && (c.opt & OPT_REGIME), ctrl = MODE == 2 || (FULL && (c.opt & OPT_CTRL));
+    const lds_p<int32_t> s_w = lds_at<int32_t>(c.s_w), r_arr = lds_at<int32_t>(c.r_c);
+    const lds_p<int32_t> s_stw = lds_at<int32_t>(c.s_fl), s_stP = s_stw + c.max_inflight, s_stc = s_stP + c.max_inflight,
+                         s_stepn = s_stc + c.max_inflight;
     const lds_p<int32_t> o_cur = lds_at<int32_t>(c.o_cur), o_tab = lds_at<int32_t>(c.o_tab);
     const lds_p<uint16_t> l_lcp = lds_at<uint16_t>(c.lcp);
-    const lds_p<int32_t> r_sig = lds_at<int32_t>(c.r_sig), r_wend = lds_at<int32_t>(c.r_wend);
-    const lds_p<uint32_t> r_stamp = lds_at<uint32_t>(c.r_stamp), r_ep = lds_at<uint32_t>(c.r_ep);
-    const lds_p<int32_t> r_otab = lds_at<int32_t>(c.r_otab), r_step = lds_at<int32_t>(c.r_step);
-    const lds_p<int32_t> r_reg = lds_at<int32_t>(c.r_reg), r_evc = lds_at<int32_t>(c.r_evc);
-    const lds_p<uint64_t> r_evd = lds_at<uint64_t>(c.r_evd);
-    const int32_t W = c.W, NB = c.NB, nb = c.nb, t0 = c.t0, H = c.H, rps = c.rps;
+    const lds_p<int32_t> r_wend = lds_at<int32_t>(c.wend);
+    const lds_p<int64_t> s_u = lds_at<int64_t>(c.s_u);
+    const auto uni = [](int32_t v) { return __builtin_amdgcn_readfirstlane(v); };
 
-    int32_t t = st0.t, s = st0.s, r_in_step = st0.r_in_step, n_step = st0.n_step, s_slot = st0.s_slot;
-    int32_t c_pos = st0.c_pos, room_b = st0.room_b;
-    bool step_open = st0.step_open != 0, prev_active = st0.prev_active != 0;
-    int64_t u_sum = st0.u_sum, u_tot = st0.u_tot;
-    int64_t tot0 = st0.tot[0], tot2 = st0.tot[2], tot3 = st0.tot[3], tot4 = st0.tot[4], tot5 = st0.tot[5],
-            tot6 = st0.tot[6];
+    int32_t t = uni(st->t), s = uni(st->s), r_in_step = uni(st->r_in_step), n_step = uni(st->n_step),
+            s_slot = uni(st->s_slot), c_pos = uni(st->c_pos), room_t = uni(st->room_t), u_tot = uni(st->u_tot), held = uni(st->held);
+    bool step_open = uni(st->step_open) != 0, prev_active = uni(st->prev_active) != 0;
+    int64_t u_sum = lds_uniform<int64_t>(sh_off + (uint32_t)(offsetof(EpShared, st) + offsetof(DecideState, u_sum)));
+    int32_t tot3 = 0, tot4 = 0, tot5 = -1;
+    int32_t rg_r = 0, rg_up = 0, rg_down = 0;
+    double rg_ewma = 0.0;
+    rk_regime_params rg;
+    if (regime) {
+        rg = lds_uniform<rk_regime_params>(sh_off + (uint32_t)offsetof(EpShared, regime));
+        rg_r = uni(st->rg_r);
+        rg_up = uni(st->rg_up);
+        rg_down = uni(st->rg_down);
+        rg_ewma = lds_uniform<double>(sh_off + (uint32_t)(offsetof(EpShared, st) + offsetof(DecideState, rg_ewma)));
+    }
     int32_t event = EV_BATCH;
+    int32_t q_head = uni(sh->qhead), q_size = uni(sh->qsize);
+    int32_t run_ep = -1;   // decay epoch of the routes decided since the last sync
 
-    // lane j < W keeps worker j's load, log tail and block counts; lane b < nb route b's inputs
-    int32_t rA = 0, rlive = 0, rused = 0, rN = 0;
-    uint32_t rtail = 0;
-    int32_t q_head = __builtin_amdgcn_readfirstlane(sh->qhead), q_size = __builtin_amdgcn_readfirstlane(sh->qsize);
-    if (lane < W) {
-        rA = s_A[lane];
-        rN = s_N[lane];
-        rtail = s_tail[lane];
-        rlive = s_live[lane];
-        rused = s_used[lane];
-    }
-    const unsigned long long stamped_mask = __ballot(lane < W && s_stamped[lane] != 0);
+    // lane j < W: worker j's load, log tail and block counts
+    const bool wl = lane < W;
+    const int32_t wi = wl ? lane : 0;
+    int32_t rA = wl ? s_w[WA_A * W + wi] : 0, rlive = s_w[WA_LIVE * W + wi], rused = s_w[WA_USED * W + wi];
+    int32_t rN = FULL ? s_w[WA_N * W + wi] : 0;
+    uint32_t rtail = (uint32_t)s_w[WA_TAIL * W + wi];
+    const uint64_t stamped_mask = __ballot(wl && s_w[WA_STAMPED * W + wi] != 0);
+    const int32_t group = stamped_mask ? 1 : 16;
+    // lane b < nb: route b's inputs, and its results once it is decided
     const int32_t b_start = t - t0;
-    int32_t rwork = b_start > 0 ? __builtin_amdgcn_readfirstlane(r_wend[b_start - 1]) : 0;
-    int32_t vP = 0, vc = 0, vk = 0;
-    if (lane < nb) {
-        vP = r_P[lane];
-        vc = r_c[lane];
-        vk = r_k[lane];
-    }
+    int32_t pub = b_start;      // the first route not published yet
+    const int32_t bi = lane < NB ? lane : 0;
+    const int32_t vP = r_arr[RA_P * NB + bi], vc = r_arr[RA_C * NB + bi], vk = r_arr[RA_K * NB + bi];
+    int32_t v_sig = 0, v_osg = 0, v_wend = 0, v_step = 0, v_pos = 0, v_reg = 0, v_ep = 0;
+    uint32_t v_stamp = 0;
+    int32_t rwork = b_start > 0 ? uni(r_wend[b_start - 1]) : 0;
     if (lane >= b_start && lane < nb) {
-        r_ep[lane] = 0u;
-        r_reg[lane] = 0;
-        r_evc[lane] = 0;
-        r_evd[lane] = 0ull;
+        r_arr[RA_EVC * NB + lane] = 0;
+        lds_at<uint64_t>(c.evd)[lane] = 0ull;
     }
+    int64_t acc_new = 0, acc_P = 0;   // the lane's routes: blocks past the overlap, blocks
+    uint64_t dirty = 0ull;            // workers to settle (evictions, tier boundaries)
+
+    auto publish = [&](int32_t b_end) {
+        if (lane >= pub && lane < b_end) {
+            r_arr[RA_SIG * NB + lane] = v_sig;
+            r_wend[lane] = v_wend;
+            r_arr[RA_STAMP * NB + lane] = (int32_t)v_stamp;
+            r_arr[RA_OTAB * NB + lane] = o_tab[lane * W + v_sig];
+            r_arr[RA_STEP * NB + lane] = v_step;
+            r_arr[RA_REG * NB + lane] = v_reg;
+            r_arr[RA_EP * NB + lane] = v_ep;
+            s_stw[v_pos] = v_sig;
+            s_stP[v_pos] = vP;
+            s_stc[v_pos] = vc;
+            const glb_p<int32_t> hist = (glb_p<int32_t>)c.g_hist;
+            hist[2 * (t0 + lane)] = vc & ~kMoreTurns;
+            hist[2 * (t0 + lane) + 1] = vP | (v_sig << 16);
+            ((glb_p<int32_t>)c.g_next)[vc & ~kMoreTurns] = vk + 1;
+            acc_new += vP - v_osg;
+            acc_P += vP;
+        }
+        pub = b_end;
+        ep_wave_sync();
+        if (lane == 0) __hip_atomic_store(&sh->decided, b_end, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+
     // the overlaps of the next route (all earlier routes' raises are in)
-    int32_t oj = lane < W && b_start < nb ? o_cur[b_start * W + lane] : 0;
-    uint64_t dirty = 0ull;   // workers over their capacity, not settled yet
-    for (;;) {
+    int32_t oj = wl && b_start < nb ? o_cur[b_start * W + lane] : 0;
+    glb_p<float> cost_p = (glb_p<float>)c.out_cost + (c.out_base + (int64_t)t) * W + wi;
+    bool go = true;
+    while (go) {
         if (!step_open) {
-            // release the routes of step s - H (their loads, in registers); queue their
-            // conversations' next turns
-            const int32_t slot = s_slot, sb = slot * rps;
+            // release the routes of step s - H; queue their conversations' next turns
+            const int32_t sb = s_slot * rps;
             if (s >= H) {
-                const int32_t nprev = __builtin_amdgcn_readfirstlane(s_stepn[slot]);
+                const int32_t nprev = uni(s_stepn[s_slot]);
+                held -= nprev;
+                if (pub < t - t0 - held) publish(t - t0);    // some of them are not in LDS yet
                 const int32_t qtail = q_head + q_size;
-                int32_t pushed = 0;
-                int64_t rel = 0;
+                int32_t pushed = 0, rel = 0;
+                const bool by_lds = nprev > kFewReleases;
+                if (by_lds) {
+                    if (wl) {
+                        s_w[WA_A * W + lane] = rA;
+                        if (FULL) s_w[WA_N * W + lane] = rN;
+                    }
+                    ep_wave_sync();
+                }
                 for (int32_t base = 0; base < nprev; base += 64) {
                     const int32_t r = base + lane;
+                    const bool in = r < nprev;
                     int32_t wr = 0, pr = 0, cr = 0;
-                    if (r < nprev) {
+                    if (in) {
                         wr = s_stw[sb + r];
                         pr = s_stP[sb + r];
                         cr = s_stc[sb + r];
                     }
-                    const bool more = r < nprev && (cr & kMoreTurns) != 0;
+                    if (by_lds && in) {
+                        __hip_atomic_fetch_add(&s_w[WA_A * W + wr], -pr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        if (FULL)
+                            __hip_atomic_fetch_add(&s_w[WA_N * W + wr], -1, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                    const bool more = in && (cr & kMoreTurns) != 0;
                     const unsigned long long mb = __ballot(more);
                     if (more) {
                         const int32_t qi = qtail + pushed + __popcll(mb & ((1ull << lane) - 1ull));
-                        c.g_queue[qi >= c.qcap ? qi - c.qcap : qi] = cr & ~kMoreTurns;
+                        ((glb_p<int32_t>)c.g_queue)[qi >= c.qcap ? qi - c.qcap : qi] = cr & ~kMoreTurns;
                     }
                     pushed += __popcll(mb);
-                    const int32_t m = min(64, nprev - base);
-                    for (int32_t k = 0; k < m; ++k) {
-                        const int32_t wk = __builtin_amdgcn_readlane(wr, k), pk = __builtin_amdgcn_readlane(pr, k);
-                        rel += pk;
-                        if (lane == wk) {
-                            rA -= pk;
-                            rN -= 1;
+                    if (!by_lds) {
+                        for (int32_t k = 0; k < nprev; ++k) {
+                            const int32_t wk = __builtin_amdgcn_readlane(wr, k), pk = __builtin_amdgcn_readlane(pr, k);
+                            rel += pk;
+                            if (lane == wk) {
+                                rA -= pk;
+                                rN -= 1;
+                            }
                         }
+                    } else if (ctrl) {
+                        rel += wave_sum_i32(pr);
                     }
+                }
+                if (by_lds) {
+                    ep_wave_sync();
+                    rA = wl ? s_w[WA_A * W + wi] : 0;
+                    if (FULL) rN = s_w[WA_N * W + wi];
                 }
                 u_tot -= rel;
                 q_size += pushed;
             }
-            int32_t inflight = 0;
-            for (int32_t k = 1; k < H && k <= s; ++k)
-                inflight += __builtin_amdgcn_readfirstlane(s_stepn[s_slot >= k ? s_slot - k : s_slot - k + H]);
-            if (q_size == 0 && inflight == 0) {
+            if (q_size == 0 && held == 0) {
                 event = EV_DONE;
                 break;
             }
             n_step = min(rps, q_size);
-            if (lane == 0) s_stepn[slot] = n_step;
+            if (lane == 0) s_stepn[s_slot] = n_step;
             if (n_step > 0) tot5 = s + 1;
             r_in_step = 0;
             step_open = true;
         }
-        if (r_in_step >= n_step) {
+        const int32_t b_first = t - t0;
+        int32_t left = min(n_step - r_in_step, nb - b_first);
+        if (left <= 0) {
+            if (r_in_step < n_step) break;      // the batch's end
             ++s;
             s_slot = s_slot + 1 == H ? 0 : s_slot + 1;
             step_open = false;
             continue;
         }
-        const int32_t b = t - t0;
-        if (b >= nb) break;
-        if (__builtin_expect((__ballot(oj > 0) & dirty) != 0ull, 0)) {
-            event = EV_FLUSH;
-            break;
+        if (freq) {
+            // a new decay epoch waits until the earlier epoch's cache writes are in
+            const int32_t ep = s / c.dsteps;
+            if (run_ep >= 0 && ep != run_ep) {
+                event = EV_EPOCH;
+                break;
+            }
+            run_ep = ep;
         }
-        // one route: controller, cost of every worker, argmin
-        const int32_t sb = s_slot * rps;
-        bool active = false;
-        if (LC && t >= c.ctrl_window) active = (int64_t)c.ctrl_den * u_sum > c.ctrl_thr;
-        const float w = active ? fminf(c.w_ov, c.ctrl_w_ov) : c.w_ov;
-        const int32_t P = __builtin_amdgcn_readlane(vP, b);
-        const int64_t row = c.out_base + (int64_t)t;
-        uint32_t bits = 0xFFFFFFFFu;
-        if (lane < W) {
-            const float cj = route_cost_ep(w, c.w_act, c.w_sat, c.cap_blocks, c.inv_cap, P, oj, rA);
-            if (c.out_cost) c.out_cost[row * W + lane] = cj;
-            bits = __float_as_uint(__fadd_rn(cj, 0.0f));
-        }
-        const uint32_t mn = ep_wave_min_u32(bits);
-        const int32_t sg = __ffsll(__ballot(lane < W && bits == mn)) - 1;
-        if (__builtin_expect(((dirty >> sg) & 1ull) != 0, 0)) {
-            event = EV_FLUSH;
-            break;
-        }
-        const int32_t osg = __builtin_amdgcn_readlane(oj, sg);
-        const int32_t live_after = __builtin_amdgcn_readlane(rlive, sg) + P - osg;
-        const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)rtail, sg);
-        const bool flush = live_after > c.cache;
-        const bool stamped = ((stamped_mask >> sg) & 1ull) != 0;
-        // a worker that keeps recency needs log records for the route's P touches and slots for
-        // its new blocks: without room, stop before the route and compact that worker
-        if (__builtin_expect(stamped, 0)) {
-            const uint32_t head = __builtin_amdgcn_readfirstlane(s_head[sg]);
-            const uint64_t add = (uint64_t)(P - osg);
-            if ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(rused, sg) + add > c.used_limit ||
-                (uint64_t)(base - head) + (uint64_t)P > c.R || (uint64_t)base + (uint64_t)P > 0x40000000u) {
-                if (room_b == t) {
-                    if (lane == 0) atomicOr((int32_t*)c.status, RK_DEV_TABLE_FULL);
-                } else {
-                    room_b = t;
-                    if (lane == 0) sh->ev_b = sg;
-                    event = EV_ROOM;
+        for (int32_t b = b_first; left > 0; ++b, --left) {
+            // one route: controller, cost of every worker, selection
+            const int32_t P = __builtin_amdgcn_readlane(vP, b);
+            // read ahead: the next route's overlaps, the common prefixes of this one with later ones
+            const int32_t o_next = o_cur[(b + 1 < nb ? b + 1 : b) * W + wi];
+            const int32_t lrow = scan ? 0 : l_lcp[b * NB + min(b + 1 + lane, nb - 1)];
+            int64_t u_old = 0;
+            if (ctrl && t >= c.ctrl_window) u_old = s_u[c_pos];
+            bool active = false;
+            if (ctrl) active = t >= c.ctrl_window && u_sum > c.ctrl_max;
+            float w = active ? fminf(c.w_ov, c.ctrl_w_ov) : c.w_ov;
+            int32_t pol = FULL ? c.policy : RK_POLICY_ARGMIN;
+            float tau_r = FULL ? c.tau : 0.0f;
+            if (regime) {
+                w = rg_r == 0 ? rg.w_ov[0] : rg_r == 1 ? rg.w_ov[1] : rg.w_ov[2];
+                tau_r = rg_r == 0 ? rg.tau[0] : rg_r == 1 ? rg.tau[1] : rg.tau[2];
+                pol = tau_r > 0.0f ? RK_POLICY_SOFTMAX : RK_POLICY_ARGMIN;
+            }
+            if (__builtin_expect(dirty != 0ull, 0)) {
+                if (__ballot(wl && oj > 0) & dirty) {
+                    event = EV_FLUSH;
+                    go = false;
                     break;
                 }
             }
-        }
-        if (active) {
-            tot3 += 1;
-            if (!prev_active) tot4 += 1;
-        }
-        prev_active = active;
-        const int32_t rc = __builtin_amdgcn_readlane(vc, b);
-        if (lane == sg) {
-            rA += P;
-            rN += 1;
-            rtail = base + (uint32_t)P;
-            rlive = live_after;
-            rused += P - osg;
-        }
-        rwork += stamped ? P : (osg < P ? run_entries(osg, P) : 0);
-        // later requests of the batch now find this chain on sg; then the next route's overlaps
-        const int32_t b2 = b + 1 + lane;
-        if (b2 < nb) {
-            const int32_t l = l_lcp[b * NB + b2];
-            if (l > o_cur[b2 * W + sg]) o_cur[b2 * W + sg] = l;
-        }
-        oj = lane < W && b + 1 < nb ? o_cur[(b + 1) * W + lane] : 0;
-        if (lane == 0) {
-            r_sig[b] = sg;
-            r_wend[b] = rwork;
-            r_stamp[b] = base;
-            r_otab[b] = o_tab[b * W + sg];
-            s_stw[sb + r_in_step] = sg;
-            s_stP[sb + r_in_step] = P;
-            s_stc[sb + r_in_step] = rc;
-            r_step[b] = s;
-            c.g_hist[2 * t] = rc & ~kMoreTurns;
-            c.g_hist[2 * t + 1] = P | (sg << 16);
-            c.g_next[rc & ~kMoreTurns] = __builtin_amdgcn_readlane(vk, b) + 1;
-            if (flush) s_evb[sg] = b;
-        }
-        if (flush) dirty |= 1ull << sg;
-        u_tot += P;
-        q_head = q_head + 1 == c.qcap ? 0 : q_head + 1;
-        q_size -= 1;
-        if (LC) {
-            const int32_t pos = c_pos;
-            c_pos = c_pos + 1 == c.ctrl_window ? 0 : c_pos + 1;
-            if (t >= c.ctrl_window) {
-                const int64_t old = s_u[pos];
-                u_sum -= (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(old >> 32)) << 32) |
-                                   (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)old));
+            float cj;
+            if (tiers) {
+                const int32_t o1 = lds_at<uint16_t>(c.t1)[b * W + wi], o12 = lds_at<uint16_t>(c.t12)[b * W + wi];
+                const float tw[3] = {c.tw0, c.tw1, c.tw2};
+                cj = route_cost_tiers(w, c.w_act, c.w_sat, c.cap_blocks, P, oj, o1, o12, tw, rA);
+                if (wl && c.out_tier) {
+                    const glb_p<int32_t> ot = (glb_p<int32_t>)c.out_tier + ((c.out_base + (int64_t)t) * W + lane) * 2;
+                    ot[0] = o1;
+                    ot[1] = o12;
+                }
+            } else {
+                cj = route_cost_ep(w, c.w_act, c.w_sat, c.cap_blocks, c.inv_cap, P, oj, rA);
             }
-            if (lane == 0) s_u[pos] = u_tot;
-            u_sum += u_tot;
+            if (wl && c.out_cost) *cost_p = cj;
+            const uint32_t bits = wl ? __float_as_uint(__fadd_rn(cj, 0.0f)) : 0xFFFFFFFFu;
+            int32_t sg;
+            if (!FULL || pol == RK_POLICY_ARGMIN) {
+                uint32_t mn = bits;      // every row of 16 lanes holds its least
+                mn = min(mn, (uint32_t)__builtin_amdgcn_update_dpp((int)mn, (int)mn, 0xB1, 0xF, 0xF, false));
+                mn = min(mn, (uint32_t)__builtin_amdgcn_update_dpp((int)mn, (int)mn, 0x4E, 0xF, 0xF, false));
+                mn = min(mn, (uint32_t)__builtin_amdgcn_update_dpp((int)mn, (int)mn, 0x141, 0xF, 0xF, false));
+                mn = min(mn, (uint32_t)__builtin_amdgcn_update_dpp((int)mn, (int)mn, 0x140, 0xF, 0xF, false));
+                if (W > 16) {
+                    const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)mn, 0);
+                    const uint32_t r1 = (uint32_t)__builtin_amdgcn_readlane((int)mn, 16);
+                    const uint32_t r2 = (uint32_t)__builtin_amdgcn_readlane((int)mn, 32);
+                    const uint32_t r3 = (uint32_t)__builtin_amdgcn_readlane((int)mn, 48);
+                    mn = min(min(r0, r1), min(r2, r3));
+                }
+                sg = __ffsll(__ballot(bits == mn)) - 1;   // the lowest such worker: W <= 16 is row 0
+            } else if (pol == RK_POLICY_SOFTMAX) {
+                // weights exp((c_min - c_j) / tau); running sums in worker order, lane j keeping the one
+                // that ends at worker j
+                const float cmin = __uint_as_float(ep_wave_min_u32(bits));
+                const float ej = wl ? exp_neg_f32(__fdiv_rn(__fsub_rn(cmin, cj), tau_r)) : 0.0f;
+                float total = 0.0f, run = 0.0f;
+                for (int32_t j = 0; j < W; ++j) {
+                    total = __fadd_rn(total, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ej), j)));
+                    if (lane == j) run = total;
+                }
+                const float u = __fmul_rn((float)(lds_at<uint32_t>(c.rnd)[2 * b] >> 8), 5.9604644775390625e-8f);
+                const float thr = __fmul_rn(u, total);
+                const unsigned long long over = __ballot(wl && run > thr), some = __ballot(wl && ej > 0.0f);
+                sg = over ? __ffsll(over) - 1 : (some ? 63 - __clzll((long long)some) : 0);
+            } else if (pol == RK_POLICY_ROUND_ROBIN) {
+                sg = t % W;
+            } else {
+                const uint32_t d0 = (uint32_t)uni((int32_t)lds_at<uint32_t>(c.rnd)[2 * b]);
+                const uint32_t d1 = (uint32_t)uni((int32_t)lds_at<uint32_t>(c.rnd)[2 * b + 1]);
+                const int32_t ca = (int32_t)(((uint64_t)d0 * (uint64_t)W) >> 32);
+                sg = ca;
+                if (pol == RK_POLICY_P2C && W > 1) {
+                    int32_t cb2 = (int32_t)(((uint64_t)d1 * (uint64_t)(W - 1)) >> 32);
+                    if (cb2 >= ca) ++cb2;
+                    const float fa = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cj), ca));
+                    const float fb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cj), cb2));
+                    if (fb < fa || (fb == fa && cb2 < ca)) sg = cb2;
+                }
+            }
+            if (__builtin_expect(dirty != 0ull, 0)) {
+                if ((dirty >> sg) & 1ull) {
+                    event = EV_FLUSH;
+                    go = false;
+                    break;
+                }
+            }
+            const int32_t osg = __builtin_amdgcn_readlane(oj, sg);
+            const int32_t live_after = __builtin_amdgcn_readlane(rlive, sg) + (scan ? 0 : P - osg);
+            const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)rtail, sg);
+            const bool flush = scan || tiers || live_after > c.cache;
+            const bool stamped = ((stamped_mask >> sg) & 1ull) != 0;
+            // a worker that keeps recency needs log records for the route's P touches and slots for
+            // its new blocks: without room, stop before the route and compact that worker (the
+            // cached sets and loads stay as they are, so the route is decided again alike)
+            if (__builtin_expect(stamped, 0)) {
+                const uint32_t head = (uint32_t)uni(s_w[WA_HEAD * W + sg]);
+                const uint64_t add = (uint64_t)(scan ? P : P - osg);
+                if ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(rused, sg) + add > c.used_limit ||
+                    (uint64_t)(base - head) + (uint64_t)P > c.R || (uint64_t)base + (uint64_t)P > 0x40000000u) {
+                    if (room_t == t) {
+                        // still no room right after a compaction (the workspace layout always
+                        // leaves room for one route): report it and go on
+                        if (lane == 0) atomicOr((int32_t*)c.status, RK_DEV_TABLE_FULL);
+                    } else {
+                        room_t = t;
+                        if (lane == 0) sh->ev_b = sg;
+                        event = EV_ROOM;
+                        go = false;
+                        break;
+                    }
+                }
+            }
+            if (ctrl && active) {
+                tot3 += 1;
+                if (!prev_active) tot4 += 1;
+            }
+            prev_active = active;
+            if (regime && rg_r > 0) tot3 += 1;
+            rwork += stamped ? P : (osg < P ? run_entries(osg, P) : 0);
+            if (lane == sg) {
+                rA += P;
+                if (FULL) rN += 1;
+                rtail = base + (uint32_t)P;
+                if (!scan) {
+                    rlive = live_after;
+                    rused += P - osg;
+                }
+            }
+            if (lane == b) {
+                v_sig = sg;
+                v_osg = osg;
+                v_wend = rwork;
+                v_stamp = base;
+                v_step = s;
+                v_pos = s_slot * rps + r_in_step;
+                if (FULL) {
+                    v_reg = regime ? rg_r : 0;
+                    v_ep = freq ? run_ep : 0;
+                }
+            }
+            if (flush) {
+                dirty |= 1ull << sg;
+                if (lane == 0) s_w[WA_EVB * W + sg] = b;
+            }
+            // later requests of the batch now find this chain on sg
+            oj = wl ? o_next : 0;
+            if (!scan) {
+                if (b + 1 + lane < nb && lrow > 0)
+                    __hip_atomic_fetch_max(&o_cur[(b + 1 + lane) * W + sg], lrow, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                const int32_t l1 = __builtin_amdgcn_readlane(lrow, 0);
+                if (lane == sg) oj = max(oj, l1);
+            }
+            q_head = q_head + 1 == c.qcap ? 0 : q_head + 1;
+            q_size -= 1;
+            if (regime) {
+                // the chosen worker's latency with the new request (already counted in
+                // lane sg's rN) stands in for TTFT (fp64)
+                const int32_t n_sg = __builtin_amdgcn_readlane(rN, sg);
+                double gap = (double)(rg.n_sat - n_sg);
+                gap = gap < 1.0 ? 1.0 : gap;
+                double pw = gap;
+                for (int32_t i = 1; i < rg.beta; ++i) pw = __dmul_rn(pw, gap);
+                const double lat = __dadd_rn(__dadd_rn(__dmul_rn(rg.a, (double)n_sg), rg.b), __ddiv_rn(rg.d, pw));
+                rg_ewma = t == 0 ? lat
+                                 : __dadd_rn(__dmul_rn(rg.alpha, lat), __dmul_rn(__dsub_rn(1.0, rg.alpha), rg_ewma));
+                if (rg_r == 0) {
+                    rg_up = rg_ewma > rg.theta1 ? rg_up + 1 : 0;
+                    if (rg_up >= rg.k) {
+                        rg_r = 1;
+                        rg_up = rg_down = 0;
+                        tot4 += 1;
+                    }
+                } else if (rg_r == 1) {
+                    rg_up = rg_ewma >= rg.theta2 ? rg_up + 1 : 0;
+                    rg_down = rg_ewma < __dsub_rn(rg.theta1, rg.eps) ? rg_down + 1 : 0;
+                    if (rg_up >= rg.k) {
+                        rg_r = 2;
+                        rg_up = rg_down = 0;
+                        tot4 += 1;
+                    } else if (rg_down >= rg.k) {
+                        rg_r = 0;
+                        rg_up = rg_down = 0;
+                    }
+                } else {
+                    rg_down = rg_ewma < __dsub_rn(rg.theta2, rg.eps) ? rg_down + 1 : 0;
+                    if (rg_down >= rg.k) {
+                        rg_r = 1;
+                        rg_up = rg_down = 0;
+                    }
+                }
+                rg_r = uni(rg_r);
+                rg_up = uni(rg_up);
+                rg_down = uni(rg_down);
+            }
+            if (ctrl) {
+                u_tot += P;
+                if (t >= c.ctrl_window)
+                    u_sum -= (int64_t)(((uint64_t)(uint32_t)uni((int32_t)(u_old >> 32)) << 32) | (uint32_t)uni((int32_t)u_old));
+                if (lane == 0) s_u[c_pos] = u_tot;
+                u_sum += u_tot;
+                c_pos = c_pos + 1 == c.ctrl_window ? 0 : c_pos + 1;
+            }
+            cost_p += W;
+            ++t;
+            ++r_in_step;
+            ++held;
+            if (b + 1 - pub >= group) publish(b + 1);
+            if (scan) {              // any route may change any later one's overlaps on its worker
+                event = EV_FLUSH;
+                go = false;
+                break;
+            }
         }
-        tot0 += P - osg;
-        tot2 += P;
-        tot6 += osg;
-        ++t;
-        ++r_in_step;
-        ep_wave_sync();
-        if (lane == 0) __hip_atomic_store(&sh->decided, b + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    if (lane < W) {
-        s_A[lane] = rA;
-        s_N[lane] = rN;
-        s_tail[lane] = rtail;
-        s_live[lane] = rlive;
-        s_used[lane] = rused;
+    if (pub < t - t0) publish(t - t0);
+    if (wl) {
+        s_w[WA_A * W + lane] = rA;
+        if (FULL) s_w[WA_N * W + lane] = rN;
+        s_w[WA_TAIL * W + lane] = (int32_t)rtail;
+        s_w[WA_LIVE * W + lane] = rlive;
+        s_w[WA_USED * W + lane] = rused;
     }
+    const int64_t sum_new = (int64_t)wave_sum_u64((uint64_t)acc_new), sum_P = (int64_t)wave_sum_u64((uint64_t)acc_P);
     if (lane == 0) {
+        st->t = t;
+        st->s = s;
+        st->r_in_step = r_in_step;
+        st->n_step = n_step;
+        st->s_slot = s_slot;
+        st->c_pos = c_pos;
+        st->room_t = room_t;
+        st->step_open = step_open;
+        st->prev_active = prev_active;
+        st->u_sum = u_sum;
+        st->u_tot = u_tot;
+        st->held = held;
+        if (regime) {
+            st->rg_r = rg_r;
+            st->rg_up = rg_up;
+            st->rg_down = rg_down;
+            st->rg_ewma = rg_ewma;
+        }
+        st->tot[0] += sum_new;
+        st->tot[2] += sum_P;
+        st->tot[3] += tot3;
+        st->tot[4] += tot4;
+        if (tot5 >= 0) st->tot[5] = tot5;
+        st->tot[6] += sum_P - sum_new;
         sh->qhead = q_head;
         sh->qsize = q_size;
         sh->event = event;
@@ -1563,23 +1777,6 @@ __device__ __noinline__ void lean_decide(const LeanCtx c_arg, LeanState* st_arg)
         sh->tdone = t;
         __hip_atomic_store(&sh->stop, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    st->t = t;
-    st->s = s;
-    st->r_in_step = r_in_step;
-    st->n_step = n_step;
-    st->s_slot = s_slot;
-    st->c_pos = c_pos;
-    st->room_b = room_b;
-    st->step_open = step_open;
-    st->prev_active = prev_active;
-    st->u_sum = u_sum;
-    st->u_tot = u_tot;
-    st->tot[0] = tot0;
-    st->tot[2] = tot2;
-    st->tot[3] = tot3;
-    st->tot[4] = tot4;
-    st->tot[5] = tot5;
-    st->tot[6] = tot6;
 }
 
 template <bool Queued, int NT>
@@ -2523,17 +2720,63 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
         __syncthreads();
     };
 
-    // state of the routing sequence, kept by wavefront 0
-    int32_t t = 0, s = 0, r_in_step = 0, n_step = 0;
-    int32_t s_slot = 0;                            // s % H
-    int32_t c_pos = 0;                             // t % ctrl_window (load controller)
-    int32_t room_b = -1;                           // route last stopped for a compaction
-    const float inv_cap = (prm.cap_blocks & (prm.cap_blocks - 1)) == 0 ? 1.0f / (float)prm.cap_blocks : 0.0f;
-    bool step_open = false, prev_active = false;
-    int64_t tot[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    int64_t u_sum = 0, u_tot = 0;
-    double rg_ewma = 0.0;                          // regime controller: smoothed latency, regime,
-    int32_t rg_r = 0, rg_up = 0, rg_down = 0;      // hysteresis counters
+    // what the decision loop reads, and the routing sequence's state
+    if (tid == 0) {
+        DecideCtx& c = sh.ctx;
+        c.s_w = lds_off(s_A);
+        c.s_fl = lds_off(s_stw);
+        c.s_u = lds_off(s_u);
+        c.r_c = lds_off(r_c);
+        c.o_cur = lds_off(o_cur);
+        c.o_tab = lds_off(o_tab);
+        c.wend = lds_off(r_wend);
+        c.evd = lds_off(r_evd);
+        c.rnd = lds_off(r_rnd);
+        c.t1 = lds_off(t1_tab);
+        c.t12 = lds_off(t12_tab);
+        c.W = W;
+        c.NB = NB;
+        c.H = H;
+        c.rps = rps;
+        c.max_inflight = a.max_inflight;
+        c.qcap = qcap;
+        c.cache = a.cache;
+        c.ctrl_window = prm.ctrl_window;
+        c.cap_blocks = prm.cap_blocks;
+        c.policy = policy;
+        c.dsteps = dsteps;
+        c.opt = (freq ? OPT_FREQ : 0) | (tiers ? OPT_TIERS : 0) | (scan ? OPT_SCAN : 0) |
+                (regime_ctl ? OPT_REGIME : 0) | (prm.controller == 1 ? OPT_CTRL : 0);
+        c.w_ov = prm.w_ov;
+        c.w_act = prm.w_act;
+        c.w_sat = prm.w_sat;
+        c.ctrl_w_ov = prm.ctrl_w_ov;
+        c.inv_cap = (prm.cap_blocks & (prm.cap_blocks - 1)) == 0 ? 1.0f / (float)prm.cap_blocks : 0.0f;
+        c.tau = tau;
+        c.tw0 = prm.tier_w[0];
+        c.tw1 = prm.tier_w[1];
+        c.tw2 = prm.tier_w[2];
+        c.g_hist = g_hist;
+        c.g_next = g_next;
+        c.g_queue = g_queue;
+        c.out_cost = a.out.cost;
+        c.out_tier = a.out.tier_overlap;
+        c.status = a.status;
+        c.out_base = prm.out_base;
+        // den * sum > num * window * W * cap, both sides integers and den >= 1
+        c.ctrl_max = prm.controller == 1
+                         ? (int64_t)prm.ctrl_num * prm.ctrl_window * W * (int64_t)prm.cap_blocks / prm.ctrl_den : 0;
+        c.used_limit = used_limit;
+        c.R = R;
+        DecideState& z = sh.st;
+        z.t = z.s = z.r_in_step = z.n_step = z.s_slot = z.c_pos = z.step_open = z.prev_active = 0;
+        z.rg_r = z.rg_up = z.rg_down = z.u_tot = z.held = 0;
+        z.room_t = -1;
+        z.rg_ewma = 0.0;
+        z.u_sum = 0;
+        for (int k = 0; k < 8; ++k) z.tot[k] = 0;
+        sh.regime = a.regime;
+    }
 
     // Longest common prefix of npair pairs of chains (all threads): pair(q, ca, cb, m, b1, b2)
     // names pair q's chain bases, the lesser length and two indices for store(q, b1, b2, lcp).
@@ -3031,7 +3274,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
         // runs (no recency kept: the run index is all the searches read) and the queue already
         // holds all of the next batch
         bool job = false;
-        if (lean || lean_ctrl) {
+        if (!eager) {
             bool stamped_any = false;
             for (int32_t j = 0; j < W; ++j) stamped_any |= s_stamped[j] != 0;
             job = !stamped_any && sh.qsize >= nb + NB;
@@ -3059,335 +3302,12 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
         }
 
         // ---- B. routing decisions in order (wavefront 0); stops for a flush, a new batch or the end
-        const int32_t t0 = t;
+        if (tid == 0) {
+            sh.ctx.nb = nb;
+            sh.ctx.t0 = tb0;
+            sh.ctx.lcp = lds_off(l_lcp);
+        }
         int32_t event = EV_BATCH;
-        // ---- B. the decisions of wavefront 0 (below).  LN: the episode runs in prefix
-        // mode, routed by argmin under LRU, without memory tiers or the regime controller
-        // (LC: with the load controller, else without); those copies of the decision loop
-        // are compiled with the other features switched off, which shortens the serial
-        // decision chain.
-        auto decide = [&](auto lean_tag) {
-            constexpr bool LN = decltype(lean_tag)::value != 0;
-            constexpr bool LC = decltype(lean_tag)::value == 2;
-            const bool freq_d = !LN && freq, tiers_d = !LN && tiers, regime_d = !LN && regime_ctl, scan_d = !LN && scan;
-            const bool ctrl1_d = LC || (!LN && prm.controller == 1);
-            const int32_t policy_d = LN ? RK_POLICY_ARGMIN : policy;
-            event = EV_BATCH;
-            // lane j < W keeps worker j's load, log tail and block counts in registers
-            int32_t rA = 0, rlive = 0, rused = 0, rN = 0;
-            uint32_t rtail = 0;
-            int32_t run_ep = -1;   // decay epoch of the routes decided since the last sync
-            int32_t q_head = sh.qhead, q_size = sh.qsize;   // the ready queue, kept in registers
-            if (lane < W) {
-                rA = s_A[lane];
-                rN = s_N[lane];
-                rtail = s_tail[lane];
-                rlive = s_live[lane];
-                rused = s_used[lane];
-            }
-            // workers that keep recency (write log records)
-            const unsigned long long stamped_mask = __ballot(lane < W && s_stamped[lane] != 0);
-            // writes of the batch's routes decided so far (run-index entries or touches; the
-            // decisions go on in the same batch after a stop)
-            int32_t rwork = t > t0 ? r_wend[t - t0 - 1] : 0;
-            uint64_t dirty = 0ull;   // workers to settle (evictions, tier boundaries)
-            for (;;) {
-                if (!step_open) {
-                    // release the routes of step s - H; queue their conversations' next turns
-                    const int32_t slot = s_slot, sb = slot * rps;
-                    if (s >= H) {
-                        if (lane < W) {
-                            s_A[lane] = rA;
-                            s_N[lane] = rN;
-                        }
-                        ep_wave_sync();
-                        const int32_t nprev = s_stepn[slot];
-                        const int32_t qtail = q_head + q_size;
-                        int32_t pushed = 0, rel = 0;
-                        for (int32_t base = 0; base < nprev; base += 64) {
-                            const int32_t r = base + lane;
-                            bool more = false;
-                            int32_t c = 0;
-                            if (r < nprev) {
-                                const int32_t cc = s_stc[sb + r];
-                                c = cc & ~kMoreTurns;
-                                more = (cc & kMoreTurns) != 0;
-                                rel += s_stP[sb + r];
-                                atomicSub(&s_A[s_stw[sb + r]], s_stP[sb + r]);
-                                atomicSub(&s_N[s_stw[sb + r]], 1);
-                            }
-                            const unsigned long long mb = __ballot(more);
-                            if (more) {
-                                int32_t qi = qtail + pushed + __popcll(mb & ((1ull << lane) - 1ull));
-                                g_queue[qi >= qcap ? qi - qcap : qi] = c;
-                            }
-                            pushed += __popcll(mb);
-                        }
-                        u_tot -= wave_sum_i32(rel);
-                        ep_wave_sync();
-                        q_size += pushed;
-                        if (lane < W) {
-                            rA = s_A[lane];
-                            rN = s_N[lane];
-                        }
-                        ep_wave_sync();
-                    }
-                    int32_t inflight = 0;
-                    for (int32_t k = 1; k < H && k <= s; ++k) inflight += s_stepn[s_slot >= k ? s_slot - k : s_slot - k + H];
-                    const int32_t qs = q_size;
-                    if (qs == 0 && inflight == 0) {
-                        event = EV_DONE;
-                        break;
-                    }
-                    n_step = min(rps, qs);
-                    if (lane == 0) s_stepn[slot] = n_step;
-                    if (n_step > 0) tot[5] = s + 1;
-                    r_in_step = 0;
-                    step_open = true;
-                    ep_wave_sync();
-                }
-                if (r_in_step >= n_step) {
-                    ++s;
-                    s_slot = s_slot + 1 == H ? 0 : s_slot + 1;
-                    step_open = false;
-                    continue;
-                }
-                const int32_t b = t - t0;
-                if (b >= nb) break;
-                if (__builtin_expect(freq_d, 0)) {
-                    // a new decay epoch waits until the earlier epoch's cache writes are in
-                    const int32_t ep = s / dsteps;
-                    if (run_ep >= 0 && ep != run_ep) {
-                        event = EV_EPOCH;
-                        break;
-                    }
-                    run_ep = ep;
-                }
-                // one route: controller, cost of every worker, argmin
-                const int32_t slot = s_slot, sb = slot * rps;
-                bool active = false;
-                if (__builtin_expect(ctrl1_d && t >= prm.ctrl_window, 0))
-                    active = (int64_t)prm.ctrl_den * u_sum >
-                             (int64_t)prm.ctrl_num * prm.ctrl_window * W * (int64_t)prm.cap_blocks;
-                float w = prm.w_ov;
-                if (active) w = fminf(prm.w_ov, prm.ctrl_w_ov);
-                int32_t pol = policy_d;
-                float tau_r = tau;
-                if (__builtin_expect(regime_d, 0)) {
-                    w = rg.w_ov[rg_r];
-                    tau_r = rg.tau[rg_r];
-                    pol = tau_r > 0.0f ? RK_POLICY_SOFTMAX : RK_POLICY_ARGMIN;
-                }
-                const int32_t P = r_P[b];
-                const int64_t row = prm.out_base + (int64_t)t;
-                uint32_t bits = 0xFFFFFFFFu;
-                int32_t oj = 0;
-                float cj = 0.0f;
-                if (lane < W) oj = o_cur[b * W + lane];
-                if (__builtin_expect((__ballot(oj > 0) & dirty) != 0ull, 0)) {
-                    event = EV_FLUSH;
-                    break;
-                }
-                if (lane < W) {
-                    if (__builtin_expect(tiers_d, 0)) {
-                        const int32_t o1 = t1_tab[b * W + lane], o12 = t12_tab[b * W + lane];
-                        cj = route_cost_tiers(w, prm.w_act, prm.w_sat, prm.cap_blocks, P, oj, o1, o12,
-                                              prm.tier_w, rA);
-                        if (a.out.tier_overlap) {
-                            a.out.tier_overlap[(row * W + lane) * 2] = o1;
-                            a.out.tier_overlap[(row * W + lane) * 2 + 1] = o12;
-                        }
-                    } else {
-                        cj = route_cost_ep(w, prm.w_act, prm.w_sat, prm.cap_blocks, inv_cap, P, oj, rA);
-                    }
-                    if (a.out.cost) a.out.cost[row * W + lane] = cj;
-                    bits = __float_as_uint(__fadd_rn(cj, 0.0f));
-                }
-                int32_t sg;
-                if (__builtin_expect(pol == RK_POLICY_ARGMIN, 1)) {
-                    const uint32_t mn = ep_wave_min_u32(bits);
-                    sg = __ffsll(__ballot(lane < W && bits == mn)) - 1;
-                } else if (pol == RK_POLICY_SOFTMAX) {
-                    // weights exp((c_min - c_j) / tau); running sums in worker order
-                    const float cmin = __uint_as_float(ep_wave_min_u32(bits));
-                    const float ej = lane < W ? exp_neg_f32(__fdiv_rn(__fsub_rn(cmin, cj), tau_r)) : 0.0f;
-                    float total = 0.0f;
-                    for (int32_t j = 0; j < W; ++j)
-                        total = __fadd_rn(total, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ej), j)));
-                    const float u = __fmul_rn((float)(r_rnd[2 * b] >> 8), 5.9604644775390625e-8f);
-                    const float thr = __fmul_rn(u, total);
-                    float run = 0.0f;
-                    int32_t last = 0;
-                    sg = -1;
-                    for (int32_t j = 0; j < W && sg < 0; ++j) {
-                        const float e = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ej), j));
-                        run = __fadd_rn(run, e);
-                        if (e > 0.0f) last = j;
-                        if (run > thr) sg = j;
-                    }
-                    if (sg < 0) sg = last;
-                } else if (pol == RK_POLICY_ROUND_ROBIN) {
-                    sg = t % W;
-                } else {
-                    const int32_t ca = (int32_t)(((uint64_t)r_rnd[2 * b] * (uint64_t)W) >> 32);
-                    sg = ca;
-                    if (pol == RK_POLICY_P2C && W > 1) {
-                        int32_t cb2 = (int32_t)(((uint64_t)r_rnd[2 * b + 1] * (uint64_t)(W - 1)) >> 32);
-                        if (cb2 >= ca) ++cb2;
-                        const float fa = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cj), ca));
-                        const float fb = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cj), cb2));
-                        if (fb < fa || (fb == fa && cb2 < ca)) sg = cb2;
-                    }
-                }
-                if (__builtin_expect(((dirty >> sg) & 1ull) != 0, 0)) {
-                    event = EV_FLUSH;
-                    break;
-                }
-                const int32_t osg = __builtin_amdgcn_readlane(oj, sg);
-                const int32_t live_after = __builtin_amdgcn_readlane(rlive, sg) + (scan_d ? 0 : P - osg);
-                const uint32_t base = (uint32_t)__builtin_amdgcn_readlane((int)rtail, sg);
-                const bool flush = scan_d || tiers_d || live_after > a.cache;
-                // a worker that keeps recency needs log records for the route's P touches and slots
-                // for its new blocks: without room, stop before the route and compact that worker
-                // (the cached sets and loads stay as they are, so the route is decided again alike)
-                if (__builtin_expect((stamped_mask >> sg) & 1ull, 0)) {
-                    const uint32_t head = s_head[sg];
-                    const uint64_t add = scan_d ? (uint64_t)P : (uint64_t)(P - osg);
-                    if ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(rused, sg) + add > used_limit ||
-                        (uint64_t)(base - head) + (uint64_t)P > R || (uint64_t)base + (uint64_t)P > 0x40000000u) {
-                        if (room_b == t) {
-                            // still no room right after a compaction (the workspace layout always
-                            // leaves room for one route): report it and go on
-                            if (lane == 0) atomicOr(a.status, RK_DEV_TABLE_FULL);
-                        } else {
-                            room_b = t;
-                            if (lane == 0) sh.ev_b = sg;
-                            event = EV_ROOM;
-                            break;
-                        }
-                    }
-                }
-                if (active) {
-                    tot[3] += 1;
-                    if (!prev_active) tot[4] += 1;
-                }
-                prev_active = active;
-                if (regime_d && rg_r > 0) tot[3] += 1;
-                const int32_t rc = r_c[b];
-                if (lane == sg) {
-                    rA += P;
-                    rN += 1;
-                    rtail = base + (uint32_t)P;
-                    if (!scan_d) {
-                        rlive = live_after;
-                        rused += P - osg;
-                    }
-                }
-                rwork += ((stamped_mask >> sg) & 1ull) ? P : (osg < P ? run_entries(osg, P) : 0);
-                if (lane == 0) {
-                    r_sig[b] = sg;
-                    r_wend[b] = rwork;
-                    r_stamp[b] = base;
-                    r_ep[b] = freq_d ? (uint32_t)run_ep : 0u;
-                    g_hist[2 * t] = rc & ~kMoreTurns;
-                    g_hist[2 * t + 1] = P | (sg << 16);
-                    r_otab[b] = o_tab[b * W + sg];
-                    s_stw[sb + r_in_step] = sg;
-                    s_stP[sb + r_in_step] = P;
-                    s_stc[sb + r_in_step] = rc;
-                    g_next[rc & ~kMoreTurns] = r_k[b] + 1;
-                    r_step[b] = (int32_t)s;
-                    r_reg[b] = regime_d ? rg_r : 0;
-                    r_evc[b] = 0;
-                    r_evd[b] = 0ull;
-                    if (flush) s_evb[sg] = b;
-                }
-                if (flush) dirty |= 1ull << sg;
-                u_tot += P;
-                q_head = q_head + 1 == qcap ? 0 : q_head + 1;
-                q_size -= 1;
-                if (__builtin_expect(regime_d, 0)) {
-                    // the chosen worker's latency with the new request (already counted in
-                    // lane sg's rN) stands in for TTFT (fp64)
-                    const int32_t n_sg = __builtin_amdgcn_readlane(rN, sg);
-                    double gap = (double)(rg.n_sat - n_sg);
-                    gap = gap < 1.0 ? 1.0 : gap;
-                    double pw = gap;
-                    for (int32_t i = 1; i < rg.beta; ++i) pw = __dmul_rn(pw, gap);
-                    const double lat = __dadd_rn(__dadd_rn(__dmul_rn(rg.a, (double)n_sg), rg.b), __ddiv_rn(rg.d, pw));
-                    rg_ewma = t == 0 ? lat
-                                     : __dadd_rn(__dmul_rn(rg.alpha, lat), __dmul_rn(__dsub_rn(1.0, rg.alpha), rg_ewma));
-                    if (rg_r == 0) {
-                        rg_up = rg_ewma > rg.theta1 ? rg_up + 1 : 0;
-                        if (rg_up >= rg.k) {
-                            rg_r = 1;
-                            rg_up = rg_down = 0;
-                            tot[4] += 1;
-                        }
-                    } else if (rg_r == 1) {
-                        rg_up = rg_ewma >= rg.theta2 ? rg_up + 1 : 0;
-                        rg_down = rg_ewma < __dsub_rn(rg.theta1, rg.eps) ? rg_down + 1 : 0;
-                        if (rg_up >= rg.k) {
-                            rg_r = 2;
-                            rg_up = rg_down = 0;
-                            tot[4] += 1;
-                        } else if (rg_down >= rg.k) {
-                            rg_r = 0;
-                            rg_up = rg_down = 0;
-                        }
-                    } else {
-                        rg_down = rg_ewma < __dsub_rn(rg.theta2, rg.eps) ? rg_down + 1 : 0;
-                        if (rg_down >= rg.k) {
-                            rg_r = 1;
-                            rg_up = rg_down = 0;
-                        }
-                    }
-                }
-                if (__builtin_expect(ctrl1_d, 0)) {
-                    const int32_t pos = c_pos;
-                    c_pos = c_pos + 1 == prm.ctrl_window ? 0 : c_pos + 1;
-                    if (t >= prm.ctrl_window) u_sum -= s_u[pos];
-                    ep_wave_sync();
-                    if (lane == 0) s_u[pos] = u_tot;
-                    u_sum += u_tot;
-                }
-                tot[0] += P - osg;
-                tot[2] += P;
-                tot[6] += osg;
-                // later requests of the batch now find this chain on sg
-                if (!scan_d) {
-                    const int32_t b2 = b + 1 + lane;
-                    if (b2 < nb) {
-                        const int32_t l = l_lcp[b * NB + b2];
-                        if (l > o_cur[b2 * W + sg]) o_cur[b2 * W + sg] = l;
-                    }
-                }
-                ++t;
-                ++r_in_step;
-                ep_wave_sync();
-                if (lane == 0)
-                    __hip_atomic_store(&sh.decided, b + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (scan_d) {              // any route may change any later one's overlaps on its worker
-                    event = EV_FLUSH;
-                    break;
-                }
-            }
-            if (lane < W) {
-                s_A[lane] = rA;
-                s_N[lane] = rN;
-                s_tail[lane] = rtail;
-                s_live[lane] = rlive;
-                s_used[lane] = rused;
-            }
-            if (lane == 0) {
-                sh.qhead = q_head;
-                sh.qsize = q_size;
-                sh.event = event;
-                sh.dirty = dirty;
-                sh.tdone = t;
-                __hip_atomic_store(&sh.stop, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-        };
         nb_cur = nb;
         bool had_stop = false;      // an eviction, compaction or epoch stop in this batch
         bool job_ran = false;
@@ -3395,99 +3315,10 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
             if (wave == 0) {
                 // the serial chain of decisions goes first on its SIMD
                 __builtin_amdgcn_s_setprio(3);
-                if (!Queued && (lean || lean_ctrl) && t == t0) {
-                    // a batch's first decisions in the one-episode kernel: the lean loop as a function
-                    // of its own (the queued kernel, and the decisions after a stop, keep the copy
-                    // inside the kernel and spare the call's register saves)
-                    LeanCtx lc;
-                    lc.sh = lds_off(&sh);
-                    lc.s_A = lds_off(s_A);
-                    lc.s_N = lds_off(s_N);
-                    lc.s_tail = lds_off(s_tail);
-                    lc.s_live = lds_off(s_live);
-                    lc.s_used = lds_off(s_used);
-                    lc.s_head = lds_off(s_head);
-                    lc.s_stamped = lds_off(s_stamped);
-                    lc.s_evb = lds_off(s_evb);
-                    lc.s_stw = lds_off(s_stw);
-                    lc.s_stP = lds_off(s_stP);
-                    lc.s_stc = lds_off(s_stc);
-                    lc.s_stepn = lds_off(s_stepn);
-                    lc.s_u = lds_off(s_u);
-                    lc.r_P = lds_off(r_P);
-                    lc.r_c = lds_off(r_c);
-                    lc.r_k = lds_off(r_k);
-                    lc.o_cur = lds_off(o_cur);
-                    lc.o_tab = lds_off(o_tab);
-                    lc.lcp = lds_off(l_lcp);
-                    lc.r_sig = lds_off(r_sig);
-                    lc.r_wend = lds_off(r_wend);
-                    lc.r_stamp = lds_off(r_stamp);
-                    lc.r_ep = lds_off(r_ep);
-                    lc.r_otab = lds_off(r_otab);
-                    lc.r_step = lds_off(r_step);
-                    lc.r_reg = lds_off(r_reg);
-                    lc.r_evc = lds_off(r_evc);
-                    lc.r_evd = lds_off(r_evd);
-                    lc.g_hist = (glb_p<int32_t>)g_hist;
-                    lc.g_next = (glb_p<int32_t>)g_next;
-                    lc.g_queue = (glb_p<int32_t>)g_queue;
-                    lc.out_cost = (glb_p<float>)a.out.cost;
-                    lc.status = (glb_p<int32_t>)a.status;
-                    lc.out_base = prm.out_base;
-                    lc.ctrl_thr = (int64_t)prm.ctrl_num * prm.ctrl_window * W * (int64_t)prm.cap_blocks;
-                    lc.used_limit = used_limit;
-                    lc.R = R;
-                    lc.W = W;
-                    lc.NB = NB;
-                    lc.nb = nb;
-                    lc.t0 = t0;
-                    lc.H = H;
-                    lc.rps = rps;
-                    lc.qcap = qcap;
-                    lc.cache = a.cache;
-                    lc.ctrl_window = prm.ctrl_window;
-                    lc.ctrl_den = prm.ctrl_den;
-                    lc.cap_blocks = prm.cap_blocks;
-                    lc.w_ov = prm.w_ov;
-                    lc.w_act = prm.w_act;
-                    lc.w_sat = prm.w_sat;
-                    lc.ctrl_w_ov = prm.ctrl_w_ov;
-                    lc.inv_cap = inv_cap;
-                    LeanState ls;
-                    ls.t = t;
-                    ls.s = s;
-                    ls.r_in_step = r_in_step;
-                    ls.n_step = n_step;
-                    ls.s_slot = s_slot;
-                    ls.c_pos = c_pos;
-                    ls.room_b = room_b;
-                    ls.step_open = step_open;
-                    ls.prev_active = prev_active;
-                    ls.u_sum = u_sum;
-                    ls.u_tot = u_tot;
-                    for (int k = 0; k < 8; ++k) ls.tot[k] = tot[k];
-                    if (lean_ctrl) lean_decide<true>(lc, &ls);
-                    else lean_decide<false>(lc, &ls);
-                    t = ls.t;
-                    s = ls.s;
-                    r_in_step = ls.r_in_step;
-                    n_step = ls.n_step;
-                    s_slot = ls.s_slot;
-                    c_pos = ls.c_pos;
-                    room_b = ls.room_b;
-                    step_open = ls.step_open != 0;
-                    prev_active = ls.prev_active != 0;
-                    u_sum = ls.u_sum;
-                    u_tot = ls.u_tot;
-                    for (int k = 0; k < 8; ++k) tot[k] = ls.tot[k];
-                } else if (lean) {
-                    decide(LeanTag<1>{});
-                } else if (lean_ctrl) {
-                    decide(LeanTag<2>{});
-                } else {
-                    decide(LeanTag<0>{});
-                }
+                ep_wave_sync();
+                if (lean) decide_routes<1>(lds_off(&sh));
+                else if (lean_ctrl) decide_routes<2>(lds_off(&sh));
+                else decide_routes<0>(lds_off(&sh));
                 __builtin_amdgcn_s_setprio(0);
                 writer();           // the decided routes not yet claimed
             } else {
@@ -3591,9 +3422,9 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
     if (tid == 0 && a.out.totals) {
         int64_t cachedsum = 0;
         for (int32_t j = 0; j < W; ++j) cachedsum += s_live[j];
-        tot[1] = (int64_t)sh.ev_total;
-        tot[7] = cachedsum;
-        for (int k = 0; k < 8; ++k) a.out.totals[(int64_t)e * 8 + k] = tot[k];
+        sh.st.tot[1] = (int64_t)sh.ev_total;
+        sh.st.tot[7] = cachedsum;
+        for (int k = 0; k < 8; ++k) a.out.totals[(int64_t)e * 8 + k] = sh.st.tot[k];
     }
     }();
     __syncthreads();
