@@ -133,13 +133,14 @@ struct DecideState {
 };
 
 struct EpShared {
-    int32_t next_e, nlist, jn, jsync, jnext, jp, jpnext, jq, jqnext;
+    int32_t next_e, nlist, jn, jsync, jnext, jq;
     int32_t qhead, qsize, nb, event, ev_b, ins, decided, claimed, stop, tdone;
     unsigned long long ev_total, dirty;
     int32_t wtot[kMaxWaves];
     DecideCtx ctx;
     DecideState st;
     rk_regime_params regime;
+    uint32_t lead[2 * kMaxBatch];   // longest route of each prefix group of the batch and of the next one
 };
 
 // NT below: the threads of the episode's workgroup.
@@ -695,6 +696,7 @@ static __device__ __forceinline__ uint32_t ep_wave_min_u32(uint32_t v)
 
 constexpr int KI = 4;   // searches a thread keeps in flight together
 constexpr int KP = 4;   // batch pairs a thread searches together for their common prefix
+constexpr int32_t kSearchPair = 0x8000;   // on a pair's common prefix (below 2^14): a lower bound so far
 
 // Longest cached prefix for items i = threadIdx.x, + NT, ... < n: item i
 // names a chain, its length, its hash at block 0 and a worker table (info,
@@ -2895,9 +2897,8 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
     // run-index search of run_searches: a first probe of block 0 settles the misses and lists the
     // rest; once these waves have listed theirs, the listed items are searched with KI slots
     // per thread, each slot taking the next listed item when its search ends.
-    auto job_search_part = [&]() {
-        enum : int32_t { DONE = 0, HASH = 1, LOOK = 2, CMP = 3, CKPT = 4 };
-        constexpr int NJ = NT - 128;                 // the searching threads
+    auto job_probe_part = [&]() {
+        constexpr int NJ = NT - 128;                 // the probing threads
         const int32_t tj = tid - 64;
         const int32_t n = NB * W;
         for (int32_t base = 0; base < n; base += NJ * KI) {
@@ -2933,9 +2934,12 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                 if (hit) l_items[wb + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)i;
             }
         }
-        // barrier of the searching waves: their lists are complete
         ep_wave_sync();
         if (lane == 0) __hip_atomic_fetch_add(&sh.jsync, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto job_list_part = [&]() {
+        enum : int32_t { DONE = 0, HASH = 1, LOOK = 2, CMP = 3, CKPT = 4 };
+        // the probing waves' lists are complete
         while (__builtin_amdgcn_readfirstlane(
                    __hip_atomic_load(&sh.jsync, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) < NW - 2)
             __builtin_amdgcn_s_sleep(1);
@@ -3084,46 +3088,95 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
             }
         }
     };
+    // The common prefixes of the next batch's pairs, into nx_lcp, and of its routes with this batch's
+    // (nb_cur routes), listed in l_pairs (next route << 6 | route) with the prefix in l_pval (one
+    // wavefront, lane i for next route i and for route i).  Of three chains the two least common
+    // prefixes are equal, so a route's prefix with one route of its group settles most of its
+    // pairs: with a, b the prefixes of two routes with that leader, theirs is min(a, b) unless
+    // a = b, and then at least a.  The leader is the group's longest route of this batch (whose
+    // prefixes among themselves are known), or else of the next one; only the pairs with a = b are
+    // searched, from a on.
     auto job_pair_part = [&]() {
-        // ---- common prefixes of pairs (pair(q, ...) as for pair_lcps): direct(q, b1, b2, same, m)
-        //      stores a pair's prefix at once or returns true to list the pair; the listed pairs are
-        //      searched with KP slots per thread, each taking the next listed pair when its search
-        //      ends, store(listed index, q, prefix)
-        auto job_pairs = [&](int32_t npair, int32_t* cnt, int32_t* next, const auto& pair, const auto& direct,
-                             const auto& store) {
-            for (int32_t q0 = 0; q0 < npair; q0 += 64) {
-                const int32_t q = q0 + lane;
-                bool lst = false;
-                if (q < npair) {
-                    int64_t ca, cc;
-                    int32_t m, b1, b2;
-                    const bool same = pair(q, ca, cc, m, b1, b2);
-                    lst = direct(q, b1, b2, same, m);
-                }
-                const unsigned long long mb = __ballot(lst);
-                int32_t wb = 0;
-                if (lane == 0 && mb) wb = atomicAdd(cnt, (int32_t)__popcll(mb));
-                wb = __builtin_amdgcn_readfirstlane(wb);
-                if (lst) l_pairs[wb + __popcll(mb & ((1ull << lane) - 1ull))] = (uint16_t)q;
+        const int32_t nbc = nb_cur;
+        const int32_t Pi = lane < NB ? nx_P[lane] : 0, Pc = lane < nbc ? r_P[lane] : 0;
+        const uint64_t fi = Pi > 0 ? nx_first[lane] : 0ull, fc = Pc > 0 ? r_first[lane] : 0ull;   // 0: no route
+        // routes of the lane's group: of this batch for next route i (mi) and route i (mc), of the
+        // next batch (mn)
+        uint64_t mi = 0, mc = 0, mn = 0;
+        for (int32_t k = 0; k < nbc; ++k) {
+            const uint64_t f = readlane64(fc, k);
+            const uint64_t bit = 1ull << k;
+            if (fi == f) mi |= bit;
+            if (fc == f) mc |= bit;
+        }
+        for (int32_t k = 0; k < NB; ++k) {
+            const uint64_t f = readlane64(fi, k);
+            if (fi == f) mn |= 1ull << k;
+        }
+        if (fi == 0ull) mi = mn = 0ull;
+        if (fc == 0ull) mc = 0ull;
+        sh.lead[lane] = 0u;
+        sh.lead[kMaxBatch + lane] = 0u;
+        ep_wave_sync();
+        if (mc) atomicMax(&sh.lead[__ffsll((unsigned long long)mc) - 1], ((uint32_t)Pc << 6) | (uint32_t)lane);
+        if (mn) atomicMax(&sh.lead[kMaxBatch + __ffsll((unsigned long long)mn) - 1], ((uint32_t)Pi << 6) | (uint32_t)lane);
+        ep_wave_sync();
+        // the lane's next route against its leader: a, the common prefix (its own length if it leads)
+        const uint32_t le = mi ? sh.lead[__ffsll((unsigned long long)mi) - 1]
+                               : (mn ? sh.lead[kMaxBatch + __ffsll((unsigned long long)mn) - 1] : 0u);
+        const int32_t ld = (int32_t)(le & 63u);
+        int32_t lo = 0, hi = 0;
+        int64_t ca = 0, cl = 0;
+        if (fi != 0ull) {
+            ca = nx_cb[lane];
+            cl = mi ? r_cb[ld] : nx_cb[ld];
+            hi = min(Pi, (int32_t)(le >> 6));
+            lo = !mi && ld == lane ? hi : 1;       // block 0 is common
+        }
+        while (__ballot(lo < hi)) {
+            // four near-equal parts of [lo, hi): the first differing block's part is kept
+            const int32_t n = hi - lo;
+            const int64_t mk = -(int64_t)(n > 0);
+            int32_t q[3];
+            uint64_t va[3], vb[3];
+#pragma unroll
+            for (int x = 0; x < 3; ++x) {
+                q[x] = lo + (((x + 1) * n) >> 2);
+                if (q[x] >= hi) q[x] = hi - 1;
+                va[x] = a.chains[mk & (ca + q[x])];
+                vb[x] = a.chains[mk & (cl + q[x])];
             }
-            ep_wave_sync();
-            const int32_t nl = __builtin_amdgcn_readfirstlane(
-                __hip_atomic_load(cnt, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
-            int32_t lo[KP], hi[KP], it[KP];
-            int64_t ca[KP], cc[KP];
-            auto takep = [&](int k, int32_t idx) {
-                it[k] = -1;
-                lo[k] = hi[k] = 0;
-                ca[k] = cc[k] = 0;
-                if (idx >= nl) return;
-                int32_t m, b1, b2;
-                it[k] = idx;
-                pair(l_pairs[idx], ca[k], cc[k], m, b1, b2);
-                lo[k] = 1;                 // block 0 is common
-                hi[k] = m;
+            if (n > 0) {
+                if (va[0] != vb[0]) {
+                    hi = q[0];
+                } else if (va[1] != vb[1]) {
+                    lo = q[0] + 1;
+                    hi = q[1];
+                } else if (va[2] != vb[2]) {
+                    lo = q[1] + 1;
+                    hi = q[2];
+                } else {
+                    lo = q[2] + 1;
+                }
+            }
+        }
+        const int32_t av = lo;
+        // pairs that need a search, KP slots per lane: entry idx for which fetch gives the chains, the
+        // first block not known to be common and the lesser length
+        auto search_pairs = [&](int32_t n, const auto& fetch, const auto& store) {
+            int32_t slo[KP], shi[KP], it[KP];
+            int64_t sa[KP], sb[KP];
+            auto take = [&](int k, int32_t idx) {
+                for (; idx < n; idx += 64 * KP)
+                    if (fetch(idx, sa[k], sb[k], slo[k], shi[k])) break;
+                it[k] = idx < n ? idx : -1;
+                if (it[k] < 0) {
+                    slo[k] = shi[k] = 0;
+                    sa[k] = sb[k] = 0;
+                }
             };
 #pragma unroll
-            for (int k = 0; k < KP; ++k) takep(k, atomicAdd(next, 1));
+            for (int k = 0; k < KP; ++k) take(k, 64 * k + lane);
             for (;;) {
                 bool any = false;
 #pragma unroll
@@ -3133,75 +3186,89 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                 uint64_t va[KP], vb[KP];
 #pragma unroll
                 for (int k = 0; k < KP; ++k) {
-                    mid[k] = (lo[k] + hi[k]) >> 1;
-                    const int64_t mk = -(int64_t)(lo[k] < hi[k]);
-                    va[k] = a.chains[mk & (ca[k] + mid[k])];
-                    vb[k] = a.chains[mk & (cc[k] + mid[k])];
+                    mid[k] = (slo[k] + shi[k]) >> 1;
+                    const int64_t mk = -(int64_t)(slo[k] < shi[k]);
+                    va[k] = a.chains[mk & (sa[k] + mid[k])];
+                    vb[k] = a.chains[mk & (sb[k] + mid[k])];
                 }
 #pragma unroll
                 for (int k = 0; k < KP; ++k) {
-                    if (lo[k] < hi[k]) {
-                        if (va[k] == vb[k]) lo[k] = mid[k] + 1;
-                        else hi[k] = mid[k];
+                    if (slo[k] < shi[k]) {
+                        if (va[k] == vb[k]) slo[k] = mid[k] + 1;
+                        else shi[k] = mid[k];
                     }
-                    if (it[k] >= 0 && lo[k] >= hi[k]) {
-                        store(it[k], (int32_t)l_pairs[it[k]], lo[k]);
-                        takep(k, atomicAdd(next, 1));
+                    if (it[k] >= 0 && slo[k] >= shi[k]) {
+                        store(it[k], slo[k]);
+                        take(k, it[k] + 64 * KP);
                     }
                 }
             }
         };
-        // within the next batch, into nx_lcp
-        job_pairs(
-            NB * (NB - 1) / 2, &sh.jp, &sh.jpnext,
-            [&](int32_t q, int64_t& ca, int64_t& cc, int32_t& m, int32_t& b1, int32_t& b2) {
-                b1 = (int32_t)((1.0f + sqrtf(1.0f + 8.0f * (float)q)) * 0.5f);
-                while (b1 > 1 && b1 * (b1 - 1) / 2 > q) --b1;
-                while ((b1 + 1) * b1 / 2 <= q) ++b1;
-                b2 = q - b1 * (b1 - 1) / 2;
-                ca = nx_cb[b1];
-                cc = nx_cb[b2];
-                m = min(nx_P[b1], nx_P[b2]);
-                return m > 0 && nx_first[b1] == nx_first[b2];
+        // within the next batch
+        int32_t n_l = 0;
+        for (int32_t k = 0; k < NB; ++k) {
+            const bool same = lane > k && ((mn >> k) & 1ull);
+            const int32_t ak = __builtin_amdgcn_readlane(av, k);
+            if (lane > k && lane < NB) nx_lcp[k * NB + lane] = (uint16_t)(same ? min(av, ak) : 0);
+            const unsigned long long m = __ballot(same && av == ak);
+            if (same && av == ak) l_pairs[n_l + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(k << 6 | lane);
+            n_l += __popcll(m);
+        }
+        ep_wave_sync();
+        search_pairs(
+            n_l,
+            [&](int32_t idx, int64_t& xa, int64_t& xb, int32_t& xlo, int32_t& xhi) {
+                const int32_t k = l_pairs[idx] >> 6, i = l_pairs[idx] & 63;
+                xa = nx_cb[i];
+                xb = nx_cb[k];
+                xlo = nx_lcp[k * NB + i];
+                xhi = min(nx_P[i], nx_P[k]);
+                return true;
             },
-            [&](int32_t q, int32_t b1, int32_t b2, bool same, int32_t m) {
-                if (same && m > 1) return true;
-                nx_lcp[b2 * NB + b1] = (uint16_t)(same && m > 0 ? 1 : 0);
-                return false;
-            },
-            [&](int32_t idx, int32_t q, int32_t l) {
-                int32_t b1 = (int32_t)((1.0f + sqrtf(1.0f + 8.0f * (float)q)) * 0.5f);
-                while (b1 > 1 && b1 * (b1 - 1) / 2 > q) --b1;
-                while ((b1 + 1) * b1 / 2 <= q) ++b1;
-                nx_lcp[(q - b1 * (b1 - 1) / 2) * NB + b1] = (uint16_t)l;
-            });
+            [&](int32_t idx, int32_t l) { nx_lcp[(l_pairs[idx] >> 6) * NB + (l_pairs[idx] & 63)] = (uint16_t)l; });
         ep_wave_sync();            // the within-batch list is no longer read
-        // between the next batch's routes and this batch's (nb routes), every pair whose first
-        // blocks agree listed, its prefix in l_pval: the overlaps rise by them at the next batch
-        const int32_t nbc = nb_cur;
-        job_pairs(
-            NB * nbc, &sh.jq, &sh.jqnext,
-            [&](int32_t q, int64_t& ca, int64_t& cc, int32_t& m, int32_t& b1, int32_t& b2) {
-                b1 = q / nbc;
-                b2 = q - b1 * nbc;
-                ca = nx_cb[b1];
-                cc = r_cb[b2];
-                m = min(nx_P[b1], r_P[b2]);
-                return m > 0 && nx_first[b1] == r_first[b2];
+        // between the next batch's routes and this batch's: the overlaps rise by them at the next batch
+        n_l = 0;
+        for (int32_t k = 0; k < nbc; ++k) {
+            const bool same = ((mi >> k) & 1ull) != 0;
+            const unsigned long long m = __ballot(same);
+            if (m == 0ull) continue;
+            if (same) {
+                const int32_t bk = k == ld ? r_P[k] : l_lcp[min(k, ld) * NB + max(k, ld)];
+                const int32_t idx = n_l + __popcll(m & ((1ull << lane) - 1ull));
+                l_pairs[idx] = (uint16_t)(lane << 6 | k);
+                l_pval[idx] = (uint16_t)(av == bk ? kSearchPair | av : min(av, bk));
+            }
+            n_l += __popcll(m);
+        }
+        if (lane == 0) sh.jq = n_l;
+        ep_wave_sync();
+        search_pairs(
+            n_l,
+            [&](int32_t idx, int64_t& xa, int64_t& xb, int32_t& xlo, int32_t& xhi) {
+                const int32_t v = l_pval[idx];
+                if (!(v & kSearchPair)) return false;
+                const int32_t i = l_pairs[idx] >> 6, k = l_pairs[idx] & 63;
+                xa = nx_cb[i];
+                xb = r_cb[k];
+                xlo = v & (kSearchPair - 1);
+                xhi = min(nx_P[i], r_P[k]);
+                return true;
             },
-            [&](int32_t q, int32_t b1, int32_t b2, bool same, int32_t m) { return same; },
-            [&](int32_t idx, int32_t q, int32_t l) { l_pval[idx] = (uint16_t)l; });
+            [&](int32_t idx, int32_t l) { l_pval[idx] = (uint16_t)l; });
     };
-    // The job's two parts run side by side: waves 1 .. NW-2 search the run index, the last wave
-    // takes the common prefixes of the batch pairs.
+    // The job's parts run side by side: waves 1 .. NW-2 probe the run index, the last wave takes the
+    // common prefixes of the batch pairs, and each then takes listed searches.
     auto next_batch_job = [&]() {
         if (wave == NW - 1) {
             job_pair_part();
         } else {
             __builtin_amdgcn_s_setprio(2);   // the searches end the job: ahead of writers and pairs
-            job_search_part();
-            __builtin_amdgcn_s_setprio(0);
+            job_probe_part();
         }
+        __builtin_amdgcn_s_setprio(2);
+        job_list_part();
+        __builtin_amdgcn_s_setprio(0);
     };
 
     // the next batch's overlaps, computed by the other waves while wavefront 0 decides this batch
@@ -3209,7 +3276,6 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
     // complete and this batch had no eviction, compaction or epoch stop, so the caches grew by
     // this batch's chains only
     bool nx_ready = false;
-    int32_t nb_prev = 0;
     for (;;) {
         // ---- A. the batch: the next nb queued requests (queue order is routing order)
         const int32_t qh0 = sh.qhead;
@@ -3226,9 +3292,8 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
             nx_lcp = tl;
             const int32_t nxl = sh.jq;
             for (int32_t i = tid; i < nxl; i += NT) {
-                const int32_t q = l_pairs[i], l = l_pval[i];
-                const int32_t b1 = q / nb_prev, b2 = q - b1 * nb_prev;
-                if (l > 0) atomicMax(&nx_o[b1 * W + r_sig[b2]], l);
+                const int32_t b1 = l_pairs[i] >> 6, b2 = l_pairs[i] & 63;
+                atomicMax(&nx_o[b1 * W + r_sig[b2]], (int32_t)l_pval[i]);
             }
             __syncthreads();
         }
@@ -3293,10 +3358,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                 sh.jn = 0;
                 sh.jsync = 0;
                 sh.jnext = 0;
-                sh.jp = 0;
-                sh.jpnext = 0;
                 sh.jq = 0;
-                sh.jqnext = 0;
             }
             __syncthreads();
         }
@@ -3416,7 +3478,6 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
         if (tid == 0) sh.ins = 0;
         __syncthreads();
         nx_ready = job_ran && !had_stop && event == EV_BATCH;
-        nb_prev = nb;
         if (event == EV_DONE) break;
     }
     if (tid == 0 && a.out.totals) {
