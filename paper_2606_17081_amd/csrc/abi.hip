@@ -313,40 +313,246 @@ __global__ __launch_bounds__(kFewThreads) void hash_few_kernel(int64_t n_seq, co
 }
 
 // ------------------------------------------------------------------ tables
+//
+// As for the block index (index.hip): tables of 2^kTabLogMin .. 2^kTabLogMax
+// slots are cut into bins of kTabBin consecutive slots, a workgroup sorts a tile
+// of a worker's keys by bin in LDS and appends each run to the bin's list, which
+// lies in the bin itself, and a workgroup per bin then loads the list, builds the
+// bin in LDS and writes it over the list.  Keys that probe past a bin's end wait
+// in a side buffer until every bin is built; what does not fit sets a flag that
+// makes the last two launches build the tables by atomics.
+// 64 tables of 2^20 slots from 33.6 M keys: 2.92 -> 0.46 ms; a quarter full, 1.18 -> 0.27 ms.  One launch for
+// all workers, by atomics or not, takes the place of one for each (64 tables of 2^14 slots: 678 -> 47 us).
+constexpr int kTabBinLog = 14, kTabBin = 1 << kTabBinLog;
+constexpr int kTabLogMin = 15, kTabLogMax = 22;
+constexpr int kTabBins = 1 << (kTabLogMax - kTabBinLog);      // at most, of a table
+constexpr int kTabAllBins = 1 << 16;                          // at most, of a call
+constexpr int kTabSpills = 1 << 15;
+constexpr int64_t kTabSlotsMin = 1ll << 21;   // smaller calls: atomics (2^20 slots: 22-48 us against 34-43)
 
-__global__ __launch_bounds__(256) void table_clear_kernel(uint64_t* __restrict__ t, uint64_t n)
+struct TableSide {
+    int32_t overrun, n_spill, pad[30];
+    uint32_t cursor[kTabAllBins];
+    uint64_t spill_key[kTabSpills];
+    uint64_t spill_at[kTabSpills];                            // first slot to try (over all tables)
+};
+static __device__ TableSide g_table_side[kBuildSides];
+
+struct TableSides {
+    TableSide* addr = nullptr;
+    hipEvent_t used[kBuildSides] = {};
+    uint32_t next = 0;
+};
+static std::mutex g_table_mu;
+static TableSides g_table_sides[64];
+
+__global__ __launch_bounds__(256) void table_clear_kernel(uint64_t* __restrict__ t, uint64_t n, const int32_t* run)
 {
+    if (run && *run == 0) return;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (uint64_t)gridDim.x * blockDim.x)
         t[i] = kEmpty;
 }
 
-__global__ __launch_bounds__(256) void table_insert_kernel(const uint64_t* __restrict__ keys, int64_t n,
-                                                           uint64_t* __restrict__ t, uint64_t mask,
-                                                           int32_t* status)
+// Key into table t from slot s on, by atomics; false when there is no slot.
+__device__ __forceinline__ bool table_insert(uint64_t* t, uint64_t mask, uint64_t s, uint64_t key)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+    for (uint64_t probe = 0; probe <= mask; ++probe) {
+        const unsigned long long prev = atomicCAS((unsigned long long*)&t[s], (unsigned long long)kEmpty,
+                                                  (unsigned long long)key);
+        if (prev == kEmpty || prev == key) return true;
+        s = (s + 1) & mask;
+    }
+    return false;
+}
+
+// blockIdx.y: the table, from j0 on
+__global__ __launch_bounds__(256) void table_insert_kernel(const uint64_t* __restrict__ keys, KeyRanges r, int32_t j0,
+                                                           uint64_t* __restrict__ tables, int32_t log2_slots,
+                                                           int32_t* status, const int32_t* run)
+{
+    if (run && *run == 0) return;
+    const int64_t n = r.off[blockIdx.y + 1];
+    const uint64_t mask = (1ull << log2_slots) - 1;
+    uint64_t* t = tables + ((uint64_t)(j0 + (int32_t)blockIdx.y) << log2_slots);
+    for (int64_t i = r.off[blockIdx.y] + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
         const uint64_t key = keys[i];
         if (key == kEmpty) {
             atomicOr(status, RK_DEV_ZERO_KEY);
             continue;
         }
-        uint64_t s = key & mask;
-        bool done = false;
-        for (uint64_t probe = 0; probe <= mask; ++probe) {
-            unsigned long long prev = atomicCAS((unsigned long long*)&t[s], (unsigned long long)kEmpty,
-                                                (unsigned long long)key);
-            if (prev == kEmpty || prev == key) { done = true; break; }
-            s = (s + 1) & mask;
+        if (!table_insert(t, mask, key & mask, key)) atomicOr(status, RK_DEV_TABLE_FULL);
+    }
+}
+
+__global__ __launch_bounds__(256) void table_side_kernel(TableSide* __restrict__ side, int32_t bins)
+{
+    const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (i == 0) {
+        side->overrun = 0;
+        side->n_spill = 0;
+    }
+    if (i < bins) side->cursor[i] = 0u;
+}
+
+// Keys to the bins' lists.  blockIdx.y: the table, from j0 on; blockIdx.x: the tile of its keys.
+__global__ __launch_bounds__(kBuildThreads) void table_scatter_kernel(const uint64_t* __restrict__ keys, KeyRanges r,
+                                                                      int32_t j0, uint64_t* __restrict__ tables,
+                                                                      int32_t log2_slots, TableSide* __restrict__ side,
+                                                                      int32_t* status)
+{
+    __shared__ uint64_t s_ent[kTile];
+    __shared__ uint8_t s_bin[kTile];
+    __shared__ uint32_t s_cnt[kTabBins], s_off[kTabBins], s_gbase[kTabBins], s_tmp[16];
+    const int tid = threadIdx.x;
+    const int64_t n0 = r.off[blockIdx.y] + (int64_t)blockIdx.x * kTile, n1 = r.off[blockIdx.y + 1];
+    if (n0 >= n1) return;
+    const int32_t j = j0 + (int32_t)blockIdx.y;
+    const uint32_t bins = 1u << (log2_slots - kTabBinLog);
+    if (tid < kTabBins) s_cnt[tid] = 0u;
+    __syncthreads();
+    uint64_t key[kTile / kBuildThreads];
+    uint32_t rank[kTile / kBuildThreads];
+#pragma unroll
+    for (int u = 0; u < kTile / kBuildThreads; ++u) {
+        const int64_t i = n0 + u * kBuildThreads + tid;
+        key[u] = i < n1 ? keys[i] : kEmpty;
+        if (i < n1 && key[u] == kEmpty) atomicOr(status, RK_DEV_ZERO_KEY);
+    }
+#pragma unroll
+    for (int u = 0; u < kTile / kBuildThreads; ++u) {
+        const uint32_t b = (uint32_t)(key[u] >> kTabBinLog) & (bins - 1);
+        rank[u] = key[u] != kEmpty ? atomicAdd(&s_cnt[b], 1u) : 0u;
+    }
+    __syncthreads();
+    if (tid < kTabBins) {
+        const uint32_t c = s_cnt[tid];
+        s_off[tid] = c;
+        uint32_t g = 0;
+        if (c) {
+            g = atomicAdd(&side->cursor[(uint32_t)j * bins + (uint32_t)tid], c);
+            if (g + c > (uint32_t)kTabBin) {
+                atomicOr(&side->overrun, 1);
+                g = 0xFFFFFFFFu;                             // no room: not written
+            }
         }
-        if (!done) atomicOr(status, RK_DEV_TABLE_FULL);
+        s_gbase[tid] = g;
+    }
+    __syncthreads();
+    build_scan(s_off, kTabBins, s_tmp);
+#pragma unroll
+    for (int u = 0; u < kTile / kBuildThreads; ++u) {
+        if (key[u] == kEmpty) continue;
+        const uint32_t b = (uint32_t)(key[u] >> kTabBinLog) & (bins - 1);
+        const uint32_t p = s_off[b] + rank[u];
+        s_ent[p] = key[u];
+        s_bin[p] = (uint8_t)b;
+    }
+    __syncthreads();
+    const uint32_t total = s_off[kTabBins - 1] + s_cnt[kTabBins - 1];
+    for (uint32_t p = tid; p < total; p += kBuildThreads) {
+        const uint32_t b = s_bin[p], g = s_gbase[b];
+        if (g == 0xFFFFFFFFu) continue;
+        tables[((uint64_t)j << log2_slots) + ((uint64_t)b << kTabBinLog) + g + (p - s_off[b])] = s_ent[p];
+    }
+}
+
+// A bin from its list.  blockIdx.x: the bin, over all tables.
+__global__ __launch_bounds__(kBuildThreads) void table_bin_kernel(uint64_t* __restrict__ tables, int32_t log2_slots,
+                                                                  TableSide* __restrict__ side)
+{
+    extern __shared__ __align__(16) uint64_t s_key[];        // [kTabBin]
+    __shared__ int32_t s_over;
+    const int tid = threadIdx.x;
+    if (tid == 0) s_over = side->overrun;
+    __syncthreads();
+    if (s_over) return;
+    const uint32_t n = side->cursor[blockIdx.x];
+    uint64_t* bin = tables + ((uint64_t)blockIdx.x << kTabBinLog);
+    for (int i = tid; i < kTabBin; i += kBuildThreads) s_key[i] = kEmpty;
+    __syncthreads();
+    for (uint32_t i = tid; i < n; i += kBuildThreads) {
+        const uint64_t key = bin[i];
+        uint32_t s = (uint32_t)key & (kTabBin - 1);
+        for (; s < (uint32_t)kTabBin; ++s) {
+            const unsigned long long prev = atomicCAS((unsigned long long*)&s_key[s], (unsigned long long)kEmpty,
+                                                      (unsigned long long)key);
+            if (prev == kEmpty || prev == key) break;
+        }
+        if (s == (uint32_t)kTabBin) {
+            const int32_t x = atomicAdd(&side->n_spill, 1);
+            if (x < kTabSpills) {
+                // the next bin's first slot, within the table
+                const uint64_t mask = (1ull << log2_slots) - 1, at = (uint64_t)(blockIdx.x + 1) << kTabBinLog;
+                side->spill_key[x] = key;
+                side->spill_at[x] = (((uint64_t)blockIdx.x << kTabBinLog) & ~mask) | (at & mask);
+            } else {
+                atomicOr(&side->overrun, 1);
+            }
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < kTabBin; i += kBuildThreads) bin[i] = s_key[i];
+}
+
+__global__ __launch_bounds__(256) void table_spill_kernel(uint64_t* __restrict__ tables, int32_t log2_slots,
+                                                          TableSide* __restrict__ side, int32_t* status)
+{
+    if (side->overrun) return;
+    const uint64_t mask = (1ull << log2_slots) - 1;
+    for (int32_t x = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x); x < side->n_spill; x += gridDim.x * blockDim.x) {
+        const uint64_t at = side->spill_at[x];
+        if (!table_insert(tables + (at & ~mask), mask, at & mask, side->spill_key[x])) atomicOr(status, RK_DEV_TABLE_FULL);
     }
 }
 
 }  // namespace rk
 
 using namespace rk;
+
+// The partitioned build of tables with `total` slots in all (scatter and insert launch the keys' kernels);
+// RK_OK with *done = false when it is not for this call.
+template <class Scatter, class Insert>
+static int table_build_parts(uint64_t total, int32_t log2_slots, uint64_t* tables, hipStream_t s, const Scatter& scatter,
+                             const Insert& insert, int32_t* st, bool* done)
+{
+    *done = false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return RK_OK;
+    }
+    if (cap != hipStreamCaptureStatusNone) return RK_OK;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return RK_OK;
+    std::lock_guard<std::mutex> lk(g_table_mu);
+    TableSides& b = g_table_sides[dev];
+    if (!b.addr) {
+        void* p = nullptr;
+        int rc = hip_check(hipGetSymbolAddress(&p, HIP_SYMBOL(g_table_side)), "rk_table_build side buffers");
+        for (int k = 0; k < kBuildSides && !rc; ++k)
+            if (!b.used[k])
+                rc = hip_check(hipEventCreateWithFlags(&b.used[k], hipEventDisableTiming), "rk_table_build event");
+        if (rc) return rc;
+        b.addr = (TableSide*)p;
+    }
+    const uint32_t k = b.next++ % kBuildSides;
+    TableSide* side = b.addr + k;
+    int rc = hip_check(hipStreamWaitEvent(s, b.used[k], 0), "rk_table_build wait");
+    if (rc) return rc;
+    *done = true;
+    const unsigned bins = (unsigned)(total >> kTabBinLog);
+    hipLaunchKernelGGL(table_side_kernel, dim3((bins + 255) / 256), dim3(256), 0, s, side, (int32_t)bins);
+    scatter(side);
+    hipLaunchKernelGGL(table_bin_kernel, dim3(bins), dim3(kBuildThreads), 8 * kTabBin, s, tables, log2_slots, side);
+    hipLaunchKernelGGL(table_spill_kernel, dim3(16), dim3(256), 0, s, tables, log2_slots, side, st);
+    hipLaunchKernelGGL(table_clear_kernel, dim3(1024), dim3(256), 0, s, tables, total, &side->overrun);
+    insert(side);
+    rc = hip_check(hipGetLastError(), "rk_table_build launch");
+    const int re = hip_check(hipEventRecord(b.used[k], s), "rk_table_build record");
+    return rc ? rc : re;
+}
 
 extern "C" {
 
@@ -431,22 +637,48 @@ int rk_table_build(int32_t W, const uint64_t* keys, const int64_t* key_off, uint
     if (!st) return fail(RK_EHIP, "rk_table_build: no status word");
     hipStream_t s = (hipStream_t)stream;
     const uint64_t total = slots * (uint64_t)W;
+    // the workers' keys, 64 at a time
+    auto chunk = [&](int32_t j0, KeyRanges& r, int64_t& longest) {
+        const int32_t m = W - j0 < 64 ? W - j0 : 64;
+        longest = 0;
+        for (int32_t k = 0; k <= m; ++k) r.off[k] = key_off[j0 + k];
+        for (int32_t k = 0; k < m; ++k) longest = r.off[k + 1] - r.off[k] > longest ? r.off[k + 1] - r.off[k] : longest;
+        return m;
+    };
+    auto insert_all = [&](int64_t most_blocks, const int32_t* run) {
+        for (int32_t j0 = 0; j0 < W; j0 += 64) {
+            KeyRanges r;
+            int64_t longest;
+            const int32_t m = chunk(j0, r, longest);
+            if (longest == 0) continue;
+            int64_t b = (longest + 255) / 256;
+            if (b > most_blocks) b = most_blocks;
+            hipLaunchKernelGGL(table_insert_kernel, dim3((unsigned)b, (unsigned)m), dim3(256), 0, s, keys, r, j0, tables,
+                               log2_slots, st, run);
+        }
+    };
+    bool done = false;
+    if (log2_slots >= kTabLogMin && log2_slots <= kTabLogMax && total >= (uint64_t)kTabSlotsMin &&
+        total >> kTabBinLog <= (uint64_t)kTabAllBins) {
+        const int rc = table_build_parts(total, log2_slots, tables, s, [&](TableSide* side) {
+            for (int32_t j0 = 0; j0 < W; j0 += 64) {
+                KeyRanges r;
+                int64_t longest;
+                const int32_t m = chunk(j0, r, longest);
+                if (longest == 0) continue;
+                hipLaunchKernelGGL(table_scatter_kernel, dim3((unsigned)((longest + kTile - 1) / kTile), (unsigned)m),
+                                   dim3(kBuildThreads), 0, s, keys, r, j0, tables, log2_slots, side, st);
+            }
+        }, [&](TableSide* side) { insert_all(16, &side->overrun); }, st, &done);
+        if (rc || done) return rc;
+    }
     uint64_t blocks = (total + 255) / 256;
     if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(table_clear_kernel, dim3((unsigned)blocks), dim3(256), 0, s, tables, total);
+    hipLaunchKernelGGL(table_clear_kernel, dim3((unsigned)blocks), dim3(256), 0, s, tables, total, (const int32_t*)nullptr);
     int rc = hip_check(hipGetLastError(), "rk_table_build clear launch");
     if (rc) return rc;
-    for (int32_t j = 0; j < W; ++j) {
-        const int64_t n = key_off[j + 1] - key_off[j];
-        if (n == 0) continue;
-        int64_t b = (n + 255) / 256;
-        if (b > 65536) b = 65536;
-        hipLaunchKernelGGL(table_insert_kernel, dim3((unsigned)b), dim3(256), 0, s, keys + key_off[j], n,
-                           tables + ((uint64_t)j << log2_slots), slots - 1, st);
-        rc = hip_check(hipGetLastError(), "rk_table_build insert launch");
-        if (rc) return rc;
-    }
-    return RK_OK;
+    insert_all(65536, nullptr);
+    return hip_check(hipGetLastError(), "rk_table_build insert launch");
 }
 
 }  // extern "C"

@@ -23,6 +23,8 @@
 // overlap and cost.
 #include <hip/hip_runtime.h>
 
+#include <mutex>
+
 #include "rk_internal.h"
 
 namespace rk {
@@ -365,41 +367,383 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void sc
     }
 }
 
-__global__ __launch_bounds__(256) void index_clear_kernel(IndexSlot* __restrict__ t, uint64_t n)
+// ---------------------------------------------------------------- building the index
+//
+// Inserting every key where it belongs costs two atomics and a line of memory
+// read and written back per key, at random.  From 2^kPartLog slots on the keys
+// are partitioned first and each part of the index is built in LDS and written
+// once, in order:
+//   1. index_scatter_kernel: the index is cut into kBins bins of consecutive
+//      slots; a workgroup sorts a tile of kTile keys by bin in LDS and appends
+//      each bin's run to the bin's list.  The lists lie in the index itself, a
+//      bin's in the upper half of its slots.  An entry is the key with the bin's
+//      bits of its home slot (known from the list) replaced by the worker.
+//   2. index_bin_kernel, a workgroup per bin: the list is sorted by sub-bin of
+//      kSub slots into the bin's lower half, then each sub-bin, from the last to
+//      the first, is built in LDS (linear probing with LDS atomics, as in the
+//      index) and written out over lists that are done with.  Keys that probe
+//      past a sub-bin's end go on by global atomics in the next ones, which are
+//      final by then, and those that leave the bin wait in a side buffer.
+//   3. index_spill_kernel inserts the waiting ones.
+// Whatever does not fit this (a list or a side buffer that runs over, from keys
+// whose low bits are far from uniform) sets a flag that makes the last two
+// launches, otherwise empty, clear the index and insert every key by atomics.
+// The side buffers belong to the library (kBuildSides per device, taken in turn;
+// a call waits on its stream for the buffer's last user).  While a stream is
+// captured there is no such order between calls, and the keys are inserted by
+// atomics, all workers in one launch.
+//
+// 33.6 M keys of 64 workers into 2^27 slots (2 GiB): 4.22 -> 0.91 ms (the keys read twice and written twice, the
+// index written once: 3.5 GB, 3.8 TB/s; a large copy moves 4.8).
+constexpr int kPartLog = 20;              // smallest index that is partitioned (below: 20-40 us by atomics)
+constexpr int kBinLog = 8, kBins = 1 << kBinLog;
+constexpr int kSubLog = 13, kSub = 1 << kSubLog;
+constexpr int kSpills = 64;               // entries a bin may leave to the next one
+constexpr int kMaxSubs = 1 << (31 - kBinLog - kSubLog);
+
+struct BuildSide {
+    int32_t overrun;                      // the partition does not fit: insert by atomics
+    int32_t n_spill[kBins];
+    uint32_t cursor[kBins * 32];          // one per 128-byte line
+    uint64_t spill_key[kBins * kSpills];
+    uint64_t spill_mask[kBins * kSpills];
+};
+static __device__ BuildSide g_build_side[kBuildSides];
+
+__global__ __launch_bounds__(256) void index_clear_kernel(IndexSlot* __restrict__ t, uint64_t n, const int32_t* run)
 {
+    if (run && *run == 0) return;
     const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
         *reinterpret_cast<uint4*>(t + i) = zero;
 }
 
-__global__ __launch_bounds__(256) void index_insert_kernel(const uint64_t* __restrict__ keys, int64_t n, int32_t j,
-                                                           IndexSlot* __restrict__ t, uint64_t smask, int32_t* status)
+// Key into the index from slot s on (bits of the mask added), by atomics; false when there is no slot.
+__device__ __forceinline__ bool index_insert(IndexSlot* t, uint64_t smask, uint64_t s, uint64_t key, uint64_t mask)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    for (uint64_t probe = 0; probe <= smask; ++probe) {
+        const unsigned long long prev = atomicCAS((unsigned long long*)&t[s].key, (unsigned long long)kEmpty,
+                                                  (unsigned long long)key);
+        if (prev == kEmpty || prev == key) {
+            atomicOr((unsigned long long*)&t[s].mask, (unsigned long long)mask);
+            return true;
+        }
+        s = (s + 1) & smask;
+    }
+    return false;
+}
+
+// blockIdx.y: the worker
+__global__ __launch_bounds__(256) void index_insert_kernel(const uint64_t* __restrict__ keys, KeyRanges r,
+                                                           IndexSlot* __restrict__ t, uint64_t smask, int32_t* status,
+                                                           const int32_t* run)
+{
+    if (run && *run == 0) return;
+    const int32_t j = (int32_t)blockIdx.y;
+    const int64_t n = r.off[j + 1];
+    for (int64_t i = r.off[j] + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
         const uint64_t key = keys[i];
         if (key == kEmpty) {
             atomicOr(status, RK_DEV_ZERO_KEY);
             continue;
         }
-        uint64_t s = key & smask;
-        bool done = false;
-        for (uint64_t probe = 0; probe <= smask; ++probe) {
-            const unsigned long long prev = atomicCAS((unsigned long long*)&t[s].key, (unsigned long long)kEmpty,
-                                                      (unsigned long long)key);
-            if (prev == kEmpty || prev == key) {
-                atomicOr((unsigned long long*)&t[s].mask, 1ull << j);
-                done = true;
-                break;
-            }
-            s = (s + 1) & smask;
-        }
-        if (!done) atomicOr(status, RK_DEV_TABLE_FULL);
+        if (!index_insert(t, smask, key & smask, key, 1ull << j)) atomicOr(status, RK_DEV_TABLE_FULL);
     }
 }
+
+__global__ __launch_bounds__(kBins) void index_side_kernel(BuildSide* __restrict__ side)
+{
+    if (threadIdx.x == 0) side->overrun = 0;
+    side->n_spill[threadIdx.x] = 0;
+    side->cursor[threadIdx.x * 32] = 0u;
+}
+
+// Keys to the bins' lists.  blockIdx.y: the worker; blockIdx.x: the tile of its keys.
+__global__ __launch_bounds__(kBuildThreads) void index_scatter_kernel(const uint64_t* __restrict__ keys, KeyRanges r,
+                                                                      IndexSlot* __restrict__ t, int32_t log2_slots,
+                                                                      BuildSide* __restrict__ side, int32_t* status)
+{
+    __shared__ uint64_t s_ent[kTile];
+    __shared__ uint8_t s_bin[kTile];
+    __shared__ uint32_t s_cnt[kBins], s_off[kBins], s_gbase[kBins], s_tmp[16];
+    const int tid = threadIdx.x;
+    const int32_t j = (int32_t)blockIdx.y;
+    const int64_t n0 = r.off[j] + (int64_t)blockIdx.x * kTile, n1 = r.off[j + 1];
+    if (n0 >= n1) return;
+    const int shift = log2_slots - kBinLog;                  // slots of a bin, and the bin's bits of a key
+    const uint64_t cap = 1ull << shift;                      // entries (8 bytes) in the upper half of a bin
+    if (tid < kBins) s_cnt[tid] = 0u;
+    __syncthreads();
+    uint64_t key[kTile / kBuildThreads];
+    uint32_t rank[kTile / kBuildThreads];
+#pragma unroll
+    for (int u = 0; u < kTile / kBuildThreads; ++u) {
+        const int64_t i = n0 + u * kBuildThreads + tid;
+        key[u] = i < n1 ? keys[i] : kEmpty;
+        if (i < n1 && key[u] == kEmpty) atomicOr(status, RK_DEV_ZERO_KEY);
+    }
+#pragma unroll
+    for (int u = 0; u < kTile / kBuildThreads; ++u) {
+        const uint32_t b = (uint32_t)(key[u] >> shift) & (kBins - 1);
+        rank[u] = key[u] != kEmpty ? atomicAdd(&s_cnt[b], 1u) : 0u;
+    }
+    __syncthreads();
+    if (tid < kBins) {
+        const uint32_t c = s_cnt[tid];
+        s_off[tid] = c;
+        uint32_t g = 0;
+        if (c) {
+            g = atomicAdd(&side->cursor[tid * 32], c);
+            if ((uint64_t)g + c > cap) {
+                atomicOr(&side->overrun, 1);
+                g = 0xFFFFFFFFu;                             // no room: not written
+            }
+        }
+        s_gbase[tid] = g;
+    }
+    __syncthreads();
+    build_scan(s_off, kBins, s_tmp);
+    const uint64_t bits = (uint64_t)(kBins - 1) << shift;
+#pragma unroll
+    for (int u = 0; u < kTile / kBuildThreads; ++u) {
+        if (key[u] == kEmpty) continue;
+        const uint32_t b = (uint32_t)(key[u] >> shift) & (kBins - 1);
+        const uint32_t p = s_off[b] + rank[u];
+        s_ent[p] = (key[u] & ~bits) | ((uint64_t)j << shift);
+        s_bin[p] = (uint8_t)b;
+    }
+    __syncthreads();
+    const uint32_t total = s_off[kBins - 1] + s_cnt[kBins - 1];
+    for (uint32_t p = tid; p < total; p += kBuildThreads) {
+        const uint32_t b = s_bin[p], g = s_gbase[b];
+        if (g == 0xFFFFFFFFu) continue;
+        uint64_t* list = reinterpret_cast<uint64_t*>(t + (((uint64_t)b << shift) + (cap >> 1)));
+        list[g + (p - s_off[b])] = s_ent[p];
+    }
+}
+
+// A bin of the index from its list.
+__global__ __launch_bounds__(kBuildThreads) void index_bin_kernel(IndexSlot* __restrict__ t, int32_t log2_slots,
+                                                                  BuildSide* __restrict__ side)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int kStageEnt = 8 * kBuildThreads;             // entries sorted by sub-bin at a time
+    uint64_t* s_key = reinterpret_cast<uint64_t*>(smem);     // [kSub]; the sort's entries
+    uint64_t* s_mask = s_key + kSub;                         // [kSub]; the sort's sub-bins
+    uint16_t* s_sb = reinterpret_cast<uint16_t*>(s_mask);
+    __shared__ uint32_t s_cnt[kMaxSubs], s_off[kMaxSubs], s_cur[kMaxSubs], s_tmp[16];
+    __shared__ uint64_t s_spk[kSpills], s_spm[kSpills];
+    __shared__ int32_t s_nsp, s_over;
+    static_assert(kStageEnt <= kSub && kMaxSubs <= kBuildThreads, "the sort's arrays fit the table's");
+    const int tid = threadIdx.x;
+    const int32_t bin = (int32_t)blockIdx.x;
+    const int shift = log2_slots - kBinLog;
+    const uint64_t slots = 1ull << shift, first = (uint64_t)bin << shift, smask = (1ull << log2_slots) - 1;
+    const uint64_t bits = (uint64_t)(kBins - 1) << shift;
+    const int subs = 1 << (shift > kSubLog ? shift - kSubLog : 0);
+    const int nscan = subs < 64 ? 64 : subs;                 // the scan takes whole wavefronts
+    const int sub_log = shift < kSubLog ? shift : kSubLog;
+    // (other bins may set the flag meanwhile: one read decides for the workgroup)
+    if (tid == 0) s_over = side->overrun;
+    __syncthreads();
+    if (s_over) return;
+    const uint32_t n = side->cursor[bin * 32];
+    const uint64_t* list = reinterpret_cast<const uint64_t*>(t + (first + (slots >> 1)));
+    uint64_t* sorted = reinterpret_cast<uint64_t*>(t + first);
+    if (tid < nscan) s_cnt[tid] = 0u;
+    __syncthreads();
+    // ---- entries per sub-bin, then the list sorted by sub-bin, stage by stage
+    auto sub_of = [&](uint64_t e) { return (uint32_t)(e >> sub_log) & (uint32_t)(subs - 1); };
+    for (uint32_t i = tid; i < n; i += kBuildThreads) atomicAdd(&s_cnt[sub_of(list[i])], 1u);
+    __syncthreads();
+    if (tid < nscan) s_cur[tid] = s_cnt[tid];
+    __syncthreads();
+    build_scan(s_cur, nscan, s_tmp);
+    // the entries before sub-bin k must lie below its slots (16 bytes each): they are still unread when
+    // it is written
+    if (tid < subs && (uint64_t)s_cur[tid] > (uint64_t)tid * 2 * kSub) s_over = 1;
+    __shared__ uint32_t s_beg[kMaxSubs];
+    if (tid < nscan) s_beg[tid] = s_cur[tid];
+    __syncthreads();
+    if (s_over || (uint64_t)n > slots) {
+        if (tid == 0) atomicOr(&side->overrun, 1);
+        return;
+    }
+    if (subs > 1) {
+        for (uint32_t i0 = 0; i0 < n; i0 += kStageEnt) {
+            uint64_t e[kStageEnt / kBuildThreads];
+            uint32_t rank[kStageEnt / kBuildThreads];
+            if (tid < nscan) s_cnt[tid] = 0u;
+#pragma unroll
+            for (int u = 0; u < kStageEnt / kBuildThreads; ++u) {
+                const uint32_t i = i0 + u * kBuildThreads + tid;
+                e[u] = i < n ? list[i] : 0ull;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kStageEnt / kBuildThreads; ++u)
+                if (i0 + u * kBuildThreads + tid < n) rank[u] = atomicAdd(&s_cnt[sub_of(e[u])], 1u);
+            __syncthreads();
+            if (tid < nscan) s_off[tid] = s_cnt[tid];
+            __syncthreads();
+            build_scan(s_off, nscan, s_tmp);
+#pragma unroll
+            for (int u = 0; u < kStageEnt / kBuildThreads; ++u) {
+                if (i0 + u * kBuildThreads + tid >= n) continue;
+                const uint32_t sb = sub_of(e[u]), p = s_off[sb] + rank[u];
+                s_key[p] = e[u];
+                s_sb[p] = (uint16_t)sb;
+            }
+            __syncthreads();
+            const uint32_t m = n - i0 < (uint32_t)kStageEnt ? n - i0 : (uint32_t)kStageEnt;
+            for (uint32_t p = tid; p < m; p += kBuildThreads) {
+                const uint32_t sb = s_sb[p];
+                sorted[s_cur[sb] + (p - s_off[sb])] = s_key[p];
+            }
+            __syncthreads();
+            if (tid < subs) s_cur[tid] += s_cnt[tid];
+            __syncthreads();
+        }
+    }
+    const uint64_t* from = subs > 1 ? sorted : list;
+    // ---- the sub-bins, from the last to the first
+    const uint32_t sub_slots = 1u << sub_log;
+    for (int sb = subs - 1; sb >= 0; --sb) {
+        const uint32_t beg = s_beg[sb], end = sb + 1 < subs ? s_beg[sb + 1] : n;
+        for (uint32_t i = tid; i < sub_slots; i += kBuildThreads) {
+            s_key[i] = kEmpty;
+            s_mask[i] = 0ull;
+        }
+        if (tid == 0) s_nsp = 0;
+        __syncthreads();
+        for (uint32_t i = beg + tid; i < end; i += kBuildThreads) {
+            const uint64_t e = from[i];
+            const uint64_t key = (e & ~bits) | ((uint64_t)bin << shift), mask = 1ull << ((e & bits) >> shift);
+            uint32_t s = (uint32_t)key & (sub_slots - 1);
+            for (; s < sub_slots; ++s) {
+                const unsigned long long prev = atomicCAS((unsigned long long*)&s_key[s], (unsigned long long)kEmpty,
+                                                          (unsigned long long)key);
+                if (prev == kEmpty || prev == key) {
+                    atomicOr((unsigned long long*)&s_mask[s], (unsigned long long)mask);
+                    break;
+                }
+            }
+            if (s == sub_slots) {
+                const int32_t x = atomicAdd(&s_nsp, 1);
+                if (x < kSpills) {
+                    s_spk[x] = key;
+                    s_spm[x] = mask;
+                }
+            }
+        }
+        __syncthreads();
+        const int32_t nsp = s_nsp;
+        if (nsp > kSpills) {
+            if (tid == 0) atomicOr(&side->overrun, 1);
+            return;
+        }
+        uint4* out = reinterpret_cast<uint4*>(t + first + ((uint64_t)sb << sub_log));
+        for (uint32_t i = tid; i < sub_slots; i += kBuildThreads) {
+            const uint64_t k = s_key[i], m = s_mask[i];
+            out[i] = make_uint4((uint32_t)k, (uint32_t)(k >> 32), (uint32_t)m, (uint32_t)(m >> 32));
+        }
+        // keys past the sub-bin's end: on through the sub-bins after it, final by now, or out of the bin
+        if (tid < nsp) {
+            const uint64_t key = s_spk[tid], mask = s_spm[tid];
+            uint64_t s = first + ((uint64_t)(sb + 1) << sub_log);
+            const uint64_t stop = first + slots;
+            for (; s < stop; ++s) {
+                const unsigned long long prev = atomicCAS((unsigned long long*)&t[s].key, (unsigned long long)kEmpty,
+                                                          (unsigned long long)key);
+                if (prev == kEmpty || prev == key) {
+                    atomicOr((unsigned long long*)&t[s].mask, (unsigned long long)mask);
+                    break;
+                }
+            }
+            if (s == stop) {
+                const int32_t x = atomicAdd(&side->n_spill[bin], 1);
+                if (x < kSpills) {
+                    side->spill_key[bin * kSpills + x] = key;
+                    side->spill_mask[bin * kSpills + x] = mask;
+                } else {
+                    atomicOr(&side->overrun, 1);
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// Keys that left their bin, from the next bin's first slot on.
+__global__ __launch_bounds__(kBins) void index_spill_kernel(IndexSlot* __restrict__ t, int32_t log2_slots,
+                                                            BuildSide* __restrict__ side, int32_t* status)
+{
+    const int32_t bin = threadIdx.x;
+    const uint64_t smask = (1ull << log2_slots) - 1;
+    if (side->overrun) return;
+    const int32_t n = side->n_spill[bin];
+    for (int32_t x = 0; x < n; ++x)
+        if (!index_insert(t, smask, ((uint64_t)(bin + 1) << (log2_slots - kBinLog)) & smask,
+                          side->spill_key[bin * kSpills + x], side->spill_mask[bin * kSpills + x]))
+            atomicOr(status, RK_DEV_TABLE_FULL);
+}
+
+// The library's side buffers of a device and the event after each one's last use.
+struct BuildSides {
+    BuildSide* addr = nullptr;
+    hipEvent_t used[kBuildSides] = {};
+    uint32_t next = 0;
+};
+static std::mutex g_sides_mu;
+static BuildSides g_sides[64];
 
 }  // namespace rk
 
 using namespace rk;
+
+// The partitioned build; RK_OK with *done = false when it is not for this call.
+static int index_build_parts(int32_t W, const uint64_t* keys, const KeyRanges& r, int64_t longest, IndexSlot* t,
+                             int32_t log2_slots, int32_t* st, hipStream_t s, bool* done)
+{
+    *done = false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return RK_OK;
+    }
+    if (cap != hipStreamCaptureStatusNone) return RK_OK;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return RK_OK;
+    std::lock_guard<std::mutex> lk(g_sides_mu);
+    BuildSides& b = g_sides[dev];
+    if (!b.addr) {
+        void* p = nullptr;
+        int rc = hip_check(hipGetSymbolAddress(&p, HIP_SYMBOL(g_build_side)), "rk_index_build side buffers");
+        for (int k = 0; k < kBuildSides && !rc; ++k)
+            if (!b.used[k])
+                rc = hip_check(hipEventCreateWithFlags(&b.used[k], hipEventDisableTiming), "rk_index_build event");
+        if (rc) return rc;
+        b.addr = (BuildSide*)p;
+    }
+    const uint32_t k = b.next++ % kBuildSides;
+    BuildSide* side = b.addr + k;
+    // (an event that was never recorded counts as done)
+    int rc = hip_check(hipStreamWaitEvent(s, b.used[k], 0), "rk_index_build wait");
+    if (rc) return rc;
+    *done = true;
+    hipLaunchKernelGGL(index_side_kernel, dim3(1), dim3(kBins), 0, s, side);
+    hipLaunchKernelGGL(index_scatter_kernel, dim3((unsigned)((longest + kTile - 1) / kTile), (unsigned)W),
+                       dim3(kBuildThreads), 0, s, keys, r, t, log2_slots, side, st);
+    hipLaunchKernelGGL(index_bin_kernel, dim3(kBins), dim3(kBuildThreads), 16 * kSub, s, t, log2_slots, side);
+    hipLaunchKernelGGL(index_spill_kernel, dim3(1), dim3(kBins), 0, s, t, log2_slots, side, st);
+    hipLaunchKernelGGL(index_clear_kernel, dim3(1024), dim3(256), 0, s, t, 1ull << log2_slots, &side->overrun);
+    hipLaunchKernelGGL(index_insert_kernel, dim3(16, (unsigned)W), dim3(256), 0, s, keys, r, t,
+                       (1ull << log2_slots) - 1, st, &side->overrun);
+    rc = hip_check(hipGetLastError(), "rk_index_build launch");
+    const int re = hip_check(hipEventRecord(b.used[k], s), "rk_index_build record");
+    return rc ? rc : re;
+}
 
 extern "C" int rk_index_build(int32_t W, const uint64_t* keys, const int64_t* key_off, void* index,
                               int32_t log2_slots, void* stream)
@@ -408,8 +752,14 @@ extern "C" int rk_index_build(int32_t W, const uint64_t* keys, const int64_t* ke
     if (log2_slots < 4 || log2_slots > 31) return fail(RK_EINVAL, "rk_index_build: log2_slots outside 4..31");
     if (!key_off || !index) return fail(RK_EINVAL, "rk_index_build: NULL array");
     const uint64_t slots = 1ull << log2_slots;
-    for (int32_t j = 0; j < W; ++j)
+    KeyRanges r;
+    int64_t longest = 0;
+    for (int32_t j = 0; j < W; ++j) {
         if (key_off[j + 1] < key_off[j]) return fail(RK_EINVAL, "rk_index_build: key_off not monotone at %d", j);
+        r.off[j] = key_off[j];
+        r.off[j + 1] = key_off[j + 1];
+        longest = key_off[j + 1] - key_off[j] > longest ? key_off[j + 1] - key_off[j] : longest;
+    }
     const int64_t total = key_off[W] - key_off[0];
     if ((uint64_t)total > slots / 2)
         return fail(RK_ETABLEFULL, "rk_index_build: %lld keys for %llu slots (load above 0.5)", (long long)total,
@@ -419,22 +769,21 @@ extern "C" int rk_index_build(int32_t W, const uint64_t* keys, const int64_t* ke
     if (!st) return fail(RK_EHIP, "rk_index_build: no status word");
     hipStream_t s = (hipStream_t)stream;
     IndexSlot* t = (IndexSlot*)index;
+    if (log2_slots >= kPartLog && total > 0) {
+        bool done = false;
+        const int rc = index_build_parts(W, keys, r, longest, t, log2_slots, st, s, &done);
+        if (rc || done) return rc;
+    }
     uint64_t blocks = (slots + 255) / 256;
     if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(index_clear_kernel, dim3((unsigned)blocks), dim3(256), 0, s, t, slots);
+    hipLaunchKernelGGL(index_clear_kernel, dim3((unsigned)blocks), dim3(256), 0, s, t, slots, (const int32_t*)nullptr);
     int rc = hip_check(hipGetLastError(), "rk_index_build clear launch");
-    if (rc) return rc;
-    for (int32_t j = 0; j < W; ++j) {
-        const int64_t n = key_off[j + 1] - key_off[j];
-        if (n == 0) continue;
-        int64_t b = (n + 255) / 256;
-        if (b > 65536) b = 65536;
-        hipLaunchKernelGGL(index_insert_kernel, dim3((unsigned)b), dim3(256), 0, s, keys + key_off[j], n, j, t,
-                           slots - 1, st);
-        rc = hip_check(hipGetLastError(), "rk_index_build insert launch");
-        if (rc) return rc;
-    }
-    return RK_OK;
+    if (rc || longest == 0) return rc;
+    int64_t b = (longest + 255) / 256;
+    if (b > 65536) b = 65536;
+    hipLaunchKernelGGL(index_insert_kernel, dim3((unsigned)b, (unsigned)W), dim3(256), 0, s, keys, r, t, slots - 1, st,
+                       (const int32_t*)nullptr);
+    return hip_check(hipGetLastError(), "rk_index_build insert launch");
 }
 
 extern "C" int rk_route_score_index(int32_t B, int32_t W, const uint64_t* chains, const int64_t* chain_off,

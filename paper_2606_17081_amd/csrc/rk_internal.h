@@ -245,6 +245,37 @@ __device__ __forceinline__ bool table_has(const uint64_t* __restrict__ t, uint64
     return false;
 }
 
+// ------------------------------------------------- building tables and indexes
+constexpr int kBuildThreads = 1024;
+constexpr int kTile = 8 * kBuildThreads;  // keys a workgroup partitions at a time
+constexpr int kBuildSides = 4;            // side buffers per device, taken in turn
+
+// Where the keys of up to 64 workers lie.
+struct KeyRanges {
+    int64_t off[65];
+};
+
+// Exclusive prefix sum of v[0..n) in place (n a multiple of 64, at most kBuildThreads), by the
+// whole workgroup; tmp: 16 words.
+__device__ __forceinline__ void build_scan(uint32_t* v, int n, uint32_t* tmp)
+{
+    const int tid = threadIdx.x;
+    uint32_t x = 0;
+    int32_t total = 0, mine = 0;
+    if (tid < n) {
+        x = v[tid];
+        mine = wave_excl_sum_dpp((int32_t)x, total);
+        if ((tid & 63) == 0) tmp[tid >> 6] = (uint32_t)total;
+    }
+    __syncthreads();
+    if (tid < n) {
+        uint32_t base = 0;
+        for (int w = 0; w < (tid >> 6); ++w) base += tmp[w];
+        v[tid] = base + (uint32_t)mine;
+    }
+    __syncthreads();
+}
+
 // ------------------------------------------------------------ host plumbing
 int fail(int status, const char* fmt, ...);                  // records rk_last_error
 int hip_check(hipError_t e, const char* what);

@@ -110,3 +110,141 @@ def test_hash_few_and_many_sequences(gpu, orc, n_seq):
         assert not row[n:].any()
         ref = orc.hash_chains(tokens[tok_off[s]: tok_off[s] + 16 * n], [0, 16 * n], [n])
         assert np.array_equal(row[:n], np.asarray(ref, np.uint64)[:n]), s
+
+
+def _index_slots(rk, idx):
+    """The occupied slots of an index: {key: mask}, and the slot of each key."""
+    a = idx.cpu().numpy().view(np.uint64).reshape(-1, 2)
+    s = np.nonzero(a[:, 0])[0]
+    assert not a[a[:, 0] == 0, 1].any()
+    return {int(k): int(m) for k, m in a[s]}, dict(zip(a[s, 0].tolist(), s.tolist())), a[:, 0] != 0
+
+
+@pytest.mark.parametrize("log2,W,kind", [(19, 5, "uniform"), (20, 64, "uniform"), (20, 3, "dense"), (21, 64, "shared"),
+                                         (22, 7, "uniform"), (22, 2, "ends"), (20, 2, "skewed"), (21, 1, "zeros"),
+                                         (23, 40, "uniform")])
+def test_index_build_partitioned(gpu, log2, W, kind):
+    """From 2^20 slots on the index is partitioned and built in LDS: every key in its probe order from
+    its home slot with the workers that hold it, at load 0.5, for uniform keys, keys shared by all
+    workers, keys whose home slots run on over the ends of sub-bins, bins and the table, keys that
+    crowd into a few bins (built by atomics instead) and zero keys."""
+    torch, rk = gpu
+    rng = np.random.default_rng([log2, W])
+    slots = 1 << log2
+    n = slots // 2 // W
+    hi = rng.permutation(np.arange(1, W * n + 1, dtype=np.uint64)) << np.uint64(32)
+    if kind == "shared":
+        keys = np.tile(hi[:n] | rng.integers(0, 2 ** 32, n, dtype=np.uint64), W)
+    elif kind == "dense":
+        keys = hi | np.arange(W * n, dtype=np.uint64)
+    elif kind == "ends":
+        # 40 keys at the last slots of every 8,192, among them the table's last
+        m = min(W * n, 40 * (slots >> 13))
+        low = (np.arange(m, dtype=np.uint64) // np.uint64(40) << np.uint64(13)) + np.uint64(8185) + rng.integers(
+            0, 7, m, dtype=np.uint64)
+        n = m // W
+        keys = (hi[:m] | low)[: W * n]
+    elif kind == "skewed":
+        keys = hi | rng.integers(0, slots >> 6, W * n, dtype=np.uint64)
+    else:
+        keys = hi | rng.integers(0, 2 ** 32, W * n, dtype=np.uint64)
+    keys = np.where(rng.random(keys.size) < 0.001, 0, keys) if kind == "zeros" else keys
+    off = np.arange(W + 1, dtype=np.int64) * n
+    want = {}
+    for j in range(W):
+        for k in keys[off[j]: off[j + 1]].tolist():
+            want[k] = want.get(k, 0) | 1 << j
+    zeros = want.pop(0, None)
+    up = rk.to_device(np.ascontiguousarray(keys))
+    for turn in range(2):                           # over whatever the buffer held
+        idx = torch.full((2 * slots,), -1 if turn else 5, dtype=torch.int64, device="cuda")
+        rk.index_build(up, off, log2, idx)
+        torch.cuda.synchronize()
+        assert rk.device_status(reset=True) == (4 if zeros else 0)
+        got, where, full = _index_slots(rk, idx)
+        assert got == want
+        # no empty slot between a key's home and its slot
+        holes = np.concatenate([[0], np.cumsum(~np.concatenate([full, full]))])
+        at = np.array([where[k] for k in want])
+        home = (np.array(list(want), np.uint64) & np.uint64(slots - 1)).astype(np.int64)
+        at = np.where(at < home, at + slots, at)
+        assert (holes[at] == holes[home]).all()
+
+
+def test_index_build_streams_and_capture(gpu):
+    """Builds on several streams at once, and one captured into a graph, give the same index."""
+    torch, rk = gpu
+    rng = np.random.default_rng(9)
+    log2, W, n = 20, 16, 20000
+    sets = [(np.arange(1, W * n + 1, dtype=np.uint64) << np.uint64(32)) | rng.integers(0, 2 ** 32, W * n, dtype=np.uint64)
+            for _ in range(6)]
+    off = np.arange(W + 1, dtype=np.int64) * n
+    ups = [rk.to_device(k) for k in sets]
+    idx = [torch.empty(2 << log2, dtype=torch.int64, device="cuda") for _ in sets]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in sets]
+    for _ in range(3):
+        for k, s in enumerate(streams):
+            rk.index_build(ups[k], off, log2, idx[k], stream=s)
+    torch.cuda.synchronize()
+    ref = [_index_slots(rk, i)[0] for i in idx]
+    for k, keys in enumerate(sets):
+        assert ref[k] == {int(x): 1 << (i // n) for i, x in enumerate(keys)}
+    g = torch.cuda.CUDAGraph()
+    cap = torch.empty(2 << log2, dtype=torch.int64, device="cuda")
+    with torch.cuda.graph(g):
+        rk.index_build(ups[0], off, log2, cap)
+    for _ in range(3):
+        cap.fill_(3)
+        g.replay()
+        torch.cuda.synchronize()
+        assert _index_slots(rk, cap)[0] == ref[0]
+    assert rk.device_status(reset=True) == 0
+
+
+@pytest.mark.parametrize("log2,W,kind", [(14, 70, "uniform"), (15, 70, "uniform"), (15, 32, "ends"), (16, 16, "dense"),
+                                         (18, 4, "skewed"), (20, 3, "uniform"), (22, 1, "zeros"), (23, 1, "uniform"),
+                                         (17, 66, "few")])
+def test_table_build_partitioned(gpu, log2, W, kind):
+    """Tables of 2^15 to 2^22 slots, a million in all, are partitioned and built in LDS: every key of a
+    worker in its probe order from its home slot, at load 0.5 or below."""
+    torch, rk = gpu
+    rng = np.random.default_rng([log2, W, 3])
+    slots = 1 << log2
+    n = np.full(W, slots // 2)
+    if kind == "few":
+        n = rng.integers(0, 5, W)
+    if kind == "ends":
+        n = np.full(W, 20 * (slots >> 13))
+    off = np.concatenate([[0], np.cumsum(n)]).astype(np.int64)
+    hi = rng.permutation(np.arange(1, off[-1] + 1, dtype=np.uint64)) << np.uint64(32)
+    if kind == "dense":
+        low = np.arange(off[-1], dtype=np.uint64)
+    elif kind == "ends":
+        low = (rng.integers(0, slots >> 13, off[-1], dtype=np.uint64) << np.uint64(13)) + np.uint64(8185)
+    elif kind == "skewed":
+        low = rng.integers(0, slots >> 5, off[-1], dtype=np.uint64)
+    else:
+        low = rng.integers(0, 2 ** 32, off[-1], dtype=np.uint64)
+    keys = hi | low
+    if kind == "zeros":
+        keys[rng.random(keys.size) < 0.001] = 0
+    if off[-1] > 10 and W > 1:
+        keys[off[1] - 1] = keys[off[0]]             # a worker's key twice
+    up = rk.to_device(keys)
+    for fill in (-1, 5):
+        t = torch.full((W * slots,), fill, dtype=torch.int64, device="cuda")
+        rk.table_build(up, off, log2, t)
+        torch.cuda.synchronize()
+        assert rk.device_status(reset=True) == (4 if kind == "zeros" else 0)
+        got = t.cpu().numpy().view(np.uint64).reshape(W, slots)
+        for j in range(W):
+            want = np.unique(keys[off[j]: off[j + 1]])
+            want = want[want != 0]
+            at = np.nonzero(got[j])[0]
+            assert np.array_equal(np.sort(got[j][at]), want), j
+            empty = got[j] == 0
+            holes = np.concatenate([[0], np.cumsum(np.concatenate([empty, empty]))])
+            home = (got[j][at] & np.uint64(slots - 1)).astype(np.int64)
+            at = np.where(at < home, at + slots, at)
+            assert (holes[at] == holes[home]).all(), j
