@@ -44,6 +44,7 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "rk_internal.h"
 
@@ -129,6 +130,23 @@ __device__ __forceinline__ uint32_t wave_min_u32_poa(uint32_t v)
     v = min(v, dpp32<kDppRowMirror>(v, v));
     const auto rl = [&](int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
     return min(min(rl(0), rl(16)), min(rl(32), rl(48)));
+}
+
+// Maximum over the wavefront (a NaN counts as nothing).
+__device__ __forceinline__ float wave_max_f32(float v)
+{
+    const auto mv = [](float x, int c) {
+        const uint32_t u = __float_as_uint(x);
+        const uint32_t r = c == 0 ? dpp32<kDppQuadSwap1>(u, u) : c == 1 ? dpp32<kDppQuadSwap2>(u, u)
+                         : c == 2 ? dpp32<kDppRowHalfMirror>(u, u) : dpp32<kDppRowMirror>(u, u);
+        return __uint_as_float(r);
+    };
+    v = fmaxf(v, mv(v, 0));
+    v = fmaxf(v, mv(v, 1));
+    v = fmaxf(v, mv(v, 2));
+    v = fmaxf(v, mv(v, 3));
+    const auto rl = [&](int l) { return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), l)); };
+    return fmaxf(fmaxf(rl(0), rl(16)), fmaxf(rl(32), rl(48)));
 }
 
 // Least (value, index) pair over the 64 lanes, by value and then by index;
@@ -360,15 +378,13 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         int32_t cnt = 0;   // lane y: rows on worker y in the partial optimum
         bool placed_all = true;
         // The prices: worker y's base cost below the highest one, when nearly all of the K W places
-        // will be taken; else none.
+        // will be taken; else none.  A window too short to gain from prices what the moves after them
+        // cost has them only where no place stays free (8 rows, 10 workers, 2 places free: 28.5 us a
+        // call with prices, 25.7 without).
         const int32_t slack = K * W - m;
-        float bmax = wl ? s_base[lane] : -__builtin_inff(), bmin = wl ? s_base[lane] : __builtin_inff();
-#pragma unroll
-        for (int32_t sft = 1; sft < PT; sft <<= 1) {
-            bmax = fmaxf(bmax, __shfl_xor(bmax, sft));
-            bmin = fminf(bmin, __shfl_xor(bmin, sft));
-        }
-        const bool priced = 4 * (int64_t)slack <= m && bmax - bmin < __builtin_inff();
+        const float bmax = wave_max_f32(wl ? s_base[lane] : -__builtin_inff());
+        const float bmin = -wave_max_f32(wl ? -s_base[lane] : -__builtin_inff());
+        const bool priced = (slack == 0 || (m >= 16 && 4 * (int64_t)slack <= m)) && bmax - bmin < __builtin_inff();
         const double price = wl && priced ? (double)bmax - (double)s_base[lane] : 0.0;
         // ---- rows on workers of least cost + price.  A lane takes a row and finds the workers
         //      that attain its least; rows with fewer of them choose first, those with all of them
@@ -473,7 +489,31 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         };
         const bool balance = priced && slack > 0;
         if (n_pend > 0 || balance) {
-            for (int32_t x = wave; x < W; x += WAVES) edge(x, s_cnt[x], lane / G < W && lane / G != x);
+            if (WMAX > 32 || K >= 16) {
+                for (int32_t x = wave; x < W; x += WAVES) edge(x, s_cnt[x], lane / G < W && lane / G != x);
+            } else {
+                // workers with few rows each, several side by side: lane (x, z) goes over x's rows
+                constexpr int kSide = 64 / WMAX;
+                const int32_t z = lane % WMAX;
+                for (int32_t x0 = wave * kSide; x0 < W; x0 += WAVES * kSide) {
+                    const int32_t x = x0 + lane / WMAX;
+                    const int32_t cx = x < W && z < W && z != x ? s_cnt[x < W ? x : 0] : 0;
+                    double best = dinf();
+                    int32_t brow = -1;
+                    for (int32_t k = 0; k < cx; ++k) {
+                        const int32_t q = s_mem[x * a.kmax + k];
+                        const double v = (double)cm[(int64_t)q * W + z] - (double)cm[(int64_t)q * W + x];
+                        if (v < best || (v == best && q < brow)) {
+                            best = v;
+                            brow = q;
+                        }
+                    }
+                    if (cx > 0) {
+                        s_e[x * W + z] = best;
+                        s_er[x * W + z] = (int16_t)brow;
+                    }
+                }
+            }
             __syncthreads();
         }
         // ---- the waiting rows along shortest paths, then (with prices and free places) units moved
@@ -788,7 +828,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
         }
         if (tid == 0 && a.coord && !placed_all) a.coord[w] = __longlong_as_double(0x7ff8000000000000ll);
         if (a.coord && placed_all && wave == 0) {
-            // lane G y + g adds every G-th row of worker y, then the sums in lane order
+            // lane G y + g adds every G-th row of worker y, then the G sums and the workers' in order
             const int32_t y = lane / G, yc = y < W ? y : 0;
             const int32_t cy = __shfl(cnt, yc);
             double part = 0.0;
@@ -796,7 +836,15 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
 #pragma unroll 4
                 for (int32_t k = lane % G; k < cy; k += G) part += (double)cm[(int64_t)s_mem[y * a.kmax + k] * W + y];
             double sum = 0.0;
-            for (int32_t l = 0; l < G * W; ++l) sum += lane_f64(part, l);
+            const auto fold = [&](auto c) {
+                const long long b = __double_as_longlong(part);
+                part += __longlong_as_double((long long)dpp64<decltype(c)::value>((uint64_t)b, (uint64_t)b));
+            };
+            if (G >= 2) fold(std::integral_constant<int, kDppQuadSwap1>{});
+            if (G >= 4) fold(std::integral_constant<int, kDppQuadSwap2>{});
+            if (G >= 8) fold(std::integral_constant<int, kDppRowHalfMirror>{});
+            if (G >= 16) fold(std::integral_constant<int, kDppRowMirror>{});
+            for (int32_t l = 0; l < G * W; l += G) sum += lane_f64(part, l);
             if (lane == 0) a.coord[w] = sum;
         }
         __syncthreads();
