@@ -140,11 +140,18 @@ def _check(rc: int, what: str):
         raise RkError(f"{what}: {L.rk_status_string(rc).decode()} ({rc}): {L.rk_last_error().decode()}")
 
 
+_found_torch = None
+
+
 def _torch():
-    import torch
-    if not torch.cuda.is_available():
-        raise RkError("no GPU visible: the routing library runs on an MI355X (gfx950) device only")
-    return torch
+    """torch, once it has seen a GPU (asking again costs microseconds, several times a call)."""
+    global _found_torch
+    if _found_torch is None:
+        import torch
+        if not torch.cuda.is_available():
+            raise RkError("no GPU visible: the routing library runs on an MI355X (gfx950) device only")
+        _found_torch = torch
+    return _found_torch
 
 
 def _ptr(t) -> Optional[int]:
@@ -153,8 +160,10 @@ def _ptr(t) -> Optional[int]:
 
 def _stream(stream=None):
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return C.c_void_p(stream.cuda_stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)    # the handle without a Stream object
+    return C.c_void_p(raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream)
 
 
 def _need(t, dtype, name):
