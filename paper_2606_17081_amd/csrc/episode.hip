@@ -213,14 +213,15 @@ __device__ __forceinline__ void load_slot(const Slot* p, uint64_t& key, uint32_t
 // Frequency update of a touched block in decay epoch ep: an insert leaves the
 // frequency at 1 (K at least ep + 1), a hit doubles max(K - ep, 1) up to
 // RK_FREQ_CAP.  Within one epoch these commute, so concurrent touches of a
-// block by several routes give the sequential result in any order.
-__device__ __forceinline__ void freq_touch(uint32_t* fk, bool inserted, uint32_t ep)
+// block by several routes give the sequential result in any order.  seen: the key as last loaded
+// (a guess; the exchange corrects it).
+__device__ __forceinline__ void freq_touch(uint32_t* fk, bool inserted, uint32_t ep, uint32_t seen)
 {
     if (inserted) {
         __hip_atomic_fetch_max(fk, ep + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         return;
     }
-    uint32_t old = __hip_atomic_load(fk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    uint32_t old = seen;
     for (;;) {
         const uint32_t f = old > ep + 1u ? old - ep : 1u;
         const uint32_t nf = f >= (uint32_t)RK_FREQ_CAP / 2u ? (uint32_t)RK_FREQ_CAP : 2u * f;
@@ -266,17 +267,18 @@ __device__ __forceinline__ bool finish_lookup_stamp(const Slot* t, uint64_t smas
             return true;
         }
     }
-    // further groups one slot at a time (rare: a full first group)
+    // further groups, one round trip each (a full first group)
     for (uint64_t n = kWin; n <= smask; n += kWin) {
         s = (s + kWin) & smask;
-#pragma unroll 1
+        uint64_t kk[kWin];
+        uint32_t ss[kWin];
+#pragma unroll
+        for (int r = 0; r < kWin; ++r) load_slot(t + s + group_slot(h, r), kk[r], ss[r]);
+#pragma unroll
         for (int r = 0; r < kWin; ++r) {
-            uint64_t kk;
-            uint32_t ss;
-            load_slot(t + s + group_slot(h, r), kk, ss);
-            if (kk == kEmpty) return false;
-            if (kk == h && ss != kTomb) {
-                stamp = ss;
+            if (kk[r] == kEmpty) return false;
+            if (kk[r] == h && ss[r] != kTomb) {
+                stamp = ss[r];
                 return true;
             }
         }
@@ -405,14 +407,18 @@ __device__ __forceinline__ uint64_t insert_or_touch(Slot* __restrict__ t, uint64
     inserted = 0;
     uint64_t g = home_slot(h, smask);
     for (uint64_t n = 0; n <= smask; n += kWin) {
-#pragma unroll 1
+        // the group's slots as they were when loaded: keys never change or go, so only an empty one
+        // can differ by now, and the claim tells
+        uint64_t k[kWin];
+        uint32_t st[kWin];
+#pragma unroll
+        for (int r = 0; r < kWin; ++r) load_slot(t + g + group_slot(h, r), k[r], st[r]);
+#pragma unroll
         for (int r = 0; r < kWin; ++r) {
             const uint64_t sl = g + group_slot(h, r);
-            const uint64_t k = __hip_atomic_load(&t[sl].key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            const uint32_t st = t[sl].stamp;
-            if (k == h) {
-                if (st != kTomb) return sl;
-            } else if (k == kEmpty) {
+            if (k[r] == h) {
+                if (st[r] != kTomb) return sl;
+            } else if (k[r] == kEmpty) {
                 uint64_t prev = kEmpty;
                 if (__hip_atomic_compare_exchange_strong(&t[sl].key, &prev, h, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                          __HIP_MEMORY_SCOPE_WORKGROUP)) {
@@ -484,13 +490,13 @@ __device__ __forceinline__ uint64_t touch_hinted(Slot* __restrict__ t, uint64_t 
 
 
 // touch_hinted for two keys of a lane at once (act: the key is to be touched;
-// hint as there), the claims (compare-and-swap returning the slot's previous
-// key) and group loads of both issued before either result is used.
+// hint as there; fkey: the frequency key seen at a hit, else 0), the claims
+// (compare-and-swap returning the slot's previous key) and group loads of both issued before either result is used.
 __device__ __forceinline__ void touch_hinted2(Slot* const* t, uint64_t smask, const uint64_t* h, const bool* hint,
-                                              const bool* act, uint64_t* sl, int* ins, int32_t* status)
+                                              const bool* act, uint64_t* sl, int* ins, uint32_t* fkey, int32_t* status)
 {
     uint64_t s[2], prev[2], k[2][kWin];
-    uint32_t st[2][kWin];
+    uint32_t st[2][kWin], fk[2][kWin];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         s[u] = home_slot(h[u], smask);
@@ -503,12 +509,13 @@ __device__ __forceinline__ void touch_hinted2(Slot* const* t, uint64_t smask, co
     for (int u = 0; u < 2; ++u) {
         const Slot* g = t[u] + s[u];
 #pragma unroll
-        for (int r = 0; r < kWin; ++r) load_slot(g + group_slot(h[u], r), k[u][r], st[u][r]);
+        for (int r = 0; r < kWin; ++r) load_slot(g + group_slot(h[u], r), k[u][r], st[u][r], fk[u][r]);
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         sl[u] = ~0ull;
         ins[u] = 0;
+        fkey[u] = 0u;
         if (!act[u]) continue;
         bool done = false;
         if (hint[u]) {
@@ -516,6 +523,7 @@ __device__ __forceinline__ void touch_hinted2(Slot* const* t, uint64_t smask, co
             for (int r = 0; r < kWin; ++r)
                 if (!done && k[u][r] == h[u] && st[u][r] != kTomb) {
                     sl[u] = s[u] + group_slot(h[u], r);
+                    fkey[u] = fk[u][r];
                     done = true;
                 }
         } else if (prev[u] == kEmpty) {
@@ -2120,7 +2128,8 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                 if (__ballot(act[0] || act[1]) == 0ull) continue;
                 uint64_t sl[2];
                 int ins[2];
-                touch_hinted2(tk, smask, h, hint, act, sl, ins, a.status);
+                uint32_t fkey[2];
+                touch_hinted2(tk, smask, h, hint, act, sl, ins, fkey, a.status);
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     if (!act[u]) continue;
@@ -2130,7 +2139,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                     if (sl[u] != ~0ull) {
                         const uint32_t old = __hip_atomic_fetch_max(&tk[u][sl[u]].stamp, stamp, __ATOMIC_RELAXED,
                                                                     __HIP_MEMORY_SCOPE_WORKGROUP);
-                        if (freq) freq_touch(&tk[u][sl[u]].fkey, ins[u] != 0, r_ep[b]);
+                        if (freq) freq_touch(&tk[u][sl[u]].fkey, ins[u] != 0, r_ep[b], fkey[u]);
                         if (tiers && !ins[u]) {       // a hit whose old record lay in a tier's run
                             if (old >= s_b1[sg]) atomicAdd(&s_h1[sg], 1);
                             if (old >= s_b2[sg]) atomicAdd(&s_h2[sg], 1);
@@ -2157,9 +2166,9 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
     };
 
     // ---- memory tiers: move worker j's two boundaries forward until the runs from them hold at most
-    //      K1 and K12 live records (one wavefront; 256 records from each boundary at a time)
+    //      K1 and K12 live records (one wavefront; 1,024 records from each boundary at a time)
     auto advance = [&](int32_t j) {
-        constexpr int U = 4;
+        constexpr int U = 16;
         const Slot* tk = g_slots + (uint64_t)j * S;
         const uint32_t* tl = g_log + (uint64_t)j * R;
         const uint32_t tail = __builtin_amdgcn_readfirstlane(s_tail[j]);
@@ -2502,14 +2511,15 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
         return true;
     };
 
-    // ---- evict blocks of worker sg down to the capacity (one wavefront, 512 records at a time): live
+    // ---- evict blocks of worker sg down to the capacity (one wavefront, 64 U records at a time:
+    //      where two episodes share a compute unit the wider window costs registers for nothing): live
     //      log records in log (recency) order, under frequency eviction only those at frequency 1
     //      in epoch ep; the head moves to the first record left live.  A live record that is too
     //      frequent in an epoch stays so until it is touched (and moves to the tail), so within an
     //      epoch the next eviction starts behind the last one's.  The blocks evicted and the sum
     //      of their digests go to the route at batch index b.
     auto evict = [&](int32_t sg, uint32_t ep, int32_t b) {
-        constexpr int U = 8;
+        constexpr int U = NT == kEpisodeThreadsMax ? 16 : 8;
         Slot* tk = g_slots + (uint64_t)sg * S;
         const uint32_t* tl = g_log + (uint64_t)sg * R;
         const uint32_t tail = __builtin_amdgcn_readfirstlane(s_tail[sg]);
