@@ -3592,8 +3592,17 @@ extern "C" int rk_simulate_episodes(const rk_episode_batch* b, const rk_episode_
     // LRU episodes 35.7 / 31.2 ms, 8 with frequency eviction 75.0 / 56.8 ms, 8 with tiers 168.8 /
     // 155.5 ms.  With more episodes than compute units two workgroups of 256 share one.
     const bool wide = n_slots <= compute_units();
+    const bool tiers = b->tiers != 0;
+    // a shape is supported when a batch of one route fits 76 KiB beside 11 words per worker, the
+    // in-flight routes, the controller window and 256 words of the rebuild
+    const size_t one = align_up(align_up(align_up(align_up((size_t)b->W * 11 * 4, 16) + (size_t)b->max_inflight * 16, 16) +
+                                         (size_t)b->max_ctrl_window * 8, 16) + 256 * 4, 16) +
+                       batch_layout(1, b->W, tiers).bytes;
+    if (one > 76 * 1024)
+        return fail(RK_EUNSUPPORTED, "rk_simulate_episodes: %zu bytes of LDS per episode exceed 76 KiB", one);
     // LDS: worker state, in-flight routes, controller window, then the batch arrays of the largest
-    // batch that fits in 76 KiB (two episodes can then share a CU)
+    // batch that fits, with two episodes on a CU or with one
+    const size_t limit = wide ? 148 * 1024 : 76 * 1024 + (size_t)b->W * 6 * 4 + 16;
     size_t o = 0;
     a.lds_w = 0;
     o = align_up(o + (size_t)b->W * 17 * 4, 16);
@@ -3604,13 +3613,8 @@ extern "C" int rk_simulate_episodes(const rk_episode_batch* b, const rk_episode_
     a.lds_roff = (uint32_t)o;
     o = align_up(o + (size_t)(wide ? kEpisodeThreadsMax : kEpisodeThreads) * 4, 16);
     a.lds_batch = (uint32_t)o;
-    const size_t limit = 76 * 1024;
     int32_t NB = kMaxBatch;
-    const bool tiers = b->tiers != 0;
     while (NB > 1 && o + batch_layout(NB, b->W, tiers).bytes > limit) NB /= 2;
-    if (o + batch_layout(NB, b->W, tiers).bytes > limit)
-        return fail(RK_EUNSUPPORTED, "rk_simulate_episodes: %zu bytes of LDS per episode exceed 76 KiB",
-                    o + (size_t)batch_layout(NB, b->W, tiers).bytes);
     a.NB = NB;
     const size_t lds = o + batch_layout(NB, b->W, tiers).bytes;
     hipStream_t s = (hipStream_t)stream;

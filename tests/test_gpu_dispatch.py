@@ -84,6 +84,27 @@ def test_poa_free_places(gpu, orc, W, m, spare, levels):
         assert float(sel[w]) == pytest.approx(s, rel=1e-13) and float(coo[w]) == pytest.approx(c, rel=1e-13)
 
 
+def test_poa_largest_window(gpu):
+    """4,096 rows on 64 workers, the most LDS a window takes: without overlaps every worker's 64 places
+    are taken at its base cost."""
+    torch, rk = gpu
+    W, m = 64, 4096
+    am = np.random.default_rng(1).integers(0, W, m).astype(np.int32)
+    up, pp = rk.to_device, dict(wl.POA_PARAMS)
+    sel, coo, hat = (torch.zeros(1, dtype=torch.float64, device="cuda") for _ in range(3))
+    ws = torch.empty(rk.poa_workspace_size(m, W), dtype=torch.uint8, device="cuda")
+    rk.poa_estimate(up(np.array([0, m], np.int64)), up(np.array([0, 1], np.int64)), m, m, W, up(am),
+                    up(np.zeros((m, W), np.int32)), up(np.ones(m, np.int32)),
+                    rk.PoaParams(pp["a"], pp["b"], pp["d"], pp["beta"], pp["C_cap"], pp["w_c"], 0), sel, coo, hat, ws)
+    torch.cuda.synchronize()
+    assert rk.device_status(reset=True) == 0
+    n = np.bincount(am, minlength=W).astype(np.float32)
+    gap = np.maximum(np.float32(pp["C_cap"]) - n, 1).astype(np.float32)
+    base = (np.float32(pp["a"]) * n + np.float32(pp["b"])) + np.float32(pp["d"]) / (gap * gap)
+    assert float(sel) == pytest.approx(float(base[am].astype(np.float64).sum()), rel=1e-13)
+    assert float(coo) == pytest.approx(64 * float(base.astype(np.float64).sum()), rel=1e-13)
+
+
 @pytest.mark.parametrize("n_seq", [1, 3, 8192, 8193])
 def test_hash_few_and_many_sequences(gpu, orc, n_seq):
     """Up to 8,192 sequences take a workgroup each, more a lane each: lengths around the spans of
@@ -121,8 +142,8 @@ def _index_slots(rk, idx):
 
 
 @pytest.mark.parametrize("log2,W,kind", [(19, 5, "uniform"), (20, 64, "uniform"), (20, 3, "dense"), (21, 64, "shared"),
-                                         (22, 7, "uniform"), (22, 2, "ends"), (20, 2, "skewed"), (21, 1, "zeros"),
-                                         (23, 40, "uniform")])
+                                         (22, 7, "uniform"), (22, 2, "ends"), (20, 2, "skewed"), (20, 1, "zeros"),
+                                         (22, 40, "uniform")])
 def test_index_build_partitioned(gpu, log2, W, kind):
     """From 2^20 slots on the index is partitioned and built in LDS: every key in its probe order from
     its home slot with the workers that hold it, at load 0.5, for uniform keys, keys shared by all
