@@ -69,6 +69,8 @@
 // searched against the new boundaries.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "rk_internal.h"
 
 namespace rk {
@@ -2519,7 +2521,7 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
     //      epoch the next eviction starts behind the last one's.  The blocks evicted and the sum
     //      of their digests go to the route at batch index b.
     auto evict = [&](int32_t sg, uint32_t ep, int32_t b) {
-        constexpr int U = NT == kEpisodeThreadsMax ? 16 : 8;
+        constexpr int U = NT == kEpisodeThreadsMax ? 16 : 8, kFew = 2;
         Slot* tk = g_slots + (uint64_t)sg * S;
         const uint32_t* tl = g_log + (uint64_t)sg * R;
         const uint32_t tail = __builtin_amdgcn_readfirstlane(s_tail[sg]);
@@ -2531,28 +2533,25 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
             head = max(head0, (uint32_t)__builtin_amdgcn_readfirstlane(s_sp[sg]));
         const bool skipped = head > head0;
         uint64_t dig = 0;
-        while (rem > 0) {
-            if (head >= tail) {
-                if (lane == 0) atomicOr(a.status, RK_DEV_TABLE_FULL);
-                new_head = tail;
-                break;
-            }
-            uint32_t sl[U], st[U], fk[U];
-            uint64_t key[U];
+        // the next 64 N records
+        auto round = [&](auto groups) {
+            constexpr int N = decltype(groups)::value;
+            uint32_t sl[N], st[N], fk[N];
+            uint64_t key[N];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < N; ++u) {
                 const uint32_t pos = head + (uint32_t)(64 * u + lane);
                 sl[u] = pos < tail ? tl[pos & rmask] : 0xFFFFFFFFu;
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < N; ++u) {
                 key[u] = 0ull;
                 st[u] = kTomb;
                 fk[u] = 0u;
                 if (sl[u] < S) load_slot(tk + sl[u], key[u], st[u], fk[u]);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
+            for (int u = 0; u < N; ++u) {
                 const uint32_t pos = head + (uint32_t)(64 * u + lane);
                 const bool live = st[u] == pos;
                 const bool cand = live && (!freq || fk[u] <= ep + 1u);
@@ -2568,7 +2567,22 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                 if (c > 0 && c == rem) new_head = head + (uint32_t)(64 * u + __ffsll(__ballot(gone && rank == rem - 1)));
                 rem -= c;
             }
-            head = min(head + 64u * U, tail);
+            head = min(head + 64u * N, tail);
+        };
+        // few victims, were the live records spread evenly, lie in the first 64 kFew records, and a lone
+        // wavefront is slow at loads that no victim needs (4 episodes of 700 requests on 4 workers of 700
+        // blocks, an eviction on almost every route: U groups always 7.44 ms, kFew first 5.49, or 5.74
+        // were it 4; with frequency eviction 8.10 and 6.12; multi-turn steps, with many victims, unchanged)
+        if (rem > 0 && (float)rem * (float)(tail - head) <=
+                           48.0f * kFew * (float)max(1, __builtin_amdgcn_readfirstlane(s_live[sg])))
+            round(std::integral_constant<int, kFew>{});
+        while (rem > 0) {
+            if (head >= tail) {
+                if (lane == 0) atomicOr(a.status, RK_DEV_TABLE_FULL);
+                new_head = tail;
+                break;
+            }
+            round(std::integral_constant<int, U>{});
         }
         const uint32_t first = freq ? ep_wave_min_u32(kept) : 0xFFFFFFFFu;
         const uint64_t digest = wave_sum_u64(dig);

@@ -52,6 +52,29 @@ def test_workgroup_widths(gpu, orc):
                 assert np.array_equal(got[k][key], v), (label, e, key)
 
 
+@pytest.mark.parametrize("cache,option", [(c, o) for c in (60, 400, 2500)
+                                          for o in (dict(), dict(evict_policy=wl.EVICT_FREQ, decay_steps=3))])
+def test_eviction_rounds(gpu, orc, cache, option):
+    """An eviction reads its log in rounds, a short one first where it looks for few victims: few and many,
+    live records spread evenly, crowded at the tail by conversations read again and again, and kept
+    at the head by their frequency."""
+    torch, rk = gpu
+    from paper_2606_17081_amd.episodes import EpisodeRunner
+    traces = {1: wl.tiny_trace(1, 400), 2: wl.multiturn_trace(2, 30), 3: wl.saturation_trace(3, 150)}
+    eps = [wl.EpisodeSpec(seed=s, concurrency=C, cap=2048, **option) for s in traces for C in (8, 64)]
+    w = wl.Workload("evictions", W=3, cache_blocks=cache, traces=traces, episodes=eps)
+    r = EpisodeRunner(w)
+    r.step()
+    torch.cuda.synchronize()
+    assert rk.device_status(reset=True) == 0
+    oracle, evicted = {}, 0
+    for e, sp in enumerate(eps):
+        o = _oracle_episode(orc, w, sp, oracle)
+        evicted = max(evicted, int(o["evict_count"].max()))
+        _compare_episode(r.episode_results(e), o, w.W, window=sp.concurrency, label=f"{cache} {e}")
+    assert evicted > 64                                # more than one group of records in an eviction
+
+
 @pytest.mark.parametrize("W,m,spare", [(1, 9, 0), (3, 64, 0), (6, 32, 0), (6, 300, 40), (16, 8, 0), (16, 65, 3),
                                        (16, 256, 0), (16, 256, 4), (16, 256, 20), (32, 255, 1), (33, 130, 0),
                                        (64, 64, 0), (64, 200, 1), (64, 512, 0)])
