@@ -332,6 +332,7 @@ constexpr int64_t kTabSlotsMin = 1ll << 21;   // smaller calls: atomics (2^20 sl
 
 struct TableSide {
     int32_t overrun, n_spill, pad[30];
+    uint32_t refilled[kTabAllBins >> (kTabLogMin - kTabBinLog + 6)];    // of every 64 tables: chunks of keys taken
     uint32_t cursor[kTabAllBins];
     uint64_t spill_key[kTabSpills];
     uint64_t spill_at[kTabSpills];                            // first slot to try (over all tables)
@@ -354,36 +355,57 @@ __global__ __launch_bounds__(256) void table_clear_kernel(uint64_t* __restrict__
         t[i] = kEmpty;
 }
 
-// Key into table t from slot s on, by atomics; false when there is no slot.
+// Key into table t from slot s on, by atomics; false when there is no slot.  After kReads slots the walk
+// reads a slot first: a slot read as taken stays so, and one read as empty may be taken by now, as the
+// exchange tells.
+constexpr uint64_t kNoReads = ~0ull;
+template <uint64_t kReads>
 __device__ __forceinline__ bool table_insert(uint64_t* t, uint64_t mask, uint64_t s, uint64_t key)
 {
     for (uint64_t probe = 0; probe <= mask; ++probe) {
-        const unsigned long long prev = atomicCAS((unsigned long long*)&t[s], (unsigned long long)kEmpty,
-                                                  (unsigned long long)key);
-        if (prev == kEmpty || prev == key) return true;
+        uint64_t seen = kEmpty;
+        if (probe >= kReads) seen = __hip_atomic_load(&t[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (seen == key) return true;
+        if (seen == kEmpty) {
+            const unsigned long long prev = atomicCAS((unsigned long long*)&t[s], (unsigned long long)kEmpty,
+                                                      (unsigned long long)key);
+            if (prev == kEmpty || prev == key) return true;
+        }
         s = (s + 1) & mask;
     }
     return false;
 }
 
+template <uint64_t kReads>
+__device__ __forceinline__ void table_insert_key(uint64_t* tables, int32_t log2_slots, int32_t j, uint64_t key,
+                                                 int32_t* status)
+{
+    const uint64_t mask = (1ull << log2_slots) - 1;
+    if (key == kEmpty) atomicOr(status, RK_DEV_ZERO_KEY);
+    else if (!table_insert<kReads>(tables + ((uint64_t)j << log2_slots), mask, key & mask, key))
+        atomicOr(status, RK_DEV_TABLE_FULL);
+}
+
 // blockIdx.y: the table, from j0 on
 __global__ __launch_bounds__(256) void table_insert_kernel(const uint64_t* __restrict__ keys, KeyRanges r, int32_t j0,
                                                            uint64_t* __restrict__ tables, int32_t log2_slots,
-                                                           int32_t* status, const int32_t* run)
+                                                           int32_t* status)
 {
-    if (run && *run == 0) return;
     const int64_t n = r.off[blockIdx.y + 1];
-    const uint64_t mask = (1ull << log2_slots) - 1;
-    uint64_t* t = tables + ((uint64_t)(j0 + (int32_t)blockIdx.y) << log2_slots);
     for (int64_t i = r.off[blockIdx.y] + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const uint64_t key = keys[i];
-        if (key == kEmpty) {
-            atomicOr(status, RK_DEV_ZERO_KEY);
-            continue;
-        }
-        if (!table_insert(t, mask, key & mask, key)) atomicOr(status, RK_DEV_TABLE_FULL);
-    }
+         i += (int64_t)gridDim.x * blockDim.x)
+        table_insert_key<kNoReads>(tables, log2_slots, j0 + (int32_t)blockIdx.y, keys[i], status);
+}
+
+// The keys of m <= 64 tables, from j0 on, if the partition did not fit.
+__global__ __launch_bounds__(kRefillKeys) void table_refill_kernel(const uint64_t* __restrict__ keys, KeyRanges r,
+                                                                   int32_t j0, int32_t m, uint64_t* __restrict__ tables,
+                                                                   int32_t log2_slots, int32_t* status,
+                                                                   TableSide* __restrict__ side)
+{
+    if (side->overrun == 0) return;
+    refill(r, m, &side->refilled[j0 / 64],
+           [&](int64_t i, int32_t j) { table_insert_key<8>(tables, log2_slots, j0 + j, keys[i], status); });
 }
 
 __global__ __launch_bounds__(256) void table_side_kernel(TableSide* __restrict__ side, int32_t bins)
@@ -394,6 +416,7 @@ __global__ __launch_bounds__(256) void table_side_kernel(TableSide* __restrict__
         side->n_spill = 0;
     }
     if (i < bins) side->cursor[i] = 0u;
+    if (i < (int32_t)(sizeof side->refilled / sizeof side->refilled[0])) side->refilled[i] = 0u;
 }
 
 // Keys to the bins' lists.  blockIdx.x: the table, from j0 on, of m, then the tile of its keys: all
@@ -506,7 +529,7 @@ __global__ __launch_bounds__(256) void table_spill_kernel(uint64_t* __restrict__
     const uint64_t mask = (1ull << log2_slots) - 1;
     for (int32_t x = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x); x < side->n_spill; x += gridDim.x * blockDim.x) {
         const uint64_t at = side->spill_at[x];
-        if (!table_insert(tables + (at & ~mask), mask, at & mask, side->spill_key[x])) atomicOr(status, RK_DEV_TABLE_FULL);
+        if (!table_insert<kNoReads>(tables + (at & ~mask), mask, at & mask, side->spill_key[x])) atomicOr(status, RK_DEV_TABLE_FULL);
     }
 }
 
@@ -514,11 +537,11 @@ __global__ __launch_bounds__(256) void table_spill_kernel(uint64_t* __restrict__
 
 using namespace rk;
 
-// The partitioned build of tables with `total` slots in all (scatter and insert launch the keys' kernels);
+// The partitioned build of tables with `total` slots in all (scatter and refill launch the keys' kernels);
 // RK_OK with *done = false when it is not for this call.
-template <class Scatter, class Insert>
+template <class Scatter, class Refill>
 static int table_build_parts(uint64_t total, int32_t log2_slots, uint64_t* tables, hipStream_t s, const Scatter& scatter,
-                             const Insert& insert, int32_t* st, bool* done)
+                             const Refill& refill, int32_t* st, bool* done)
 {
     *done = false;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -551,7 +574,7 @@ static int table_build_parts(uint64_t total, int32_t log2_slots, uint64_t* table
     hipLaunchKernelGGL(table_bin_kernel, dim3(bins), dim3(kBuildThreads), 8 * kTabBin, s, tables, log2_slots, side);
     hipLaunchKernelGGL(table_spill_kernel, dim3(16), dim3(256), 0, s, tables, log2_slots, side, st);
     hipLaunchKernelGGL(table_clear_kernel, dim3(1024), dim3(256), 0, s, tables, total, &side->overrun);
-    insert(side);
+    refill(side);
     rc = hip_check(hipGetLastError(), "rk_table_build launch");
     const int re = hip_check(hipEventRecord(b.used[k], s), "rk_table_build record");
     return rc ? rc : re;
@@ -648,18 +671,6 @@ int rk_table_build(int32_t W, const uint64_t* keys, const int64_t* key_off, uint
         for (int32_t k = 0; k < m; ++k) longest = r.off[k + 1] - r.off[k] > longest ? r.off[k + 1] - r.off[k] : longest;
         return m;
     };
-    auto insert_all = [&](int64_t most_blocks, const int32_t* run) {
-        for (int32_t j0 = 0; j0 < W; j0 += 64) {
-            KeyRanges r;
-            int64_t longest;
-            const int32_t m = chunk(j0, r, longest);
-            if (longest == 0) continue;
-            int64_t b = (longest + 255) / 256;
-            if (b > most_blocks) b = most_blocks;
-            hipLaunchKernelGGL(table_insert_kernel, dim3((unsigned)b, (unsigned)m), dim3(256), 0, s, keys, r, j0, tables,
-                               log2_slots, st, run);
-        }
-    };
     bool done = false;
     if (log2_slots >= kTabLogMin && log2_slots <= kTabLogMax && total >= (uint64_t)kTabSlotsMin &&
         total >> kTabBinLog <= (uint64_t)kTabAllBins) {
@@ -672,7 +683,16 @@ int rk_table_build(int32_t W, const uint64_t* keys, const int64_t* key_off, uint
                 hipLaunchKernelGGL(table_scatter_kernel, dim3((unsigned)((longest + kTile - 1) / kTile * m)),
                                    dim3(kBuildThreads), 0, s, keys, r, j0, m, tables, log2_slots, side, st);
             }
-        }, [&](TableSide* side) { insert_all(16, &side->overrun); }, st, &done);
+        }, [&](TableSide* side) {
+            for (int32_t j0 = 0; j0 < W; j0 += 64) {
+                KeyRanges r;
+                int64_t longest;
+                const int32_t m = chunk(j0, r, longest);
+                if (longest == 0) continue;
+                hipLaunchKernelGGL(table_refill_kernel, dim3(refill_blocks(r.off[m] - r.off[0])), dim3(kRefillKeys), 0, s,
+                                   keys, r, j0, m, tables, log2_slots, st, side);
+            }
+        }, st, &done);
         if (rc || done) return rc;
     }
     uint64_t blocks = (total + 255) / 256;
@@ -680,7 +700,16 @@ int rk_table_build(int32_t W, const uint64_t* keys, const int64_t* key_off, uint
     hipLaunchKernelGGL(table_clear_kernel, dim3((unsigned)blocks), dim3(256), 0, s, tables, total, (const int32_t*)nullptr);
     int rc = hip_check(hipGetLastError(), "rk_table_build clear launch");
     if (rc) return rc;
-    insert_all(65536, nullptr);
+    for (int32_t j0 = 0; j0 < W; j0 += 64) {
+        KeyRanges r;
+        int64_t longest;
+        const int32_t m = chunk(j0, r, longest);
+        if (longest == 0) continue;
+        int64_t b = (longest + 255) / 256;
+        if (b > 65536) b = 65536;
+        hipLaunchKernelGGL(table_insert_kernel, dim3((unsigned)b, (unsigned)m), dim3(256), 0, s, keys, r, j0, tables,
+                           log2_slots, st);
+    }
     return hip_check(hipGetLastError(), "rk_table_build insert launch");
 }
 

@@ -403,6 +403,7 @@ constexpr int kMaxSubs = 1 << (31 - kBinLog - kSubLog);
 
 struct BuildSide {
     int32_t overrun;                      // the partition does not fit: insert by atomics
+    uint32_t refilled;                    // and the chunks of keys taken for that
     int32_t n_spill[kBins];
     uint32_t cursor[kBins * 32];          // one per 128-byte line
     uint64_t spill_key[kBins * kSpills];
@@ -433,28 +434,39 @@ __device__ __forceinline__ bool index_insert(IndexSlot* t, uint64_t smask, uint6
     return false;
 }
 
+__device__ __forceinline__ void index_insert_key(IndexSlot* t, uint64_t smask, uint64_t key, int32_t j, int32_t* status)
+{
+    if (key == kEmpty) atomicOr(status, RK_DEV_ZERO_KEY);
+    else if (!index_insert(t, smask, key & smask, key, 1ull << j)) atomicOr(status, RK_DEV_TABLE_FULL);
+}
+
 // blockIdx.y: the worker
 __global__ __launch_bounds__(256) void index_insert_kernel(const uint64_t* __restrict__ keys, KeyRanges r,
-                                                           IndexSlot* __restrict__ t, uint64_t smask, int32_t* status,
-                                                           const int32_t* run)
+                                                           IndexSlot* __restrict__ t, uint64_t smask, int32_t* status)
 {
-    if (run && *run == 0) return;
     const int32_t j = (int32_t)blockIdx.y;
     const int64_t n = r.off[j + 1];
     for (int64_t i = r.off[j] + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const uint64_t key = keys[i];
-        if (key == kEmpty) {
-            atomicOr(status, RK_DEV_ZERO_KEY);
-            continue;
-        }
-        if (!index_insert(t, smask, key & smask, key, 1ull << j)) atomicOr(status, RK_DEV_TABLE_FULL);
-    }
+         i += (int64_t)gridDim.x * blockDim.x)
+        index_insert_key(t, smask, keys[i], j, status);
+}
+
+// The keys of all W workers, if the partition did not fit.
+__global__ __launch_bounds__(kRefillKeys) void index_refill_kernel(const uint64_t* __restrict__ keys, KeyRanges r,
+                                                                   int32_t W, IndexSlot* __restrict__ t, uint64_t smask,
+                                                                   int32_t* status, BuildSide* __restrict__ side)
+{
+    if (side->overrun == 0) return;
+    refill(r, W, &side->refilled,
+           [&](int64_t i, int32_t j) { index_insert_key(t, smask, keys[i], j, status); });
 }
 
 __global__ __launch_bounds__(kBins) void index_side_kernel(BuildSide* __restrict__ side)
 {
-    if (threadIdx.x == 0) side->overrun = 0;
+    if (threadIdx.x == 0) {
+        side->overrun = 0;
+        side->refilled = 0u;
+    }
     side->n_spill[threadIdx.x] = 0;
     side->cursor[threadIdx.x * 32] = 0u;
 }
@@ -738,8 +750,8 @@ static int index_build_parts(int32_t W, const uint64_t* keys, const KeyRanges& r
     hipLaunchKernelGGL(index_bin_kernel, dim3(kBins), dim3(kBuildThreads), 16 * kSub, s, t, log2_slots, side);
     hipLaunchKernelGGL(index_spill_kernel, dim3(1), dim3(kBins), 0, s, t, log2_slots, side, st);
     hipLaunchKernelGGL(index_clear_kernel, dim3(1024), dim3(256), 0, s, t, 1ull << log2_slots, &side->overrun);
-    hipLaunchKernelGGL(index_insert_kernel, dim3(16, (unsigned)W), dim3(256), 0, s, keys, r, t,
-                       (1ull << log2_slots) - 1, st, &side->overrun);
+    hipLaunchKernelGGL(index_refill_kernel, dim3(refill_blocks(r.off[W] - r.off[0])), dim3(kRefillKeys), 0, s, keys, r, W,
+                       t, (1ull << log2_slots) - 1, st, side);
     rc = hip_check(hipGetLastError(), "rk_index_build launch");
     const int re = hip_check(hipEventRecord(b.used[k], s), "rk_index_build record");
     return rc ? rc : re;
@@ -781,8 +793,7 @@ extern "C" int rk_index_build(int32_t W, const uint64_t* keys, const int64_t* ke
     if (rc || longest == 0) return rc;
     int64_t b = (longest + 255) / 256;
     if (b > 65536) b = 65536;
-    hipLaunchKernelGGL(index_insert_kernel, dim3((unsigned)b, (unsigned)W), dim3(256), 0, s, keys, r, t, slots - 1, st,
-                       (const int32_t*)nullptr);
+    hipLaunchKernelGGL(index_insert_kernel, dim3((unsigned)b, (unsigned)W), dim3(256), 0, s, keys, r, t, slots - 1, st);
     return hip_check(hipGetLastError(), "rk_index_build insert launch");
 }
 

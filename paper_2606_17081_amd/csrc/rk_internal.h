@@ -255,6 +255,50 @@ struct KeyRanges {
     int64_t off[65];
 };
 
+// The launch that inserts every key by atomics when a partition did not fit is empty when it did, so it
+// has the workgroups that fill the chip, whatever the keys.  They take kRefillKeys keys at a time from a
+// counter: crowded keys probe thousands of slots, and a wavefront that finds more of them than others
+// must not hold the rest up.  2^21 keys of one table, 17,000 of them in one bin: 16 workgroups that
+// stride over the keys 967 ms, 2,048 that stride 39.6, this way 23.5, and 14.5 with a walk that reads
+// the slots first; a workgroup for every 256 keys and no partition before it 15.5 (17.3 with reads).  2^23 keys into an index of
+// 2^24 slots, 200 of them at one slot: 8.68 -> 1.68 ms, 1.35-1.54 without the partition that did not fit.
+constexpr int kRefillKeys = 256, kRefillBlocks = 2048;
+inline unsigned refill_blocks(int64_t keys)
+{
+    const int64_t b = (keys + kRefillKeys - 1) / kRefillKeys;
+    return (unsigned)(b < 1 ? 1 : b < kRefillBlocks ? b : kRefillBlocks);
+}
+
+// The range of off[0..n] that holds i.
+__device__ __forceinline__ int32_t range_of(const int64_t* off, int32_t n, int64_t i)
+{
+    int32_t lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int32_t mid = (lo + hi + 1) >> 1;
+        if (off[mid] <= i) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// insert(key index, worker) for the keys of r's n workers, shared out through *next.
+template <class Insert>
+__device__ __forceinline__ void refill(const KeyRanges& r, int32_t n, uint32_t* next, const Insert& insert)
+{
+    __shared__ int64_t s_off[65];
+    __shared__ uint32_t s_next;
+    if ((int32_t)threadIdx.x <= n) s_off[threadIdx.x] = r.off[threadIdx.x];
+    for (;;) {
+        if (threadIdx.x == 0) s_next = atomicAdd(next, 1u);
+        __syncthreads();
+        const int64_t i = s_off[0] + (int64_t)s_next * kRefillKeys + threadIdx.x;
+        const bool more = s_off[0] + (int64_t)s_next * kRefillKeys < s_off[n];
+        if (i < s_off[n]) insert(i, range_of(s_off, n, i));
+        __syncthreads();
+        if (!more) break;
+    }
+}
+
 // Exclusive prefix sum of v[0..n) in place (n a multiple of 64, at most kBuildThreads), by the
 // whole workgroup; tmp: 16 words.
 __device__ __forceinline__ void build_scan(uint32_t* v, int n, uint32_t* tmp)
