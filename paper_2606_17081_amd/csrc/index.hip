@@ -382,8 +382,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void sc
 //      kSub slots into the bin's lower half, then each sub-bin, from the last to
 //      the first, is built in LDS (linear probing with LDS atomics, as in the
 //      index) and written out over lists that are done with.  Keys that probe
-//      past a sub-bin's end go on by global atomics in the next ones, which are
-//      final by then, and those that leave the bin wait in a side buffer.
+//      past a sub-bin's end (each counted once, however many workers hold it: a
+//      prefix cached everywhere comes 64 times) go on by global atomics in the
+//      next ones, which are final by then, and those that leave the bin wait in
+//      a side buffer.
 //   3. index_spill_kernel inserts the waiting ones.
 // Whatever does not fit this (a list or a side buffer that runs over, from keys
 // whose low bits are far from uniform) sets a flag that makes the last two
@@ -398,7 +400,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void sc
 constexpr int kPartLog = 20;              // smallest index that is partitioned (below: 20-40 us by atomics)
 constexpr int kBinLog = 8, kBins = 1 << kBinLog;
 constexpr int kSubLog = 13, kSub = 1 << kSubLog;
-constexpr int kSpills = 64;               // entries a bin may leave to the next one
+constexpr int kSpills = 64;               // keys that may probe past a sub-bin's end, and past a bin's
 constexpr int kMaxSubs = 1 << (31 - kBinLog - kSubLog);
 
 struct BuildSide {
@@ -546,7 +548,7 @@ __global__ __launch_bounds__(kBuildThreads) void index_bin_kernel(IndexSlot* __r
     uint16_t* s_sb = reinterpret_cast<uint16_t*>(s_mask);
     __shared__ uint32_t s_cnt[kMaxSubs], s_off[kMaxSubs], s_cur[kMaxSubs], s_tmp[16];
     __shared__ uint64_t s_spk[kSpills], s_spm[kSpills];
-    __shared__ int32_t s_nsp, s_over;
+    __shared__ int32_t s_full, s_over;
     static_assert(kStageEnt <= kSub && kMaxSubs <= kBuildThreads, "the sort's arrays fit the table's");
     const int tid = threadIdx.x;
     const int32_t bin = (int32_t)blockIdx.x;
@@ -557,7 +559,10 @@ __global__ __launch_bounds__(kBuildThreads) void index_bin_kernel(IndexSlot* __r
     const int nscan = subs < 64 ? 64 : subs;                 // the scan takes whole wavefronts
     const int sub_log = shift < kSubLog ? shift : kSubLog;
     // (other bins may set the flag meanwhile: one read decides for the workgroup)
-    if (tid == 0) s_over = side->overrun;
+    if (tid == 0) {
+        s_over = side->overrun;
+        s_full = 0;
+    }
     __syncthreads();
     if (s_over) return;
     const uint32_t n = side->cursor[bin * 32];
@@ -627,7 +632,10 @@ __global__ __launch_bounds__(kBuildThreads) void index_bin_kernel(IndexSlot* __r
             s_key[i] = kEmpty;
             s_mask[i] = 0ull;
         }
-        if (tid == 0) s_nsp = 0;
+        if (tid < kSpills) {
+            s_spk[tid] = kEmpty;
+            s_spm[tid] = 0ull;
+        }
         __syncthreads();
         for (uint32_t i = beg + tid; i < end; i += kBuildThreads) {
             const uint64_t e = from[i];
@@ -642,16 +650,19 @@ __global__ __launch_bounds__(kBuildThreads) void index_bin_kernel(IndexSlot* __r
                 }
             }
             if (s == sub_slots) {
-                const int32_t x = atomicAdd(&s_nsp, 1);
-                if (x < kSpills) {
-                    s_spk[x] = key;
-                    s_spm[x] = mask;
+                // kept once, whichever workers hold it
+                int32_t x = 0;
+                for (; x < kSpills; ++x) {
+                    const unsigned long long prev = atomicCAS((unsigned long long*)&s_spk[x], (unsigned long long)kEmpty,
+                                                              (unsigned long long)key);
+                    if (prev == kEmpty || prev == key) break;
                 }
+                if (x < kSpills) atomicOr((unsigned long long*)&s_spm[x], (unsigned long long)mask);
+                else s_full = 1;
             }
         }
         __syncthreads();
-        const int32_t nsp = s_nsp;
-        if (nsp > kSpills) {
+        if (s_full) {
             if (tid == 0) atomicOr(&side->overrun, 1);
             return;
         }
@@ -661,7 +672,7 @@ __global__ __launch_bounds__(kBuildThreads) void index_bin_kernel(IndexSlot* __r
             out[i] = make_uint4((uint32_t)k, (uint32_t)(k >> 32), (uint32_t)m, (uint32_t)(m >> 32));
         }
         // keys past the sub-bin's end: on through the sub-bins after it, final by now, or out of the bin
-        if (tid < nsp) {
+        if (tid < kSpills && s_spk[tid] != kEmpty) {
             const uint64_t key = s_spk[tid], mask = s_spm[tid];
             uint64_t s = first + ((uint64_t)(sb + 1) << sub_log);
             const uint64_t stop = first + slots;
