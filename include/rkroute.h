@@ -25,7 +25,8 @@
  * Conventions shared by every entry point:
  *   - Array arguments are DEVICE pointers unless a comment says "host".
  *     The caller owns every buffer; the library keeps no pointer after a call
- *     returns.
+ *     returns.  (rk_table_build, rk_index_build and rk_poa_estimate_noalloc work
+ *     in static device buffers of the library's own beside them.)
  *   - Work is enqueued asynchronously on `stream` (a hipStream_t; NULL is the
  *     default stream).  Argument checks happen before any launch; a failed
  *     check launches nothing.
@@ -105,6 +106,13 @@ int rk_hash_chains(int64_t n_seq, const int32_t* tokens, const int64_t* tok_off,
  * keys[key_off[j] .. key_off[j+1]) are inserted (duplicates once, zero keys
  * skipped with RK_DEV_ZERO_KEY).
  *
+ * The tables are built from keys partitioned by home slot where their sizes make
+ * that faster, in one of a few static device buffers (about 4 MiB per device for
+ * both kinds of build); a call waits for no other stream's work.  While its
+ * stream is captured, and when calls on other streams have every buffer in use,
+ * the keys are inserted by atomics instead: the same sets, at slots that may
+ * differ within the probe order, several times slower for large tables.
+ *
  *   W          number of tables (>= 1)
  *   keys       uint64 [key_off[W]]
  *   key_off    int64 [W+1], HOST pointer
@@ -171,6 +179,7 @@ int rk_route_score_batch(int32_t B, int32_t W, const uint64_t* chains, const int
  * rk_index_build -- clear the index and insert worker j's keys
  * keys[key_off[j] .. key_off[j+1]) for j < W (the same key sets as
  * rk_table_build; duplicates once, zero keys skipped with RK_DEV_ZERO_KEY).
+ * Partitioned or by atomics, on several streams and under capture, as there.
  *   W          1..64 (else RK_EUNSUPPORTED)
  *   keys       uint64 [key_off[W]], device
  *   key_off    int64 [W+1], HOST pointer, non-decreasing

@@ -48,6 +48,17 @@ int32_t* status_word()
     return g_status_addr[dev];
 }
 
+bool event_done(hipEvent_t e)
+{
+    // the query is a call that a capture elsewhere in the process would otherwise be ended by
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool changed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const hipError_t before = hipPeekAtLastError(), q = hipEventQuery(e);
+    if (q != hipSuccess && before == hipSuccess) (void)hipGetLastError();     // "not ready" is no failure
+    if (changed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return q == hipSuccess;
+}
+
 // The current device's compute units, asked for once per device (0 if unknown).
 int32_t compute_units()
 {
@@ -339,13 +350,8 @@ struct TableSide {
 };
 static __device__ TableSide g_table_side[kBuildSides];
 
-struct TableSides {
-    TableSide* addr = nullptr;
-    hipEvent_t used[kBuildSides] = {};
-    uint32_t next = 0;
-};
 static std::mutex g_table_mu;
-static TableSides g_table_sides[64];
+static SidePool<TableSide> g_table_sides[64];
 
 __global__ __launch_bounds__(256) void table_clear_kernel(uint64_t* __restrict__ t, uint64_t n, const int32_t* run)
 {
@@ -553,19 +559,19 @@ static int table_build_parts(uint64_t total, int32_t log2_slots, uint64_t* table
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return RK_OK;
     std::lock_guard<std::mutex> lk(g_table_mu);
-    TableSides& b = g_table_sides[dev];
+    SidePool<TableSide>& b = g_table_sides[dev];
     if (!b.addr) {
         void* p = nullptr;
         int rc = hip_check(hipGetSymbolAddress(&p, HIP_SYMBOL(g_table_side)), "rk_table_build side buffers");
-        for (int k = 0; k < kBuildSides && !rc; ++k)
-            if (!b.used[k])
-                rc = hip_check(hipEventCreateWithFlags(&b.used[k], hipEventDisableTiming), "rk_table_build event");
+        if (!rc) rc = b.make_events("rk_table_build event");
         if (rc) return rc;
         b.addr = (TableSide*)p;
     }
-    const uint32_t k = b.next++ % kBuildSides;
+    const int k = b.take(s);
+    if (k < 0) return RK_OK;
     TableSide* side = b.addr + k;
-    int rc = hip_check(hipStreamWaitEvent(s, b.used[k], 0), "rk_table_build wait");
+    // (a stream's handle may be that of a stream destroyed with its work under way)
+    int rc = b.once[k] ? hip_check(hipStreamWaitEvent(s, b.used[k], 0), "rk_table_build wait") : RK_OK;
     if (rc) return rc;
     *done = true;
     const unsigned bins = (unsigned)(total >> kTabBinLog);
@@ -576,7 +582,7 @@ static int table_build_parts(uint64_t total, int32_t log2_slots, uint64_t* table
     hipLaunchKernelGGL(table_clear_kernel, dim3(1024), dim3(256), 0, s, tables, total, &side->overrun);
     refill(side);
     rc = hip_check(hipGetLastError(), "rk_table_build launch");
-    const int re = hip_check(hipEventRecord(b.used[k], s), "rk_table_build record");
+    const int re = b.record(k, s, "rk_table_build record");
     return rc ? rc : re;
 }
 

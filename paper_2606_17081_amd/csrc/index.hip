@@ -390,10 +390,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void sc
 // Whatever does not fit this (a list or a side buffer that runs over, from keys
 // whose low bits are far from uniform) sets a flag that makes the last two
 // launches, otherwise empty, clear the index and insert every key by atomics.
-// The side buffers belong to the library (kBuildSides per device, taken in turn;
-// a call waits on its stream for the buffer's last user).  While a stream is
-// captured there is no such order between calls, and the keys are inserted by
-// atomics, all workers in one launch.
+// The side buffers belong to the library, kBuildSides per device (SidePool).  When
+// other streams' calls have all of them in use, and while the stream is captured
+// (its graph may run at any time), the keys are inserted by atomics, all workers
+// in one launch.
 //
 // 33.6 M keys of 64 workers into 2^27 slots (2 GiB): 4.22 -> 0.91 ms (the keys read twice and written twice, the
 // index written once: 3.5 GB, 3.8 TB/s; a large copy moves 4.8).
@@ -712,14 +712,8 @@ __global__ __launch_bounds__(kBins) void index_spill_kernel(IndexSlot* __restric
             atomicOr(status, RK_DEV_TABLE_FULL);
 }
 
-// The library's side buffers of a device and the event after each one's last use.
-struct BuildSides {
-    BuildSide* addr = nullptr;
-    hipEvent_t used[kBuildSides] = {};
-    uint32_t next = 0;
-};
 static std::mutex g_sides_mu;
-static BuildSides g_sides[64];
+static SidePool<BuildSide> g_sides[64];
 
 }  // namespace rk
 
@@ -739,20 +733,19 @@ static int index_build_parts(int32_t W, const uint64_t* keys, const KeyRanges& r
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return RK_OK;
     std::lock_guard<std::mutex> lk(g_sides_mu);
-    BuildSides& b = g_sides[dev];
+    SidePool<BuildSide>& b = g_sides[dev];
     if (!b.addr) {
         void* p = nullptr;
         int rc = hip_check(hipGetSymbolAddress(&p, HIP_SYMBOL(g_build_side)), "rk_index_build side buffers");
-        for (int k = 0; k < kBuildSides && !rc; ++k)
-            if (!b.used[k])
-                rc = hip_check(hipEventCreateWithFlags(&b.used[k], hipEventDisableTiming), "rk_index_build event");
+        if (!rc) rc = b.make_events("rk_index_build event");
         if (rc) return rc;
         b.addr = (BuildSide*)p;
     }
-    const uint32_t k = b.next++ % kBuildSides;
+    const int k = b.take(s);
+    if (k < 0) return RK_OK;
     BuildSide* side = b.addr + k;
-    // (an event that was never recorded counts as done)
-    int rc = hip_check(hipStreamWaitEvent(s, b.used[k], 0), "rk_index_build wait");
+    // (a stream's handle may be that of a stream destroyed with its work under way)
+    int rc = b.once[k] ? hip_check(hipStreamWaitEvent(s, b.used[k], 0), "rk_index_build wait") : RK_OK;
     if (rc) return rc;
     *done = true;
     hipLaunchKernelGGL(index_side_kernel, dim3(1), dim3(kBins), 0, s, side);
@@ -764,7 +757,7 @@ static int index_build_parts(int32_t W, const uint64_t* keys, const KeyRanges& r
     hipLaunchKernelGGL(index_refill_kernel, dim3(refill_blocks(r.off[W] - r.off[0])), dim3(kRefillKeys), 0, s, keys, r, W,
                        t, (1ull << log2_slots) - 1, st, side);
     rc = hip_check(hipGetLastError(), "rk_index_build launch");
-    const int re = hip_check(hipEventRecord(b.used[k], s), "rk_index_build record");
+    const int re = b.record(k, s, "rk_index_build record");
     return rc ? rc : re;
 }
 

@@ -248,7 +248,7 @@ __device__ __forceinline__ bool table_has(const uint64_t* __restrict__ t, uint64
 // ------------------------------------------------- building tables and indexes
 constexpr int kBuildThreads = 1024;
 constexpr int kTile = 8 * kBuildThreads;  // keys a workgroup partitions at a time
-constexpr int kBuildSides = 4;            // side buffers per device, taken in turn
+constexpr int kBuildSides = 4;            // side buffers per device
 
 // Where the keys of up to 64 workers lie.
 struct KeyRanges {
@@ -325,6 +325,50 @@ int fail(int status, const char* fmt, ...);                  // records rk_last_
 int hip_check(hipError_t e, const char* what);
 int32_t* status_word();                                      // device address for the current device
 int32_t compute_units();                                     // of the current device
+bool event_done(hipEvent_t e);                               // without a wait, also while some stream is captured
+
+// A device's side buffers of one kind of build (held under the owner's lock from take to record).  A
+// call takes a buffer that was last used on its own stream, or whose last use has ended, and so waits
+// for no other stream's work, whatever that waits for; -1 when there is none.
+template <class T>
+struct SidePool {
+    T* addr = nullptr;
+    hipEvent_t used[kBuildSides] = {};
+    hipStream_t on[kBuildSides] = {};
+    bool once[kBuildSides] = {};
+
+    int take(hipStream_t s) const
+    {
+        // (one handle stands for every thread's own default stream)
+        for (int k = 0; k < kBuildSides; ++k)
+            if (once[k] && on[k] == s && s != hipStreamPerThread) return k;
+        for (int k = 0; k < kBuildSides; ++k)
+            if (!once[k] || (used[k] && event_done(used[k]))) return k;
+        return -1;
+    }
+    int make_events(const char* what)
+    {
+        for (int k = 0; k < kBuildSides; ++k)
+            if (!used[k]) {
+                const int rc = hip_check(hipEventCreateWithFlags(&used[k], hipEventDisableTiming), what);
+                if (rc) return rc;
+            }
+        return RK_OK;
+    }
+    // buffer k's use on s, just launched, is its last
+    int record(int k, hipStream_t s, const char* what)
+    {
+        once[k] = true;
+        on[k] = s;
+        const int rc = hip_check(hipEventRecord(used[k], s), what);
+        if (rc) {                  // nothing tells when this use ends: the buffer is not taken again
+            on[k] = hipStreamPerThread;
+            used[k] = nullptr;
+        }
+        return rc;
+    }
+};
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline uint64_t next_pow2(uint64_t x)
 {

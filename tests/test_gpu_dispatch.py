@@ -364,3 +364,124 @@ def test_shared_keys_past_an_end(gpu, shared, at):
     assert (slots[k, 1] == -1).all()                # every worker's bit
     assert rk.device_status(reset=True) == 0
     assert ms < 3 * plain                           # 1.0 to 1.6 measured, 6.3 to 7.4 before
+
+
+def _sleep_cycles(torch, ms):
+    a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    a.record()
+    torch.cuda._sleep(10_000_000)
+    b.record()
+    torch.cuda.synchronize()
+    return int(ms / a.elapsed_time(b) * 1e7)
+
+
+def _build_inputs(torch, rk, layout, sets, seed):
+    """Key sets on the device, key offsets, log2 slots and the partitioned build of a layout."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    W, log2 = 4, 20
+    n = (1 << log2) // 2 // (W if layout == "index" else 1)
+    keys = [((torch.arange(1, W * n + 1, device="cuda") + k * W * n) << 32)
+            | torch.randint(0, 1 << 32, (W * n,), generator=g, device="cuda") for k in range(sets)]
+    out = [torch.empty((2 if layout == "index" else W) << log2, dtype=torch.int64, device="cuda") for _ in keys]
+    return keys, np.arange(W + 1, dtype=np.int64) * n, log2, out, rk.index_build if layout == "index" else rk.table_build
+
+
+def _assert_built(torch, layout, keys, out):
+    """Every key of the set and no other, in its worker's table or with its worker's bit."""
+    W = 4
+    if layout == "index":
+        slots = out.view(-1, 2)
+        slots = slots[slots[:, 0] != 0]
+        key, k = torch.sort(slots[:, 0])
+        want, worker = torch.sort(keys)
+        assert torch.equal(key, want) and torch.equal(slots[k, 1], 1 << (worker // (keys.numel() // W)))
+    else:
+        got = torch.sort(out.view(W, -1), dim=1)[0]
+        want = torch.sort(keys.view(W, -1), dim=1)[0]
+        assert torch.equal(got[:, -want.shape[1]:], want) and not got[:, : -want.shape[1]].any()
+
+
+def _stream_beside(torch, busy, cycles):
+    """A stream whose work does not share busy's hardware queue."""
+    x = torch.zeros(8, device="cuda")
+    for _ in range(8):
+        s, ended = torch.cuda.Stream(), torch.cuda.Event()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(busy):
+            torch.cuda._sleep(cycles)
+            ended.record()
+        with torch.cuda.stream(s):
+            x.add_(1)
+        s.synchronize()
+        if not ended.query():
+            return s
+    pytest.skip("every stream shares the busy one's hardware queue")
+
+
+@pytest.mark.parametrize("layout", ["index", "tables"])
+def test_builds_wait_for_no_other_stream(gpu, layout):
+    """A build ends while builds of another stream wait behind 200 ms of other work (before, the fifth
+    build waited for the first one's stream)."""
+    import time
+    torch, rk = gpu
+    keys, off, log2, out, build = _build_inputs(torch, rk, layout, 5, 1)
+    busy, cycles = torch.cuda.Stream(), _sleep_cycles(torch, 200)
+    free = _stream_beside(torch, busy, cycles // 4)
+    build(keys[4], off, log2, out[4], stream=free)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(busy):
+        torch.cuda._sleep(cycles)
+        ended = torch.cuda.Event()
+        ended.record()
+    t = time.perf_counter()
+    for k in range(4):
+        build(keys[k], off, log2, out[k], stream=busy)
+    for _ in range(3):
+        build(keys[4], off, log2, out[4], stream=free)
+    free.synchronize()
+    ms = (time.perf_counter() - t) * 1e3
+    early = not ended.query()
+    torch.cuda.synchronize()
+    say(layout, "ended after", ms, "ms, before the other stream's work:", early)
+    for k in range(5):
+        _assert_built(torch, layout, keys[k], out[k])
+    assert rk.device_status(reset=True) == 0
+    assert early
+
+
+@pytest.mark.parametrize("layout", ["index", "tables"])
+def test_builds_on_many_streams_and_captured(gpu, layout):
+    """More streams with builds under way than there are side buffers, builds on one stream while
+    another is captured, and a captured build."""
+    torch, rk = gpu
+    keys, off, log2, out, build = _build_inputs(torch, rk, layout, 7, 2)
+    cycles = _sleep_cycles(torch, 20)
+    streams = [torch.cuda.Stream() for _ in keys]
+    for _ in range(3):
+        for s, k, o in zip(streams, keys, out):
+            with torch.cuda.stream(s):
+                torch.cuda._sleep(cycles // 10)
+            build(k, off, log2, o, stream=s)
+            build(k, off, log2, o, stream=s)
+    torch.cuda.synchronize()
+    for k, o in zip(keys, out):
+        _assert_built(torch, layout, k, o)
+        o.fill_(5)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        build(keys[0], off, log2, out[0])
+        for i in (1, 2, 1, 2, 3, 4, 5, 6):
+            build(keys[i], off, log2, out[i], stream=streams[i])
+    for _ in range(3):
+        torch.cuda.synchronize()
+        for k, o in zip(keys[1:], out[1:]):
+            _assert_built(torch, layout, k, o)
+        out[0].fill_(3)
+        graph.replay()
+        torch.cuda.synchronize()
+        _assert_built(torch, layout, keys[0], out[0])
+        for i in range(1, 7):
+            out[i].fill_(3)
+            build(keys[i], off, log2, out[i])
+    assert rk.device_status(reset=True) == 0
