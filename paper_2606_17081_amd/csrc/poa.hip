@@ -884,7 +884,8 @@ static void launch_windows(int32_t W, unsigned grid, size_t lds, hipStream_t s, 
     if (W <= 8) hipLaunchKernelGGL((poa_window_kernel<LDSMAT, 8, WAVES>), g, b, lds, s, a);
     else if (W <= 16) hipLaunchKernelGGL((poa_window_kernel<LDSMAT, 16, WAVES>), g, b, lds, s, a);
     else if (W <= 32) hipLaunchKernelGGL((poa_window_kernel<LDSMAT, 32, WAVES>), g, b, lds, s, a);
-    else if constexpr (WAVES > 1) hipLaunchKernelGGL((poa_window_kernel<LDSMAT, 64, WAVES>), g, b, lds, s, a);
+    else if (WAVES == 1 && W <= 48) hipLaunchKernelGGL((poa_window_kernel<LDSMAT, WAVES == 1 ? 48 : 64, WAVES>), g, b, lds, s, a);
+    else hipLaunchKernelGGL((poa_window_kernel<LDSMAT, 64, WAVES>), g, b, lds, s, a);
 }
 
 // Argument checks shared by rk_poa_estimate and rk_poa_estimate_noalloc;
@@ -985,8 +986,17 @@ static int poa_launch(int32_t n_windows, const int64_t* win_off, int32_t n_episo
         unsigned grid = (unsigned)(n_windows < 131072 ? n_windows : 131072);
         // four wavefronts per window where the windows leave the chip's SIMDs idle (128 windows of
         // 512 rows x 64 workers: 1.05 ms with one, 0.62 ms with four) and a window has enough entries
-        // to spread, and always for W > 32, where one wavefront's 64 edge weights per lane would leave a SIMD one window
-        const bool four = W > 32 || (n_windows <= 2 * compute_units() && (int64_t)max_window * W >= 2048);
+        // to spread.  Above 32 workers an edge column takes a lane two registers a worker: up to 48 one
+        // wavefront still shares its SIMD, and many windows take it (40 workers, four / one wavefront:
+        // 23,437 windows of 64 rows 20.97 / 9.45 ms, 60,000 of 1 row 6.32 / 5.45, but 40 of 8 rows 41 /
+        // 60 us and 600 of 20 rows 232 / 236 us, of 1 row 86 / 77); above 48 it has the SIMD to itself, and only the
+        // shortest windows gain from fewer wavefronts (60,000 of 3 rows x 56 workers 6.74 / 6.16 ms, of
+        // 20 rows x 64 workers 9.35 / 10.76 ms)
+        const int32_t cus = compute_units();
+        const bool many = n_windows > (max_window <= 2 ? 2 : 4) * cus;
+        const bool four = W > 48   ? !(many && max_window <= 4)
+                          : W > 32 ? !many
+                                   : n_windows <= 2 * cus && (int64_t)max_window * W >= 2048;
         if (lds_mat) {
             if (four) launch_windows<true, 4>(W, grid, o, s, a);
             else launch_windows<true, 1>(W, grid, o, s, a);

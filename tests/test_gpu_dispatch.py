@@ -107,6 +107,44 @@ def test_poa_free_places(gpu, orc, W, m, spare, levels):
         assert float(sel[w]) == pytest.approx(s, rel=1e-13) and float(coo[w]) == pytest.approx(c, rel=1e-13)
 
 
+@pytest.mark.parametrize("W,m,spare", [(8, 20, 1), (16, 256, 2), (17, 40, 0), (32, 256, 0), (33, 70, 0), (40, 3, 0),
+                                       (48, 130, 1), (49, 4, 0), (49, 5, 0), (64, 3, 0), (64, 64, 0)])
+def test_poa_many_windows(gpu, orc, W, m, spare):
+    """Few windows, in index order, and many, ordered by length, choose their wavefronts by other
+    rules; either side gives a window's sums, and those of the oracle."""
+    torch, rk = gpu
+    rng = np.random.default_rng([W, m, spare])
+    lens = rng.integers(1, m + 1, 10)
+    lens[0] = m
+    n, K = int(lens.sum()), (-(-m // W) + spare) if spare else 0
+    P = rng.integers(1, 300, n).astype(np.int32)
+    am = np.minimum(rng.integers(0, W, n), rng.integers(0, W, n)).astype(np.int32)
+    ov = np.floor(rng.choice((0.0, 0.25, 0.5, 0.9), size=(n, W)) * P[:, None]).astype(np.int32)
+    up, pp = rk.to_device, dict(wl.POA_PARAMS)
+    params = rk.PoaParams(pp["a"], pp["b"], pp["d"], pp["beta"], pp["C_cap"], pp["w_c"], K)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    sums = []
+    for copies in (1, 4 * cus // len(lens) + 2):
+        nw, rows = len(lens) * copies, n * copies
+        win = np.concatenate([[0], np.cumsum(np.tile(lens, copies))]).astype(np.int64)
+        sel, coo = (torch.zeros(nw, dtype=torch.float64, device="cuda") for _ in range(2))
+        hat = torch.zeros(1, dtype=torch.float64, device="cuda")
+        ws = torch.empty(rk.poa_workspace_size(rows, W), dtype=torch.uint8, device="cuda")
+        rk.poa_estimate(up(win), up(np.array([0, nw], np.int64)), rows, m, W, up(np.tile(am, copies)),
+                        up(np.tile(ov, (copies, 1))), up(np.tile(P, copies)), params, sel, coo, hat, ws)
+        torch.cuda.synchronize()
+        assert rk.device_status(reset=True) == 0
+        sums.append((sel.cpu().numpy().reshape(copies, -1), coo.cpu().numpy().reshape(copies, -1)))
+    assert len(lens) <= 2 * cus < 4 * cus < nw
+    at = np.concatenate([[0], np.cumsum(lens)])
+    for w in range(len(lens)):
+        r = slice(at[w], at[w + 1])
+        s, c, _ = orc.poa_window(am[r], ov[r], P[r], W, K=K or -(-int(lens[w]) // W), **pp)
+        for sel, coo in sums:                       # sums of at most 256 fp32 costs in fp64 on both sides
+            np.testing.assert_allclose(sel[:, w], s, rtol=1e-13)
+            np.testing.assert_allclose(coo[:, w], c, rtol=1e-13)
+
+
 def test_poa_largest_window(gpu):
     """4,096 rows on 64 workers, the most LDS a window takes: without overlaps every worker's 64 places
     are taken at its base cost."""
