@@ -298,13 +298,10 @@ __global__ __launch_bounds__(kFewThreads) void hash_few_kernel(int64_t n_seq, co
                     const int m = (int)(n - k1 < 64 ? n - k1 : 64);
                     const uint64_t f = s_f[cur][(int)(k1 - k0) + lane];
                     int lo = 0, hi = 0;
-                    // lane x keeps the value (the lane comes from m0: a VALU instruction reads one scalar)
                     auto step = [&](int x) {
                         h = chain_next(h, readlane64(f, x));
-                        asm("s_mov_b32 m0, %4\n\tv_writelane_b32 %0, %2, m0\n\tv_writelane_b32 %1, %3, m0"
-                            : "+v"(lo), "+v"(hi)
-                            : "s"((uint32_t)h), "s"((uint32_t)(h >> 32)), "s"(x)
-                            : "m0");
+                        lo = writelane32((int)(uint32_t)h, x, lo);       // lane x keeps the value
+                        hi = writelane32((int)(uint32_t)(h >> 32), x, hi);
                     };
                     int x = 0;
                     for (; x + 4 <= m; x += 4) {

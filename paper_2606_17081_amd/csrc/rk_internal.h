@@ -140,6 +140,12 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, int l)
     return ((uint64_t)hi << 32) | lo;
 }
 
+// old with lane `lane` (uniform across the wavefront) replaced by v (uniform).  The compiler has no
+// builtin for v_writelane; by the name of its intrinsic it places the instruction itself, with the
+// wait states that an instruction after one that wrote its scalar operands needs.
+extern "C" __device__ __attribute__((const, convergent)) int writelane32(int v, int lane, int old)
+    __asm("llvm.amdgcn.writelane.i32");
+
 // Inclusive prefix AND over the lanes (lane order): shifts within each row of
 // 16 lanes, then each row's total carried into the rows after it.  All lanes
 // must be active.
