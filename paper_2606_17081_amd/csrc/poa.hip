@@ -54,6 +54,7 @@ constexpr int PT = 64;   // threads of a wavefront
 constexpr int kMat = 4;  // matrix entries a lane computes together
 // a row that is not placed yet, in place of its position: it waits for a path, or any worker is as good
 constexpr int32_t kPending = -2, kAnywhere = -3;
+constexpr int32_t kNoMoves = 0x40000000;   // in place of the count of moves: the search found none
 
 struct PoaArgs {
     int32_t n_windows, max_window, W, kmax;
@@ -534,7 +535,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
                 i = pbase + __ffsll((unsigned long long)pend) - 1;
                 pend &= pend - 1;
                 --n_pend;
-            } else if (!balance || moves++ >= m + W) {
+            } else if (!balance || moves++ > m) {
                 more = false;
             }
             if constexpr (kSplit) {
@@ -725,11 +726,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
                 if (lane == 0) atomicOr(a.status, RK_DEV_NO_CONVERGE);
                 placed_all = false;
                 n_pend = 0;
-                moves = m + W;
+                moves = kNoMoves;
                 continue;
             }
             if (i < 0 && !(bd < 0.0)) {
-                moves = m + W;         // no move lowers the cost
+                moves = kNoMoves;      // no move lowers the cost
                 continue;
             }
             // walk the path back from the target, moving one row per edge; lane h
@@ -826,6 +827,11 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((
             }
             wave_sync_poa();
         }
+        // Every move is the best of all moves of one unit, and the least cost for given counts is M-convex
+        // in the counts (a transportation problem), so steepest descent reaches the nearest optimal counts
+        // by its minimizer cuts (Shioura 1998), each move one unit nearer: after m moves at most a search
+        // finds none.  One more can only come from rounding, and is reported.
+        if (tid == 0 && moves == m + 2) atomicOr(a.status, RK_DEV_NO_CONVERGE);
         if (tid == 0 && a.coord && !placed_all) a.coord[w] = __longlong_as_double(0x7ff8000000000000ll);
         if (a.coord && placed_all && wave == 0) {
             // lane G y + g adds every G-th row of worker y, then the G sums and the workers' in order
