@@ -488,6 +488,7 @@ __global__ __launch_bounds__(kBuildThreads) void table_scatter_kernel(const uint
 }
 
 // A bin from its list.  blockIdx.x: the bin, over all tables.
+template <bool PastCaches>
 __global__ __launch_bounds__(kBuildThreads) void table_bin_kernel(uint64_t* __restrict__ tables, int32_t log2_slots,
                                                                   TableSide* __restrict__ side)
 {
@@ -522,7 +523,10 @@ __global__ __launch_bounds__(kBuildThreads) void table_bin_kernel(uint64_t* __re
         }
     }
     __syncthreads();
-    for (int i = tid; i < kTabBin; i += kBuildThreads) bin[i] = s_key[i];
+    for (int i = tid; i < kTabBin; i += kBuildThreads) {
+        if constexpr (PastCaches) __builtin_nontemporal_store(s_key[i], bin + i);
+        else bin[i] = s_key[i];
+    }
 }
 
 __global__ __launch_bounds__(256) void table_spill_kernel(uint64_t* __restrict__ tables, int32_t log2_slots,
@@ -574,7 +578,10 @@ static int table_build_parts(uint64_t total, int32_t log2_slots, uint64_t* table
     const unsigned bins = (unsigned)(total >> kTabBinLog);
     hipLaunchKernelGGL(table_side_kernel, dim3((bins + 255) / 256), dim3(256), 0, s, side, (int32_t)bins);
     scatter(side);
-    hipLaunchKernelGGL(table_bin_kernel, dim3(bins), dim3(kBuildThreads), 8 * kTabBin, s, tables, log2_slots, side);
+    if (total * sizeof(uint64_t) > kCacheBytes)
+        hipLaunchKernelGGL(table_bin_kernel<true>, dim3(bins), dim3(kBuildThreads), 8 * kTabBin, s, tables, log2_slots, side);
+    else
+        hipLaunchKernelGGL(table_bin_kernel<false>, dim3(bins), dim3(kBuildThreads), 8 * kTabBin, s, tables, log2_slots, side);
     hipLaunchKernelGGL(table_spill_kernel, dim3(16), dim3(256), 0, s, tables, log2_slots, side, st);
     hipLaunchKernelGGL(table_clear_kernel, dim3(1024), dim3(256), 0, s, tables, total, &side->overrun);
     refill(side);

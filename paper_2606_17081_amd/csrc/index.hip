@@ -538,6 +538,7 @@ __global__ __launch_bounds__(kBuildThreads) void index_scatter_kernel(const uint
 }
 
 // A bin of the index from its list.
+template <bool PastCaches>
 __global__ __launch_bounds__(kBuildThreads) void index_bin_kernel(IndexSlot* __restrict__ t, int32_t log2_slots,
                                                                   BuildSide* __restrict__ side)
 {
@@ -666,10 +667,12 @@ __global__ __launch_bounds__(kBuildThreads) void index_bin_kernel(IndexSlot* __r
             if (tid == 0) atomicOr(&side->overrun, 1);
             return;
         }
-        uint4* out = reinterpret_cast<uint4*>(t + first + ((uint64_t)sb << sub_log));
+        u32x4* out = reinterpret_cast<u32x4*>(t + first + ((uint64_t)sb << sub_log));
         for (uint32_t i = tid; i < sub_slots; i += kBuildThreads) {
             const uint64_t k = s_key[i], m = s_mask[i];
-            out[i] = make_uint4((uint32_t)k, (uint32_t)(k >> 32), (uint32_t)m, (uint32_t)(m >> 32));
+            const u32x4 v = {(uint32_t)k, (uint32_t)(k >> 32), (uint32_t)m, (uint32_t)(m >> 32)};
+            if constexpr (PastCaches) __builtin_nontemporal_store(v, out + i);
+            else out[i] = v;
         }
         // keys past the sub-bin's end: on through the sub-bins after it, final by now, or out of the bin
         if (tid < kSpills && s_spk[tid] != kEmpty) {
@@ -751,7 +754,10 @@ static int index_build_parts(int32_t W, const uint64_t* keys, const KeyRanges& r
     hipLaunchKernelGGL(index_side_kernel, dim3(1), dim3(kBins), 0, s, side);
     hipLaunchKernelGGL(index_scatter_kernel, dim3((unsigned)((longest + kTile - 1) / kTile), (unsigned)W),
                        dim3(kBuildThreads), 0, s, keys, r, t, log2_slots, side, st);
-    hipLaunchKernelGGL(index_bin_kernel, dim3(kBins), dim3(kBuildThreads), 16 * kSub, s, t, log2_slots, side);
+    if (sizeof(IndexSlot) << log2_slots > kCacheBytes)
+        hipLaunchKernelGGL(index_bin_kernel<true>, dim3(kBins), dim3(kBuildThreads), 16 * kSub, s, t, log2_slots, side);
+    else
+        hipLaunchKernelGGL(index_bin_kernel<false>, dim3(kBins), dim3(kBuildThreads), 16 * kSub, s, t, log2_slots, side);
     hipLaunchKernelGGL(index_spill_kernel, dim3(1), dim3(kBins), 0, s, t, log2_slots, side, st);
     hipLaunchKernelGGL(index_clear_kernel, dim3(1024), dim3(256), 0, s, t, 1ull << log2_slots, &side->overrun);
     hipLaunchKernelGGL(index_refill_kernel, dim3(refill_blocks(r.off[W] - r.off[0])), dim3(kRefillKeys), 0, s, keys, r, W,

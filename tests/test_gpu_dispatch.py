@@ -523,3 +523,39 @@ def test_builds_on_many_streams_and_captured(gpu, layout):
             out[i].fill_(3)
             build(keys[i], off, log2, out[i])
     assert rk.device_status(reset=True) == 0
+
+
+def test_scoring_right_after_a_large_build(gpu):
+    """The first scoring of hashed requests after an index larger than the caches is built still finds
+    the requests there (before, it took 1.4 times a repeated one's time, now 1.1)."""
+    torch, rk = gpu
+    g = torch.Generator(device="cuda").manual_seed(3)
+    log2, W, B, L = 27, 64, 65536, 256
+    n = (1 << log2) // 4 // W
+    rand = lambda k: (torch.arange(1, k + 1, device="cuda") << 32) | torch.randint(  # noqa: E731
+        0, 1 << 32, (k,), generator=g, device="cuda")
+    shared = rand(256 * L).view(256, L)
+    chains = (rand(B * L) + (1 << 60)).view(B, L)
+    chains[:, : L // 2] = shared[torch.randint(0, 256, (B,), generator=g, device="cuda"), : L // 2]
+    keys = (rand(W * n) + (1 << 61)).view(W, n)
+    keys[:, : shared.numel()] = shared.view(-1)
+    off, chains = torch.arange(B + 1, device="cuda") * L, chains.reshape(-1)
+    active = torch.zeros(W, dtype=torch.int32, device="cuda")
+    keys, key_off = keys.reshape(-1), np.arange(W + 1, dtype=np.int64) * n
+    index = rk.index_build(keys, key_off, log2)
+    ov, cost, am = rk.route_score_index(chains, off, index, log2, active)
+    assert (ov == L // 2).all()
+    first, again = [], []
+    for _ in range(9):
+        rk.index_build(keys, key_off, log2, index)
+        for t in (first, again):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            rk.route_score_index(chains, off, index, log2, active, overlap=ov, cost=cost, argmin=am)
+            b.record()
+            torch.cuda.synchronize()
+            t.append(a.elapsed_time(b) * 1e3)
+    first, again = sorted(first)[4], sorted(again)[4]
+    say("first", first, "us, again", again, "us")
+    assert rk.device_status(reset=True) == 0
+    assert first < 1.25 * again
