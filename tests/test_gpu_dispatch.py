@@ -253,6 +253,66 @@ def test_index_build_partitioned(gpu, log2, W, kind):
         assert (holes[at] == holes[home]).all()
 
 
+def _assert_index(torch, keys, off, log2, out):
+    """The index holds the key sets and nothing else, every key in its probe order from its home slot."""
+    W = len(off) - 1
+    worker = torch.repeat_interleave(torch.arange(W, device="cuda"), torch.from_numpy(np.diff(off)).cuda())
+    want, at = torch.unique(keys, return_inverse=True)
+    mask = torch.zeros_like(want).index_add_(0, at, torch.ones_like(worker) << worker)    # (no pair twice)
+    slot = torch.nonzero(out.view(-1, 2)[:, 0]).flatten()
+    key, k = torch.sort(out.view(-1, 2)[slot, 0])
+    assert torch.equal(key, want) and torch.equal(out.view(-1, 2)[slot, 1][k], mask)
+    empty = out.view(-1, 2)[:, 0] == 0
+    assert not (out.view(-1, 2)[:, 1] != 0).logical_and_(empty).any()
+    holes = torch.cumsum(empty, 0, dtype=torch.int32)         # empty slots up to each
+    home, total = out.view(-1, 2)[slot, 0] & ((1 << log2) - 1), holes[-1]
+    wrapped = (slot < home).int()
+    assert torch.equal(holes[slot] + wrapped * total, holes[home] - empty[home].int())
+
+
+# low bits of keys that every worker holds (shared) and of the first worker's own; what they reach
+_CROWDED = {
+    "64 past a sub-bin's end": lambda lg: ([8191] * 5, [8191] * 60),
+    "65 past a sub-bin's end": lambda lg: ([8191] * 5, [8191] * 61),
+    "64 out of a bin": lambda lg: ([], [*range(8192, 16384), *[16383] * 30, *[8191] * 35]),
+    "65 out of a bin": lambda lg: ([], [*range(8192, 16384), *[16383] * 30, *[8191] * 36]),
+    "through three sub-bins": lambda lg: ([], [*range(8192, 24576), *[8191] * 50, *[24575] * 20]),
+    "out of the index": lambda lg: ([(1 << lg) - 1] * 9, [(1 << lg) - 2] * 30),
+    "a first sub-bin's entries to the limit": lambda lg: ([7 + 30 * i for i in range(256)], []),
+    "a first sub-bin's entries past it": lambda lg: ([7 + 30 * i for i in range(257)], []),
+}
+
+
+@pytest.mark.parametrize("log2,W,kind", [
+    (25, 64, "uniform"), (25, 3, "uniform"), (29, 2, "uniform"),
+    (22, 9, "64 past a sub-bin's end"), (22, 9, "65 past a sub-bin's end"), (22, 1, "64 out of a bin"),
+    (22, 1, "65 out of a bin"), (25, 2, "through three sub-bins"), (22, 9, "out of the index"),
+    (29, 9, "out of the index"), (23, 64, "a first sub-bin's entries to the limit"),
+    (23, 64, "a first sub-bin's entries past it")])
+def test_index_build_sub_bins(gpu, log2, W, kind):
+    """The partitioned index with 2 to 256 sub-bins of 8,192 slots in each of its 256 bins: uniform keys,
+    and keys that fill what may pass an end (64 keys) or lie before a sub-bin's place (16,384 entries),
+    or run it over by one, which is found after other bins have been written."""
+    torch, rk = gpu
+    g = torch.Generator(device="cuda").manual_seed(log2 + W)
+    if kind == "uniform":
+        n = min((1 << log2) // 2, 1 << 24) // W
+        low = torch.randint(0, 1 << 32, (W * n,), generator=g, device="cuda")
+        keys, off = (torch.arange(1, W * n + 1, device="cuda") << 32) | low, np.arange(W + 1, dtype=np.int64) * n
+    else:
+        shared, own = (torch.tensor(x, dtype=torch.int64, device="cuda") for x in _CROWDED[kind](log2))
+        number = torch.randperm(shared.numel() + own.numel(), generator=g, device="cuda") + 1
+        shared, own = shared | number[: shared.numel()] << 32, own | number[shared.numel():] << 32
+        keys = torch.cat([own] + [shared[torch.randperm(shared.numel(), generator=g, device="cuda")] for _ in range(W)])
+        off = np.concatenate([[0], own.numel() + shared.numel() * np.arange(1, W + 1)]).astype(np.int64)
+    out = torch.full((2 << log2,), 5, dtype=torch.int64, device="cuda")
+    for _ in range(2):
+        rk.index_build(keys, off, log2, out)
+        torch.cuda.synchronize()
+        assert rk.device_status(reset=True) == 0
+        _assert_index(torch, keys, off, log2, out)
+
+
 def test_index_build_streams_and_capture(gpu):
     """Builds on several streams at once, and one captured into a graph, give the same index."""
     torch, rk = gpu
@@ -284,16 +344,25 @@ def test_index_build_streams_and_capture(gpu):
     assert rk.device_status(reset=True) == 0
 
 
-@pytest.mark.parametrize("log2,W,kind", [(14, 70, "uniform"), (15, 70, "uniform"), (15, 32, "ends"), (16, 16, "dense"),
-                                         (18, 4, "skewed"), (20, 3, "uniform"), (22, 1, "zeros"), (23, 1, "uniform"),
-                                         (17, 66, "few")])
+@pytest.mark.parametrize("log2,W,kind", [(14, 140, "uniform"), (15, 63, "uniform"), (15, 70, "uniform"), (15, 64, "ends"),
+                                         (16, 32, "dense"), (18, 8, "skewed"), (20, 3, "uniform"), (22, 1, "zeros"),
+                                         (23, 1, "uniform"), (17, 66, "few"), (15, 64, "500 past an end"),
+                                         (15, 64, "600 past an end")])
 def test_table_build_partitioned(gpu, log2, W, kind):
-    """Tables of 2^15 to 2^22 slots, a million in all, are partitioned and built in LDS: every key of a
-    worker in its probe order from its home slot, at load 0.5 or below."""
+    """Tables of 2^15 to 2^22 slots, 2^21 in all or more, are partitioned and built in LDS, others by
+    atomics: every key of a worker in its probe order from its home slot, at load 0.5 or below.  Of the
+    partitioned ones, "dense" fills bins' lists to the last entry, "skewed" runs one over, and the keys
+    past the bins' ends fill their buffer (2^15) almost, or run it over."""
     torch, rk = gpu
     rng = np.random.default_rng([log2, W, 3])
     slots = 1 << log2
+    assert (15 <= log2 <= 22 and W * slots >= 1 << 21) == ((log2, W) not in ((14, 140), (15, 63), (23, 1)))
     n = np.full(W, slots // 2)
+    if kind == "skewed":
+        n = np.full(W, 20000)                       # in the first of the 2^14 slots of a bin
+    if "past" in kind:
+        n = np.full(W, int(kind[:3]))
+        assert (W * (n[0] - 1) > 1 << 15) == (kind[:3] == "600")
     if kind == "few":
         n = rng.integers(0, 5, W)
     if kind == "ends":
@@ -306,12 +375,14 @@ def test_table_build_partitioned(gpu, log2, W, kind):
         low = (rng.integers(0, slots >> 13, off[-1], dtype=np.uint64) << np.uint64(13)) + np.uint64(8185)
     elif kind == "skewed":
         low = rng.integers(0, slots >> 5, off[-1], dtype=np.uint64)
+    elif "past" in kind:
+        low = np.full(off[-1], (1 << 14) - 1, np.uint64)
     else:
         low = rng.integers(0, 2 ** 32, off[-1], dtype=np.uint64)
     keys = hi | low
     if kind == "zeros":
         keys[rng.random(keys.size) < 0.001] = 0
-    if off[-1] > 10 and W > 1:
+    if off[-1] > 10 and W > 1 and "past" not in kind:
         keys[off[1] - 1] = keys[off[0]]             # a worker's key twice
     up = rk.to_device(keys)
     for fill in (-1, 5):
