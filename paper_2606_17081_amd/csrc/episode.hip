@@ -295,66 +295,33 @@ __device__ __forceinline__ bool finish_lookup(const Slot* t, uint64_t smask, uin
     return finish_lookup_stamp(t, smask, h, s, k, st, stamp);
 }
 
-constexpr int32_t kFullProbe = 64;   // intervals this wide are probed position by position
-
-// Positions sampled in a round over an interval of `span` > kFullProbe blocks:
-// about sqrt(span), so two rounds cover span with few probes, and at most 64
-// so that the next interval fits one round when span <= 64 * 64.
-__device__ __forceinline__ int32_t fanout(int32_t span)
-{
-    int32_t f = (int32_t)ceilf(sqrtf((float)span));
-    f = f < 4 ? 4 : f;
-    f = f > 64 ? 64 : f;
-    return span > 64 * f ? 64 : f;     // the next interval, at most ceil(span / f) wide, fits 64
-}
-
-// Longest cached prefix of the staged chain on the workers j = jfirst,
-// jfirst + jstride, ... (< W) handled by this wavefront; worker jspecial's
-// search starts at block lo_special (its blocks below are known cached).
-// Every round issues, per lane, one probe (two adjacent slots) for each
-// unresolved worker before any result is used, so all of the wavefront's
-// probes are in flight together.
-//   PREFIX mode (caches prefix-closed along the chain): while an interval is
-//   wider than kFullProbe a round probes spread positions and keeps the
-//   sub-interval holding the first miss; the last round probes every position.
-//   SCAN mode: rounds probe blocks [lo, lo + 64) from block 0 on.
+// First block of the chain that worker j lacks, for j = jfirst .. jend - 1 (JPW at most), by one
+// wavefront: rounds probe blocks [lo, lo + 64) from block 0 on (the caches need not be prefix-closed).
+// Every round issues, per lane, one probe for each unresolved worker before any result is used, so
+// all of the wavefront's probes are in flight together.
 template <int JPW>
-__device__ void wave_overlaps(const uint64_t* s_chain, int32_t P, int32_t jfirst, int32_t jstride, int32_t W,
-                              const Slot* slots, uint64_t S, int mode, int32_t* s_ov, int32_t jspecial,
-                              int32_t lo_special)
+__device__ void scan_overlaps(const uint64_t* chain, int32_t P, int32_t jfirst, int32_t jend, const Slot* slots,
+                              uint64_t S, int32_t* s_ov)
 {
     const int lane = threadIdx.x & 63;
     const uint64_t smask = S - 1;
-    int32_t lo[JPW], hi[JPW];
+    int32_t lo[JPW];
     uint32_t open = 0;
 #pragma unroll
     for (int jj = 0; jj < JPW; ++jj) {
-        const int32_t j = jfirst + jj * jstride;
-        lo[jj] = j == jspecial ? lo_special : 0;
-        hi[jj] = P;
-        if (j < W) open |= 1u << jj;
+        lo[jj] = 0;
+        if (jfirst + jj < jend) open |= 1u << jj;
     }
     while (open) {
         uint64_t hk[JPW], kw[JPW][kWin], sh0[JPW];
         uint32_t sw[JPW][kWin];
-        int32_t q[JPW];
         bool valid[JPW];
 #pragma unroll
         for (int jj = 0; jj < JPW; ++jj) {
-            valid[jj] = false;
-            if (!((open >> jj) & 1u)) continue;
-            const int32_t span = hi[jj] - lo[jj];
-            if (mode == RK_PROBE_PREFIX && span > kFullProbe) {
-                const uint32_t f = (uint32_t)fanout(span);
-                q[jj] = lo[jj] + (int32_t)(((uint32_t)(lane + 1) * (uint32_t)span) / f) - 1;
-                valid[jj] = (uint32_t)lane < f;
-            } else {
-                q[jj] = lo[jj] + lane;
-                valid[jj] = q[jj] < hi[jj];
-            }
+            valid[jj] = ((open >> jj) & 1u) && lo[jj] + lane < P;
             if (valid[jj]) {
-                const Slot* t = slots + (uint64_t)(jfirst + jj * jstride) * S;
-                hk[jj] = s_chain[q[jj]];
+                const Slot* t = slots + (uint64_t)(jfirst + jj) * S;
+                hk[jj] = chain[lo[jj] + lane];
                 sh0[jj] = home_slot(hk[jj], smask);
 #pragma unroll
                 for (int i = 0; i < kWin; ++i) load_slot(t + sh0[jj] + group_slot(hk[jj], i), kw[jj][i], sw[jj][i]);
@@ -364,36 +331,16 @@ __device__ void wave_overlaps(const uint64_t* s_chain, int32_t P, int32_t jfirst
         for (int jj = 0; jj < JPW; ++jj) {
             if (!((open >> jj) & 1u)) continue;
             bool hit = true;
-            if (valid[jj]) {
-                const Slot* t = slots + (uint64_t)(jfirst + jj * jstride) * S;
-                hit = finish_lookup(t, smask, hk[jj], sh0[jj], kw[jj], sw[jj]);
-            }
+            if (valid[jj])
+                hit = finish_lookup(slots + (uint64_t)(jfirst + jj) * S, smask, hk[jj], sh0[jj], kw[jj], sw[jj]);
             const unsigned long long miss = __ballot(valid[jj] && !hit);
-            const int32_t span = hi[jj] - lo[jj];
             int32_t o = -1;
-            if (mode == RK_PROBE_PREFIX && span > kFullProbe) {
-                if (miss == 0ull) {
-                    o = hi[jj];
-                } else {
-                    // lane t holds the first missing sample; lanes t and t-1 computed its bounds
-                    const int t = __ffsll(miss) - 1;
-                    const int32_t qt = __shfl(q[jj], t, 64);
-                    const int32_t qprev = __shfl(q[jj], t > 0 ? t - 1 : 0, 64);
-                    const int32_t qp = t == 0 ? lo[jj] - 1 : qprev;
-                    lo[jj] = qp + 1;
-                    hi[jj] = qt;
-                    if (hi[jj] == lo[jj]) o = lo[jj];
-                }
-            } else if (mode == RK_PROBE_PREFIX) {
-                o = miss ? lo[jj] + __ffsll(miss) - 1 : hi[jj];
-            } else {
-                if (miss) o = lo[jj] + __ffsll(miss) - 1;
-                else if (lo[jj] + 64 >= hi[jj]) o = hi[jj];
-                else lo[jj] += 64;
-            }
+            if (miss) o = lo[jj] + __ffsll(miss) - 1;
+            else if (lo[jj] + 64 >= P) o = P;
+            else lo[jj] += 64;
             if (o >= 0) {
                 open &= ~(1u << jj);
-                if (lane == 0) s_ov[jfirst + jj * jstride] = o;
+                if (lane == 0) s_ov[jfirst + jj] = o;
             }
         }
     }
@@ -436,64 +383,14 @@ __device__ __forceinline__ uint64_t insert_or_touch(Slot* __restrict__ t, uint64
     return ~0ull;
 }
 
-// Same result as insert_or_touch, in one memory round trip in the usual
-// case.  A block the overlap search found cached is looked up in its group.
-// For a block past the overlap, the claim of the first slot of its order is
-// issued together with the loads of the group's other slots: an empty first
-// slot proves the key absent (slots never return to empty between
-// compactions, and an insert of the key would have taken it), and an occupied
-// one usually leaves a free slot further along the group.  Anything else falls
-// back to the full walk.
-__device__ __forceinline__ uint64_t touch_hinted(Slot* __restrict__ t, uint64_t smask, uint64_t h, bool cached_hint,
-                                                 int& inserted, int32_t* status)
-{
-    const uint64_t s = home_slot(h, smask);
-    inserted = 0;
-    uint64_t k[kWin];
-    uint32_t st[kWin];
-    if (cached_hint) {
-#pragma unroll
-        for (int r = 0; r < kWin; ++r) load_slot(t + s + group_slot(h, r), k[r], st[r]);
-#pragma unroll
-        for (int r = 0; r < kWin; ++r)
-            if (k[r] == h && st[r] != kTomb) return s + group_slot(h, r);
-    } else {
-        uint64_t prev = kEmpty;
-        const uint64_t s0 = s + group_slot(h, 0);
-        const bool won = __hip_atomic_compare_exchange_strong(&t[s0].key, &prev, h, __ATOMIC_RELAXED,
-                                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-#pragma unroll
-        for (int r = 1; r < kWin; ++r) load_slot(t + s + group_slot(h, r), k[r], st[r]);
-        if (won) {
-            inserted = 1;
-            return s0;
-        }
-        if (prev != h) {           // the first slot holds another key: look further along the group
-#pragma unroll
-            for (int r = 1; r < kWin; ++r) {
-                const uint64_t si = s + group_slot(h, r);
-                if (k[r] == h) {
-                    if (st[r] != kTomb) return si;
-                    continue;
-                }
-                if (k[r] != kEmpty) continue;
-                uint64_t pi = kEmpty;
-                if (__hip_atomic_compare_exchange_strong(&t[si].key, &pi, h, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_WORKGROUP)) {
-                    inserted = 1;
-                    return si;
-                }
-                break;             // lost a race for the slot: walk from the start
-            }
-        }
-    }
-    return insert_or_touch(t, smask, h, inserted, status);
-}
-
-
-// touch_hinted for two keys of a lane at once (act: the key is to be touched;
-// hint as there; fkey: the frequency key seen at a hit, else 0), the claims
-// (compare-and-swap returning the slot's previous key) and group loads of both issued before either result is used.
+// Same result as insert_or_touch for two keys of a lane at once (act: the key is to be touched; fkey:
+// the frequency key seen at a hit, else 0), in one memory round trip in the usual case.  A block the
+// overlap search found cached (hint) is looked up in its group.  For a block past the overlap, the
+// claim of the first slot of its order (a compare-and-swap returning the slot's previous key) is issued
+// together with the loads of the group: an empty first slot proves the key absent (slots never return
+// to empty between compactions, and an insert of the key would have taken it), and an occupied one
+// usually leaves a free slot further along the group.  Anything else falls back to the full walk.  The
+// claims and group loads of both keys are issued before either result is used.
 __device__ __forceinline__ void touch_hinted2(Slot* const* t, uint64_t smask, const uint64_t* h, const bool* hint,
                                               const bool* act, uint64_t* sl, int* ins, uint32_t* fkey, int32_t* status)
 {
@@ -563,9 +460,9 @@ __device__ __forceinline__ void touch_hinted2(Slot* const* t, uint64_t smask, co
 
 constexpr int kRU = 4;   // touches a thread keeps in flight while a worker's recency is rebuilt
 
-// touch_hinted(t, smask, h[u], false, ...) for kRU keys (kEmpty: none) with the
-// claims and group loads of all of them issued before any result is used; the
-// slot of each key (~0 if none) goes to sl.
+// touch_hinted2 without hints for kRU keys of one table (kEmpty: none), the claims
+// and group loads of all of them issued before any result is used; the slot of
+// each key (~0 if none) goes to sl.
 __device__ __forceinline__ void touch_batch(Slot* __restrict__ t, uint64_t smask, const uint64_t* h, uint64_t* sl,
                                             int32_t* status)
 {
@@ -2643,10 +2540,9 @@ __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
                 const uint64_t* ch = a.chains + r_cb[b];
                 if (j < 0) {
                     for (int32_t jb = 0; jb < W; jb += 4)
-                        wave_overlaps<4>(ch, r_P[b], jb, 1, min(W, jb + 4), g_slots, S, RK_PROBE_SCAN, o_tab + b * W,
-                                         -1, 0);
+                        scan_overlaps<4>(ch, r_P[b], jb, min(W, jb + 4), g_slots, S, o_tab + b * W);
                 } else {
-                    wave_overlaps<1>(ch, r_P[b], j, 1, j + 1, g_slots, S, RK_PROBE_SCAN, o_tab + b * W, -1, 0);
+                    scan_overlaps<1>(ch, r_P[b], j, j + 1, g_slots, S, o_tab + b * W);
                 }
             }
             __syncthreads();

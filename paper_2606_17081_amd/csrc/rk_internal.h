@@ -176,7 +176,7 @@ __device__ __forceinline__ int32_t wave_excl_sum_dpp(int32_t v, int32_t& total)
     return (int32_t)x - v;
 }
 
-// Minimum / OR of v over the lanes, the same value in every lane: a butterfly
+// Minimum of v over the lanes, the same value in every lane: a butterfly
 // within each row of 16 (pair swap, quad swap, half-row mirror, row mirror),
 // then the four row results.  All lanes must be active.
 __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v)
@@ -187,15 +187,6 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v)
     v = mn(v, dpp64<kDppRowHalfMirror>(v, v));
     v = mn(v, dpp64<kDppRowMirror>(v, v));
     return mn(mn(readlane64(v, 0), readlane64(v, 16)), mn(readlane64(v, 32), readlane64(v, 48)));
-}
-
-__device__ __forceinline__ uint64_t wave_or_u64(uint64_t v)
-{
-    v |= dpp64<kDppQuadSwap1>(v, v);
-    v |= dpp64<kDppQuadSwap2>(v, v);
-    v |= dpp64<kDppRowHalfMirror>(v, v);
-    v |= dpp64<kDppRowMirror>(v, v);
-    return (readlane64(v, 0) | readlane64(v, 16)) | (readlane64(v, 32) | readlane64(v, 48));
 }
 
 // Sum of v over the lanes, the same value in every lane.  All lanes must be active.
@@ -235,20 +226,6 @@ __device__ __forceinline__ int32_t wave_sum_i32(int32_t v)
     x += dpp32<kDppRowMirror>(x, x);
     return (int32_t)(((uint32_t)__builtin_amdgcn_readlane((int)x, 0) + (uint32_t)__builtin_amdgcn_readlane((int)x, 16)) +
                      ((uint32_t)__builtin_amdgcn_readlane((int)x, 32) + (uint32_t)__builtin_amdgcn_readlane((int)x, 48)));
-}
-
-// ------------------------------------------------- read-only table probes
-// Open addressing, home slot key & mask, linear probing; 0 is empty.
-__device__ __forceinline__ bool table_has(const uint64_t* __restrict__ t, uint64_t mask, uint64_t key)
-{
-    uint64_t s = key & mask;
-    for (uint64_t n = 0; n <= mask; ++n) {
-        uint64_t k = t[s];
-        if (k == key) return true;
-        if (k == kEmpty) return false;
-        s = (s + 1) & mask;
-    }
-    return false;
 }
 
 // ------------------------------------------------- building tables and indexes
