@@ -278,8 +278,7 @@ int rk_route_score_index(int32_t B, int32_t W, const uint64_t* chains, const int
  *     cost's prefill term becomes, in fp32 and this order,
  *       ((((float)(P - o) + tier_w[0] * o1) + tier_w[1] * (o12 - o1))
  *        + tier_w[2] * (o - o12));
- *     every route then stops the batch (as in RK_PROBE_SCAN) so that later
- *     requests see the new tier boundaries.
+ *     later requests see the boundaries as the route leaves them.
  * The queue order, the touch order and the tie rule make every result unique.
  */
 typedef struct {

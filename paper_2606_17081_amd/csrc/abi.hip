@@ -329,7 +329,7 @@ __global__ __launch_bounds__(kFewThreads) void hash_few_kernel(int64_t n_seq, co
 // bin in LDS and writes it over the list.  Keys that probe past a bin's end wait
 // in a side buffer until every bin is built; what does not fit sets a flag that
 // makes the last two launches build the tables by atomics.
-// 64 tables of 2^20 slots from 33.6 M keys: 2.92 -> 0.46 ms; a quarter full, 1.18 -> 0.27 ms.  One launch for
+// 64 tables of 2^20 slots from 33.6 M keys: 2.87 -> 0.43 ms; a quarter full, 1.19 -> 0.20 ms.  One launch for
 // all workers, by atomics or not, takes the place of one for each (64 tables of 2^14 slots: 678 -> 47 us).
 constexpr int kTabBinLog = 14, kTabBin = 1 << kTabBinLog;
 constexpr int kTabLogMin = 15, kTabLogMax = 22;

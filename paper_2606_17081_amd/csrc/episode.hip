@@ -29,10 +29,13 @@
 //      elsewhere.  The cache writes themselves are deferred;
 //   C. meanwhile the other wavefronts apply the touches and inserts of
 //      the decided routes, a few routes per claim.
-// A route that must evict (and every route in scan mode, where caches need
-// not be prefix-closed) stops phase B: once every decided route's writes are
-// in, blocks are evicted and the pending requests searched again on that
-// worker.
+// A route that must evict leaves its worker unsettled.  The decisions go on
+// until a request holds blocks on an unsettled worker or is routed to one, or
+// the batch ends (an eviction only cuts suffixes off cached prefixes, so a
+// request with no block there is not concerned).  Then, with every decided
+// route's writes in, the unsettled workers are settled side by side, a
+// wavefront each, and the pending requests looked up again on them.  In scan
+// mode, where caches need not be prefix-closed, every route stops phase B.
 //
 // Recency is kept lazily under LRU: until a worker first has to evict, its
 // stamps decide nothing, so the writers only insert the blocks it lacks (no
@@ -65,8 +68,8 @@
 // in it (the writers count those from the stamps atomicMax returns); the
 // boundary then walks forward over surplus live records.  Along a cached
 // prefix the stamps fall, so the tier overlaps o1 and o12 are found by binary
-// search on stamps.  Every route stops the batch so that later requests are
-// searched against the new boundaries.
+// search on stamps.  Every route leaves its worker unsettled, as an eviction
+// does, and the boundaries move when the worker is settled.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -1190,15 +1193,6 @@ __global__ void episode_queue_init(int32_t* __restrict__ q)
     if (threadIdx.x == 0) *q = 0;
 }
 
-// Two waves per SIMD: two episodes of 256 threads share a CU, or one of 512 threads has it.
-// With one workspace per episode, workgroup x runs episode x.  With fewer
-// workspaces (n_slots < E), workgroup x owns workspace x and takes episodes from
-// the launch's queue counter in index order until none is left.  An episode
-// clears what it uses of its workspace itself, so no launch needs the
-// workspace cleared beforehand.
-// The queued loop is a kernel of its own (Queued = true): a loop around the
-// episode keeps more values live across it, and the one-episode kernel keeps
-// its register allocation.
 // ------------------------------------------------- the decision loop
 // LDS and global memory from code outside the kernel body: a 32-bit LDS address, a global address.
 template <typename T>
@@ -1688,6 +1682,16 @@ __device__ __noinline__ void decide_routes(uint32_t sh_off_arg)
     }
 }
 
+// ------------------------------------------------- the episode
+// Two waves per SIMD: two episodes of 256 threads share a CU, or one of 512 threads has it.
+// With one workspace per episode, workgroup x runs episode x.  With fewer
+// workspaces (n_slots < E), workgroup x owns workspace x and takes episodes from
+// the launch's queue counter in index order until none is left.  An episode
+// clears what it uses of its workspace itself, so no launch needs the
+// workspace cleared beforehand.
+// The queued loop is a kernel of its own (Queued = true): a loop around the
+// episode keeps more values live across it, and the one-episode kernel keeps
+// its register allocation.
 template <bool Queued, int NT>
 __global__ __launch_bounds__(NT, 2) void episode_kernel(EpArgs a)
 {

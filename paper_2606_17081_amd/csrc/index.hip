@@ -395,8 +395,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8))) void sc
 // (its graph may run at any time), the keys are inserted by atomics, all workers
 // in one launch.
 //
-// 33.6 M keys of 64 workers into 2^27 slots (2 GiB): 4.22 -> 0.91 ms (the keys read twice and written twice, the
-// index written once: 3.5 GB, 3.8 TB/s; a large copy moves 4.8).
+// 33.6 M keys of 64 workers into 2^27 slots (2 GiB): 4.22 -> 0.81 ms (the keys read twice and written twice, the
+// index written once: 3.5 GB, 4.3 TB/s; a large copy moves 4.8); twice the keys 9.90 -> 1.49 ms.
 constexpr int kPartLog = 20;              // smallest index that is partitioned (below: 20-40 us by atomics)
 constexpr int kBinLog = 8, kBins = 1 << kBinLog;
 constexpr int kSubLog = 13, kSub = 1 << kSubLog;
