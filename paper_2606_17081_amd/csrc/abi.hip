@@ -367,7 +367,8 @@ __device__ __forceinline__ bool table_insert(uint64_t* t, uint64_t mask, uint64_
 {
     for (uint64_t probe = 0; probe <= mask; ++probe) {
         uint64_t seen = kEmpty;
-        if (probe >= kReads) seen = __hip_atomic_load(&t[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if constexpr (kReads != kNoReads)
+            if (probe >= kReads) seen = __hip_atomic_load(&t[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         if (seen == key) return true;
         if (seen == kEmpty) {
             const unsigned long long prev = atomicCAS((unsigned long long*)&t[s], (unsigned long long)kEmpty,

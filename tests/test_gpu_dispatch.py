@@ -347,7 +347,7 @@ def test_index_build_streams_and_capture(gpu):
 @pytest.mark.parametrize("log2,W,kind", [(14, 140, "uniform"), (15, 63, "uniform"), (15, 70, "uniform"), (15, 64, "ends"),
                                          (16, 32, "dense"), (18, 8, "skewed"), (20, 3, "uniform"), (22, 1, "zeros"),
                                          (23, 1, "uniform"), (17, 66, "few"), (15, 64, "500 past an end"),
-                                         (15, 64, "600 past an end")])
+                                         (15, 64, "600 past an end"), (15, 70, "600 past an end")])
 def test_table_build_partitioned(gpu, log2, W, kind):
     """Tables of 2^15 to 2^22 slots, 2^21 in all or more, are partitioned and built in LDS, others by
     atomics: every key of a worker in its probe order from its home slot, at load 0.5 or below.  Of the
