@@ -598,7 +598,7 @@ def test_builds_on_many_streams_and_captured(gpu, layout):
 
 def test_scoring_right_after_a_large_build(gpu):
     """The first scoring of hashed requests after an index larger than the caches is built still finds
-    the requests there (before, it took 1.4 times a repeated one's time, now 1.1)."""
+    the requests there (before, it took 1.3 times a repeated one's time)."""
     torch, rk = gpu
     g = torch.Generator(device="cuda").manual_seed(3)
     log2, W, B, L = 27, 64, 65536, 256
